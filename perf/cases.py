@@ -27,27 +27,27 @@ MOST_WEIGHTS = 8192 * 57344
 def listed():
     return [
         # the smallest call: one token through LLaMA-2-7B's attention output projection, fp16 in, fp16 out
-        dict(name="linear 7b o, 1 token", kind="linear", feed="fp16", M=1, K=4096, N=4096, bits=8, group=0),
+        dict(name="linear 7b o 1 token", kind="linear", feed="fp16", M=1, K=4096, N=4096, bits=8, group=0),
         # batched decode of a program with a norm of its own in front: LLaMA-2-70B's fused QKV at 16 tokens
-        dict(name="linear 70b qkv, 16 tokens", kind="linear", feed="norm", M=16, K=8192, N=10240, bits=6, group=0),
+        dict(name="linear 70b qkv 16 tokens", kind="linear", feed="norm", M=16, K=8192, N=10240, bits=6, group=0),
         # token generation, one request: a 70B decoder block, 6 bits and 8 on the down projection
-        dict(name="block 70b, 1 token", kind="block", model="70b", M=1, bits="6668", group=0),
+        dict(name="block 70b 1 token", kind="block", model="70b", M=1, bits="6668", group=0),
         # token generation, eight requests: a 7B decoder block with 8-bit activations throughout
-        dict(name="block 7b, 8 tokens", kind="block", model="7b", M=8, bits="8888", group=0),
+        dict(name="block 7b 8 tokens", kind="block", model="7b", M=8, bits="8888", group=0),
         # batched decode of the 13B stack, group-128 weight scales
-        dict(name="block 13b g128, 32 tokens", kind="block", model="13b", M=32, bits="6666", group=128),
+        dict(name="block 13b g128 32 tokens", kind="block", model="13b", M=32, bits="6666", group=128),
         # a large decode batch or a short prompt: 70B's down projection behind the gated SiLU, an odd token count
-        dict(name="linear 70b down, 97 tokens", kind="linear", feed="swiglu", M=97, K=28672, N=8192, bits=8, group=0),
+        dict(name="linear 70b down 97 tokens", kind="linear", feed="swiglu", M=97, K=28672, N=8192, bits=8, group=0),
         # nothing a multiple of a tile: a prompt of 333 tokens on a layer of 427 row blocks and 41 groups
-        dict(name="linear ragged, 333 tokens", kind="linear", feed="fp16", M=333, K=5248, N=13664, bits=6, group=0),
+        dict(name="linear ragged 333 tokens", kind="linear", feed="fp16", M=333, K=5248, N=13664, bits=6, group=0),
         # a medium prompt: 70B's fused QKV at 1024 tokens
-        dict(name="linear 70b qkv, 1024 tokens", kind="linear", feed="fp16", M=1024, K=8192, N=10240, bits=6, group=0),
+        dict(name="linear 70b qkv 1024 tokens", kind="linear", feed="fp16", M=1024, K=8192, N=10240, bits=6, group=0),
         # prefill with one scale per group on both operands: 13B's down projection at an odd token count
-        dict(name="xgroup 13b down, 700 tokens", kind="xgroup", M=700, K=13824, N=5120, bits=8),
+        dict(name="xgroup 13b down 700 tokens", kind="xgroup", M=700, K=13824, N=5120, bits=8),
         # prefill of the 13B stack, group-128 weight scales, a layer that runs 8 bits throughout
-        dict(name="block 13b g128, 2048 tokens", kind="block", model="13b", M=2048, bits="8888", group=128),
+        dict(name="block 13b g128 2048 tokens", kind="block", model="13b", M=2048, bits="8888", group=128),
         # the largest: prefill of a 70B decoder block
-        dict(name="block 70b, 4096 tokens", kind="block", model="70b", M=4096, bits="6668", group=0),
+        dict(name="block 70b 4096 tokens", kind="block", model="70b", M=4096, bits="6668", group=0),
         # loading a checkpoint: one 70B attention output projection quantized and packed
         dict(name="pack 70b o", kind="pack", N=8192, K=8192, group=0),
     ]
