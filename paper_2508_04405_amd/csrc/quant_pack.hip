@@ -12,26 +12,15 @@
 
 namespace {
 
-__device__ __forceinline__ float block_max(float v, float *red)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        v = fmaxf(v, __shfl_xor(v, off, 64));
-    const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if (nw == 1) return v;
-    if ((threadIdx.x & 63) == 0) red[wave] = v;
-    __syncthreads();
-    float m = red[0];
-    for (int i = 1; i < nw; ++i) m = fmaxf(m, red[i]);
-    __syncthreads();
-    return m;
-}
+// A row's floats and codes are moved four at a time; the caller's pointers need no more
+// than the alignment of one element, which the types say and the hardware accepts.
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned codes4_any __attribute__((aligned(1)));
 
 // fp16 scale of a group from its absmax, and the float the codes divide by.
-__device__ __forceinline__ void make_scale(float amax, float qmax, uint16_t &bits, float &sf)
+__device__ __forceinline__ void make_scale(float amax, uint16_t &bits, float &sf)
 {
-    float s32 = amax / qmax;
-    bits = f2h(s32);
+    bits = f2h(amax / 31.0f);
     sf = h2f(bits);
     if (amax == 0.0f || sf == 0.0f) {
         bits = 0x3c00;
@@ -39,41 +28,123 @@ __device__ __forceinline__ void make_scale(float amax, float qmax, uint16_t &bit
     }
 }
 
-__device__ __forceinline__ int quant_code(float v, float sf, float qmin, float qmax)
+// Four codes clamp(rne(v / sf), -32, 31).  div_by gives the IEEE quotient of any float here:
+// sf has eleven significant bits, so its remainder is exact and the quotient is never closer
+// to a rounding boundary than 2^-12 ulp, far outside the correction's error (a quotient that
+// underflows rounds to code 0 either way).  A scale that overflowed fp16 is infinite and
+// every quotient 0: sf = 1, rf = 0 give that.
+__device__ __forceinline__ unsigned quant4(const float4_any &v, float sf, float rf)
 {
-    float q = __builtin_rintf(v / sf);
-    q = fminf(fmaxf(q, qmin), qmax);
-    return (int)q;
+    unsigned out = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(div_by(v[i], sf, rf)), -32.0f, 31.0f);
+        out = __builtin_amdgcn_cvt_pk_u8_f32(q + 128.0f, i, out);
+    }
+    return out ^ 0x80808080u;
 }
 
-// One block per (row, group): fp32 in, 6-bit codes out.
-__global__ void quant_w6_kernel(const float *__restrict__ w, int K, int G, int8_t *__restrict__ wq,
-                                uint16_t *__restrict__ sw)
+__device__ __forceinline__ void reciprocal(float &sf, float &rf)
 {
-    __shared__ float red[16];
-    const int groups = K / G;
-    const long unit = blockIdx.x;
-    const long row = unit / groups, g = unit % groups;
-    const float *src = w + row * K + g * G;
-    int8_t *dst = wq + row * K + g * G;
+    rf = 1.0f / sf;
+    if (rf == 0.0f) sf = 1.0f;
+}
+
+__device__ __forceinline__ float absmax4(const float4_any &v, float best)
+{
+    return fmaxf(fmaxf(best, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+
+// One scale per row: a workgroup of T lanes holds its row in registers, CH float4 a lane,
+// between the absmax and the codes.  Bound by HBM: five bytes an element, each moved once
+// (a loop over the row with one float a lane, read twice, took 139 us for 8192 x 8192; this
+// takes 61 us, 5.5 TB/s, and 57344 x 8192 431 us instead of 1012).
+template <int CH, int T>
+__global__ __launch_bounds__(T) void quant_w6_row_kernel(const float *__restrict__ w, int K,
+                                                         int8_t *__restrict__ wq, uint16_t *__restrict__ sw)
+{
+    __shared__ float red[T / 64];
+    const long row = blockIdx.x;
+    const int chunks = K / 4;
+    const float4_any *src = reinterpret_cast<const float4_any *>(w + row * K);
+    codes4_any *dst = reinterpret_cast<codes4_any *>(wq + row * K);
+    float4_any held[CH];
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int c = threadIdx.x + T * i;
+        if (c < chunks) held[i] = src[c];
+    }
     float amax = 0.0f;
-    for (int i = threadIdx.x; i < G; i += blockDim.x) amax = fmaxf(amax, fabsf(src[i]));
-    amax = block_max(amax, red);
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+        if (threadIdx.x + T * i < chunks) amax = absmax4(held[i], amax);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < T / 64; ++i) amax = fmaxf(amax, red[i]);
     uint16_t bits;
-    float sf;
-    make_scale(amax, 31.0f, bits, sf);
-    if (threadIdx.x == 0) sw[unit] = bits;
-    for (int i = threadIdx.x; i < G; i += blockDim.x)
-        dst[i] = (int8_t)quant_code(src[i], sf, -32.0f, 31.0f);
+    float sf, rf;
+    make_scale(amax, bits, sf);
+    if (threadIdx.x == 0) sw[row] = bits;
+    reciprocal(sf, rf);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int c = threadIdx.x + T * i;
+        if (c < chunks) dst[c] = quant4(held[i], sf, rf);
+    }
+}
+
+// One scale per 128 consecutive k: 32 lanes own a group, four floats each, and the absmax
+// meets by five shuffles.  Groups follow each other through the whole matrix, four KiB of a
+// wavefront's loads in flight (8192 x 8192: 61 us; with one wavefront per
+// group and two floats a lane it took 189 us).
+__global__ __launch_bounds__(256) void quant_w6_g128_kernel(const float *__restrict__ w, long chunks,
+                                                            int8_t *__restrict__ wq, uint16_t *__restrict__ sw)
+{
+    constexpr int CH = 4;
+    const float4_any *src = reinterpret_cast<const float4_any *>(w);
+    codes4_any *dst = reinterpret_cast<codes4_any *>(wq);
+    const long c0 = (long)blockIdx.x * (256 * CH) + threadIdx.x;    // the 32 lanes of a group leave together
+    float4_any held[CH];
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+        if (c0 + 256 * i < chunks) held[i] = src[c0 + 256 * i];
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const long c = c0 + 256 * i;
+        if (c >= chunks) return;
+        float amax = absmax4(held[i], 0.0f);
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+        uint16_t bits;
+        float sf, rf;
+        make_scale(amax, bits, sf);
+        if ((threadIdx.x & 31) == 0) sw[c >> 5] = bits;
+        reciprocal(sf, rf);
+        dst[c] = quant4(held[i], sf, rf);
+    }
 }
 
 // One thread per (tile, lane): 64 codes in, 48 packed bytes out.
-__global__ __launch_bounds__(256) void pack_w6_kernel(const int8_t *__restrict__ wq, int N, int K,
+// The first threads copy the scales as well (there are at most half as many as threads),
+// group ones from [N][K/128] to tile order [N/32][K/128][32]: a launch of its own for
+// them took 4.7 us.
+__global__ __launch_bounds__(256) void pack_w6_kernel(const int8_t *__restrict__ wq,
+                                                      const uint16_t *__restrict__ sw, int N, int K, int group,
                                                       uint8_t *__restrict__ packed)
 {
     const long gid = (long)blockIdx.x * 256 + threadIdx.x;
     const int kt = K / FLEXQ_TILE_K;
     const long tiles = (long)(N / FLEXQ_TILE_ROWS) * kt;
+    uint16_t *scales = reinterpret_cast<uint16_t *>(packed + tiles * FLEXQ_TILE_BYTES);
+    if (group == 0) {
+        if (gid < N) scales[gid] = sw[gid];
+    } else if (gid < (long)N * kt) {
+        const long nb = gid / (32 * kt), in_nb = gid - nb * 32 * kt;
+        scales[gid] = sw[(nb * 32 + (in_nb & 31)) * kt + (in_nb >> 5)];
+    }
     const long tile = gid >> 6;
     const int lane = (int)(gid & 63);
     if (tile >= tiles) return;
@@ -164,10 +235,9 @@ __global__ __launch_bounds__(256) void untile_act_kernel(const uint8_t *__restri
     }
 }
 
-// Scales into / out of the packed buffer.  group mode reorders [N][K/128] to
-// tile order [N/32][K/128][32].
-__global__ void scales_kernel(const uint16_t *__restrict__ src, int N, int K, int group,
-                              uint16_t *__restrict__ dst, int to_packed)
+// Scales out of the packed buffer; group mode: tile order [N/32][K/128][32] back to [N][K/128].
+__global__ void unpack_scales_kernel(const uint16_t *__restrict__ src, int N, int K, int group,
+                                     uint16_t *__restrict__ dst)
 {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (group == 0) {
@@ -177,11 +247,7 @@ __global__ void scales_kernel(const uint16_t *__restrict__ src, int N, int K, in
     const int kt = K / FLEXQ_TILE_K;
     if (i >= (long)N * kt) return;
     const long n = i / kt, g = i % kt;
-    const long tiled = ((n / 32) * kt + g) * 32 + (n % 32);
-    if (to_packed)
-        dst[tiled] = src[i];
-    else
-        dst[i] = src[tiled];
+    dst[i] = src[((n / 32) * kt + g) * 32 + (n % 32)];
 }
 
 __global__ void fill_zero_kernel(unsigned *p, long count)
@@ -197,10 +263,31 @@ namespace flexq {
 hipError_t launch_quant_w6(const float *w, int N, int K, int group, int8_t *wq, uint16_t *sw,
                            hipStream_t st)
 {
-    const int G = group == 0 ? K : group;
-    const long units = (long)N * (K / G);
-    const int threads = G >= 1024 ? 256 : 64;
-    hipLaunchKernelGGL(quant_w6_kernel, dim3((unsigned)units), dim3(threads), 0, st, w, K, G, wq, sw);
+    if (group != 0) {
+        const long chunks = (long)N * K / 4;
+        hipLaunchKernelGGL(quant_w6_g128_kernel, dim3((unsigned)((chunks + 1023) / 1024)), dim3(256), 0, st, w,
+                           chunks, wq, sw);
+        return hipGetLastError();
+    }
+#define FLEXQ_QUANT_ROW(CH, T) \
+    hipLaunchKernelGGL((quant_w6_row_kernel<CH, T>), dim3((unsigned)N), dim3(T), 0, st, w, K, wq, sw)
+    // at most eight float4 a lane (sixteen for the longest rows), so that enough lanes are
+    // resident to keep a CU's share of HBM busy
+    if (K <= 2048)
+        FLEXQ_QUANT_ROW(2, 256);
+    else if (K <= 4096)
+        FLEXQ_QUANT_ROW(4, 256);
+    else if (K <= 8192)
+        FLEXQ_QUANT_ROW(8, 256);
+    else if (K <= 16384)
+        FLEXQ_QUANT_ROW(8, 512);
+    else if (K <= 32768)
+        FLEXQ_QUANT_ROW(8, 1024);
+    else if (K <= 65536)
+        FLEXQ_QUANT_ROW(16, 1024);
+    else
+        return hipErrorInvalidValue;            // longer rows are refused by the caller
+#undef FLEXQ_QUANT_ROW
     return hipGetLastError();
 }
 
@@ -208,14 +295,8 @@ hipError_t launch_pack_w6(const int8_t *wq, const uint16_t *sw, int N, int K, in
                           void *packed, hipStream_t st)
 {
     const long lanes = (long)(N / 32) * (K / 128) * 64;
-    hipLaunchKernelGGL(pack_w6_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, wq,
-                       N, K, (uint8_t *)packed);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    uint16_t *dst = (uint16_t *)((uint8_t *)packed + (size_t)N * K * 6 / 8);
-    const long count = group == 0 ? N : (long)N * (K / 128);
-    hipLaunchKernelGGL(scales_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, sw, N,
-                       K, group, dst, 1);
+    hipLaunchKernelGGL(pack_w6_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, wq, sw,
+                       N, K, group, (uint8_t *)packed);
     return hipGetLastError();
 }
 
@@ -229,8 +310,8 @@ hipError_t launch_unpack_w6(const void *packed, int N, int K, int group, int8_t 
     if (e != hipSuccess) return e;
     const uint16_t *src = (const uint16_t *)((const uint8_t *)packed + (size_t)N * K * 6 / 8);
     const long count = group == 0 ? N : (long)N * (K / 128);
-    hipLaunchKernelGGL(scales_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, src,
-                       N, K, group, sw, 0);
+    hipLaunchKernelGGL(unpack_scales_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, src,
+                       N, K, group, sw);
     return hipGetLastError();
 }
 
