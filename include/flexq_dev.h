@@ -64,8 +64,11 @@ typedef struct {
  * 14: with those tiles run as 256x128 half tiles, 15: 128x256 tiles of the same kernel,
  * for up to 128 tokens on very wide layers, 16: those tiles each cut along K into
  * split_k pieces -- 65 to 128 tokens on narrower layers; 17, forced only: 13 with the
- * tail cut into 256 runs that cross tile borders), s = the number of K splits
- * (for 13, 16, 17: the number of runs in all; for 14: of half tiles; 500 more
+ * tail cut into 256 runs that cross tile borders; 18: group-128 scales, persistent 128x256
+ * tiles, those beyond the last whole round of 256 each cut along K into split_k pieces),
+ * s = the number of K splits
+ * (for 13, 16, 17: the number of runs in all; for 14: of half tiles; for 18: of pieces
+ * per cut tile; 500 more
  * when the streaming kernel read its activations in tile order).  Results are the same
  * whatever the overrides.
  */

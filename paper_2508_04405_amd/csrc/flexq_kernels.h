@@ -126,5 +126,11 @@ struct WldsChoice {
 };
 WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut);
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st);
+// Group-128 scales (on both operands with a.sxg): 128x256 tiles of the same kernel, persistent,
+// the tiles beyond the last whole round of 256 each cut along K into `pieces` (1: run whole;
+// the area must hold low_cut_bytes(their number in all)).
+hipError_t launch_gemm_group(const LinearArgs &a, int pieces, hipStream_t st);
+// Pieces of a tail tile estimated to be fastest, within that many bytes of workspace.
+int group_tail_pieces(int M, int N, int K, size_t partial_bytes);
 
 }  // namespace flexq

@@ -99,13 +99,14 @@ constexpr int SLOT_BYTES = 256 * 256 * 4;      // one workgroup's int32 sums of 
 // tiles, 1 x 8 wavefronts of 256 x 32 halve the expansion work per MFMA for twice the
 // activation reads: measured 2-5 % slower on every layer.)
 // TILE names the shape: 2 the whole tile (256 x 256), 1 the half tile (256 x 128), 3 the
-// low tile (128 x 256, 2 x 4 wavefronts of 64 x 64: for up to 128 tokens on wide layers)
+// low tile (128 x 256, 2 x 4 wavefronts of 64 x 64: for up to 128 tokens on wide layers),
+// 4 the group tile (128 x 256, eight wavefronts side by side of 128 x 32: group-128 scales)
 template <int TILE>
 struct Shape {
-    static_assert(TILE >= 1 && TILE <= 3, "half, whole or low tiles");
-    static constexpr int WN = TILE == 1 ? 2 : 4;
-    static constexpr int MT = TILE == 2 ? 4 : 2;
-    static constexpr int NT = 2;
+    static_assert(TILE >= 1 && TILE <= 4, "half, whole, low or group tiles");
+    static constexpr int WN = TILE == 1 ? 2 : TILE == 4 ? 8 : 4;
+    static constexpr int MT = TILE == 2 || TILE == 4 ? 4 : 2;
+    static constexpr int NT = TILE == 4 ? 1 : 2;
     static constexpr int BN = WN * NT * 32;
     static constexpr int BM = WAVES / WN * MT * 32;
     static_assert(BN == 256 || BN == 128, "whole or half width");
@@ -137,7 +138,11 @@ struct Shape {
     static constexpr int STG = WBASE + 2 * WSTAGE;
     static constexpr int ESTRIDE = NT * 64 + 16;
     static constexpr int STG_END = STG + WAVES * 32 * ESTRIDE;
-    static constexpr int LDS_BYTES = STG_END > WBASE + 3 * WSTAGE ? STG_END : WBASE + 3 * WSTAGE;
+    // Group tiles: the scales of a stage follow everything else, a ring of four slots.
+    static constexpr int SRING = STG_END > WBASE + 3 * WSTAGE ? STG_END : WBASE + 3 * WSTAGE;
+    static constexpr int SSLOT = BN * 2 + BM * 2;                 // weight scales, token scales
+    static constexpr int SF32 = SRING + 4 * SSLOT;                // the current stage's weight scales in fp32
+    static constexpr int LDS_BYTES = TILE == 4 ? SF32 + BN * 4 : SRING;
     static_assert(LDS_BYTES + 1024 <= 160 * 1024, "LDS of one CU (plus the static part)");
 };
 
@@ -147,10 +152,228 @@ struct Item {
     int t256, half, ks, ke, tj;
 };
 
+// The stages of one item of group tiles: every 128-k stage's int32 sums, exact, are folded
+// into the fp32 accumulators as acc = fma(float(sum), sw[n][g], acc), or, with scales on both
+// operands, fma(float(sum) * sw[n][g], sx[m][g], acc).
+//
+// That is two (three) vector operations per accumulator and stage beside a quarter of an MFMA:
+// the vector unit bounds this mode, and what the kernel can do is to keep it busy from the
+// first stage to the last and to use cheap operations.  Eight wavefronts side by side, 128 x 32
+// each, expand a weight operand once for four MFMAs (64 x 64 each would expand twice as often).  A block's four MFMAs are slots 4b .. 4b + 3, and quarter q
+// of block c is scaled in slot 4c + q + 5, when its last MFMA has surely finished; three block
+// buffers rotate.  Activation operands are read one block ahead, the next stage's weights and
+// scales after the hand-over that opens the last block; the weight operand of a k-step is
+// overwritten as soon as the last block has used it.
+// The scaling avoids the slower operations of this machine: int -> float conversions, mixed-
+// precision multiply-adds and any operand from a scalar register take twice the time of plain
+// fp32 adds and multiply-adds on vector registers.  So the MFMA chain starts from the bits of
+// 1.5 * 2^23 instead of zero -- the sum, read as a float, is then that constant plus the exact
+// integer (at most 2^21 in magnitude), and one add takes the constant off -- and the weight
+// scales are converted once per stage and wavefront, through LDS.
+// Measured against 128 x 128 tiles of four wavefronts, two workgroups a CU (conversions and
+// mixed multiply-adds): 4096 x 8192 x 8192 297 us against 336, LLaMA-2-13B's down projection at
+// 2048 tokens 170 against 219 us, with scales on both operands 209 against 293, at 700 tokens
+// 85 against 146.  Without any DMA the first takes 268 us: the instruction stream and the
+// clock it runs at are the bound.
+template <int GROUP, class DmaX, class DmaW, class DmaS>
+__device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int KN, int wave, int lane,
+                                           const DmaX &dma_x, const DmaW &dma_w, const DmaS &dma_s)
+{
+    using S = Shape<4>;
+    constexpr int MT = S::MT, NB = S::MT;
+    static_assert(S::NT == 1 && MT == 4 && S::XBUFS == 3, "the slot tables below are written for this blocking");
+    const int arow = lane & 31, ahalf = lane >> 5;
+    const int wfrag = S::WBASE + wave * FLEXQ_TILE_BYTES + lane * 16;
+
+    PackedTile w;                      // the packed planes whose operands are not all expanded yet
+    v4i bf[4], af[2][4];               // weight operands of the stage; activation operands of two blocks
+    v16i part[3];                      // int32 sums of the block in flight and the two before
+    v4f sw[4];                         // this lane's sixteen channels' scales
+    uint16_t sx_next[MT];              // GROUP == 2: this lane's token's scale of each block
+    float sx[MT];
+    // Constants in vector registers: an operand from a scalar register halves the rate.
+    v16i magic;
+    float minus_magic = -12582912.0f;
+    int top6 = (int)0xFCFCFCFC, low2 = 0x03030303;
+    asm volatile("" : "+v"(minus_magic), "+v"(top6), "+v"(low2));
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        int m = 0x4B400000;
+        asm volatile("" : "+v"(m));
+        magic[r] = m;
+    }
+    auto read_planes = [&](int buf) {
+        const v4i *t = reinterpret_cast<const v4i *>(lds + wfrag + buf * S::WSTAGE);
+        w.q0 = t[0];
+        w.q1 = t[64];
+        w.q2 = t[128];
+    };
+    auto fourth = [&](int d) {          // a dword of the fourth k-step's operand
+        int r = w.q0[d] & low2;
+        r = (r << 2) | (w.q1[d] & low2);
+        r = (r << 2) | (w.q2[d] & low2);
+        return r << 2;
+    };
+    // the weight scales of stage kb from the ring to this wavefront's fp32 copy, in two halves
+    auto scale_bits = [&](int kb) {
+        return *reinterpret_cast<const uint16_t *>(lds + S::SRING + (kb & 3) * S::SSLOT + wave * 64 + 2 * arow);
+    };
+    float *const sw32 = reinterpret_cast<float *>(lds + S::SF32) + 32 * wave;
+    auto read_sx = [&](int kb) {
+        const uint8_t *slot = lds + S::SRING + (kb & 3) * S::SSLOT + S::BN * 2;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            sx_next[mt] = *reinterpret_cast<const uint16_t *>(slot + (32 * mt + arow) * 2);
+    };
+    auto read_act = [&](const uint8_t *xs, int mt, int j) {
+        return *reinterpret_cast<const v4i *>(xs + lds_off(arow + 32 * mt, 2 * j + ahalf));
+    };
+    // quarter q of block mt, sums in p, folded in with the scales in registers
+    auto scale = [&](const v16i &p, int mt, int q) {
+        float f[4], t[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f[r] = __int_as_float(p[4 * q + r]) + minus_magic;
+        // (all four before the first is used: a dependent pair back to back waits)
+        asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
+        if (GROUP == 2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f[r] *= sw[q][r];
+            asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            t[r] = __builtin_fmaf(f[r], GROUP == 2 ? sx[mt] : sw[q][r], facc[mt][0][4 * q + r]);
+        // (an empty statement that uses the results keeps the scaling in its slot)
+        asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) facc[mt][0][4 * q + r] = t[r];
+    };
+
+    read_planes(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) af[0][j] = read_act(lds, 0, j);
+    sw32[arow] = h2f(scale_bits(0));
+    bf[0] = w.q0 & top6;
+    bf[1] = w.q1 & top6;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[i][r] = 0;
+    // "the stage before the first": finite sums times zero
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sw[q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) sx[mt] = 0.0f;
+
+    // STEADY: two more stages follow for certain (no branches but the wavefront's share of DMA)
+    auto stage = [&](int kb, auto cur_tag, auto steady_tag) {
+        constexpr int CUR = decltype(cur_tag)::value;      // kb % 3: the stage buffers it reads
+        constexpr int NXT = (CUR + 1) % 3, NXT2 = (CUR + 2) % 3;
+        constexpr bool STEADY = decltype(steady_tag)::value;
+        const bool more1 = STEADY || kb + 1 < KN, more2 = STEADY || kb + 2 < KN;
+        const uint8_t *xs = lds + CUR * S::XSTAGE, *xn = lds + NXT * S::XSTAGE;
+        uint16_t sw_bits = 0;
+#pragma unroll
+        for (int s = 0; s < 4 * NB; ++s) {
+            const int b = s >> 2, j = s & 3;
+            if (s == 4 * NB - 4) {
+                // stage kb + 1 (every wavefront's share) must have landed; the loads for stage
+                // kb + 2 may be in flight.  Behind the barrier nobody reads this stage's buffers.
+                if (!more2)
+                    wait_vmcnt<0>();
+                else if (wave < S::WDMA_SPLIT)
+                    wait_vmcnt<S::XDMA + S::WDMA_LOW>();
+                else if (wave < (GROUP == 2 ? 7 : 6))
+                    wait_vmcnt<S::XDMA + 1>();
+                else
+                    wait_vmcnt<S::XDMA>();
+                lds_barrier();
+                if (more1) read_planes(NXT);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            const int buf = (CUR * NB + b) % 3;
+            part[buf] = mfma_i8(bf[j], af[b & 1][j], j == 0 ? magic : part[buf]);
+            if (s == 0 && more2) dma_x(kb + 2, NXT2);
+            if (s == 3 && more2) {
+                dma_w(kb + 2, NXT2);
+                dma_s(kb + 2);
+            }
+            if (b + 1 < NB) {
+                if (j < 2) {
+                    af[(b + 1) & 1][2 * j] = read_act(xs, b + 1, 2 * j);
+                    af[(b + 1) & 1][2 * j + 1] = read_act(xs, b + 1, 2 * j + 1);
+                }
+            } else if (more1 && (j == 1 || j == 2)) {
+                af[0][2 * (j - 1)] = read_act(xn, 0, 2 * (j - 1));
+                af[0][2 * (j - 1) + 1] = read_act(xn, 0, 2 * (j - 1) + 1);
+                if (j == 1) sw_bits = scale_bits(kb + 1);
+            }
+            // the quarter that is due; blocks before this stage's first belong to the one
+            // before.  Its scales serve up to slot 4; behind the last use of a quarter's the
+            // new ones are read, due four slots later.
+            {
+                const int c = j == 0 ? b - 2 : b - 1, q = j == 0 ? 3 : j - 1;
+                scale(part[(CUR * NB + c + 3) % 3], (c + NB) % NB, q);
+            }
+            if (s >= 1 && s <= 4)
+                sw[s - 1] = *reinterpret_cast<const v4f *>(sw32 + 8 * (s - 1) + 4 * ahalf);
+            if (GROUP == 2) {
+                if (s == 1) read_sx(kb);
+                if (s == 4) {
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) sx[mt] = h2f(sx_next[mt]);
+                }
+            }
+            // weight operands: the fourth k-step's, dearer, over the first three slots of its
+            // stage; the next stage's first two once the last block has used this stage's
+            if (s == 0) bf[2] = w.q2 & top6;
+            if (s < 2) bf[3][s] = fourth(s);
+            if (s == 2) {
+                bf[3][2] = fourth(2);
+                bf[3][3] = fourth(3);
+            }
+            if (s == 4 * NB - 2) bf[0] = w.q0 & top6;
+            if (s == 4 * NB - 1) {
+                bf[1] = w.q1 & top6;
+                if (more1) sw32[arow] = h2f(sw_bits);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int kb = 0;
+    constexpr std::integral_constant<int, 0> c0{};
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, 2> c2{};
+    for (; kb + 5 <= KN; kb += 3) {
+        stage(kb, c0, std::true_type{});
+        stage(kb + 1, c1, std::true_type{});
+        stage(kb + 2, c2, std::true_type{});
+    }
+    if (kb < KN) stage(kb, c0, std::false_type{});
+    if (kb + 1 < KN) stage(kb + 1, c1, std::false_type{});
+    if (kb + 2 < KN) stage(kb + 2, c2, std::false_type{});
+    if (kb + 3 < KN) stage(kb + 3, c0, std::false_type{});
+    // still unscaled: the last quarter of the block before the last, and the last block
+    const int last = (KN * NB - 1) % 3, before = (KN * NB - 2) % 3;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        if (i == before) scale(part[i], NB - 2, 3);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        if (i == last) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) scale(part[i], NB - 1, q);
+        }
+    }
+}
+
 // One phase of a launch: this workgroup's share of `item_count` items that begin at the
 // 256-wide tile `item_begin` -- whole tiles (TILE = 2), half tiles (two items per tile),
 // or, with SK, the stages of `item_count` tiles cut into `tail_wgs` runs.
-template <int TILE, int SK>
+// GROUP (group tiles only): 1 = weight scales per 128-k group, one scale per token; 2 = both
+// operands' scales per group.
+template <int TILE, int SK, int GROUP = 0>
 __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *lds, int &s_last, int tiles_m,
                                           int tiles_n, int item_begin, int item_count, int tail_wgs)
 {
@@ -159,6 +382,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     constexpr int MT = S::MT, NT = S::NT;
     constexpr bool WHOLE = S::BN == 256;
     static_assert(!SK || WHOLE, "the tail is cut in whole-width tiles");
+    static_assert((GROUP != 0) == (TILE == 4) && !(GROUP && SK == 1), "group scales run group tiles");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -228,7 +452,8 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     auto locate = [&](const Item &it, Where &w) {
         int lane_l = lane;        // (opaque: recomputed per item rather than kept live, see the epilogue)
         asm volatile("" : "+v"(lane_l));
-        constexpr int SUP_M = 4;  // super-block: 4 tiles along m, then next n
+        // super-block: 4 tiles along m (8 of half the height), then next n
+        constexpr int SUP_M = GROUP ? 8 : 4;
         const int bid = it.t256;
         const int sup = bid / (SUP_M * tiles_n);
         const int first_m = sup * SUP_M;
@@ -260,6 +485,24 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     // are never stored.
     const unsigned wlane = (unsigned)lane * 16u;
     auto dma_w = [&](const Where &w, int ks, int kb, int buf) {
+        if constexpr (GROUP != 0) {
+            // (whole tiles per wavefront: the planes are immediate offsets of one address)
+            if (wave < S::WISSUERS) {
+#pragma unroll
+                for (int i = 0; i < S::WTILES / S::WISSUERS; ++i) {
+                    const int t = wave * (S::WTILES / S::WISSUERS) + i;
+                    const int wtile = min(w.bn0 / 32 + t, N / 32 - 1);
+                    void __attribute__((address_space(3))) *dst =
+                        (void __attribute__((address_space(3))) *)(lds + S::WBASE + buf * S::WSTAGE +
+                                                                   t * FLEXQ_TILE_BYTES);
+                    const unsigned soff = (unsigned)(wtile * KT + ks + kb) * FLEXQ_TILE_BYTES;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrsrc, dst, 16, wlane, soff, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrsrc, dst, 16, wlane, soff, 1024, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(wrsrc, dst, 16, wlane, soff, 2048, 0);
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int p0 = 0; p0 < 3 * S::WTILES; p0 += S::WISSUERS) {
             const int p = p0 + wave;
@@ -273,12 +516,43 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             }
         }
     };
+    // Group tiles: the stage's scales, two bytes each, by 4-byte DMA loads into a ring of four
+    // slots: the eight weight tiles' 32 scales each (wavefronts 4 and 5, four tiles a load)
+    // and, with group-wise token scales, the 128 rows' (wavefront 6).
+    const int KTs = KT;
+    const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)a.scales, 0, GROUP ? (unsigned)((long)N * KTs * 2) : 0u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xsrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(GROUP == 2 ? a.sxg : a.scales), 0, GROUP == 2 ? (unsigned)((long)KTs * a.sxg_stride * 2) : 0u,
+        0x00020000);
+    auto dma_s = [&](const Where &w, int ks, int kb) {
+        if constexpr (GROUP != 0) {
+            uint8_t *slot = lds + S::SRING + (kb & 3) * S::SSLOT;
+            if (wave == 4 || wave == 5) {
+                const int t = 4 * (wave - 4) + (lane >> 4);
+                const int wtile = min(w.bn0 / 32 + t, N / 32 - 1);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    srsrc, (void __attribute__((address_space(3))) *)(slot + (wave - 4) * 256), 4,
+                    (unsigned)wtile * (unsigned)KT * 64u + (unsigned)(lane & 15) * 4u, (unsigned)(ks + kb) * 64u, 0, 0);
+            }
+            if (GROUP == 2 && wave == 6) {
+                // (a pair of rows beyond M: an offset past the buffer reads as zero)
+                const int row = w.bm0 + 2 * lane;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    xsrsrc, (void __attribute__((address_space(3))) *)(slot + S::BN * 2), 4,
+                    row < M ? (unsigned)row * 2u : 0x80000000u,
+                    (unsigned)(ks + kb) * (unsigned)a.sxg_stride * 2u, 0, 0);
+            }
+        }
+    };
     // weights and activations of an item's stage 0, weights (and, where activations run
     // two stages ahead, activations) of its stage 1
     auto issue_prologue = [&](const Item &it, const Where &w) {
         dma_w(w, it.ks, 0, 0);
         dma_x(w, it.ks, 0, 0);
+        dma_s(w, it.ks, 0);
         if (it.ke - it.ks > 1) {
+            dma_s(w, it.ks, 1);
             dma_w(w, it.ks, 1, 1);
             if (S::XA == 2) dma_x(w, it.ks, 1, 1);
         }
@@ -299,7 +573,8 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     for (;;) {
         const int ks = cur.ks, KN = cur.ke - cur.ks;
 
-        v16i acc[MT][NT];
+        // int32 sums of 4 x the product, or (group scales) fp32 sums of the scaled group sums
+        std::conditional_t<GROUP != 0, v16f, v16i> acc[MT][NT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -307,6 +582,11 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[mt][nt][r] = 0;
 
+        if constexpr (GROUP != 0) {
+            group_item<GROUP>(acc, lds, KN, wave, lane, [&](int kb, int buf) { dma_x(at, ks, kb, buf); },
+                              [&](int kb, int buf) { dma_w(at, ks, kb, buf); },
+                              [&](int kb) { dma_s(at, ks, kb); });
+        } else {
         // operands that live across stages: the stage's packed tiles, the activation
         // operands of two consecutive k-steps, the first weight operand of a stage
         PackedTile wreg[NT];
@@ -501,6 +781,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
         }
         if (kb < KN) stage(kb, std::integral_constant<int, 0>{});
         if (S::XBUFS == 3 && kb + 1 < KN) stage(kb + 1, std::integral_constant<int, 1>{});
+        }
         // (every wavefront has passed the last stage's barrier with its LDS reads done: the
         // stage buffers are free)
 
@@ -543,8 +824,12 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const v4u piece = {(unsigned)acc[mt][nt][4 * q], (unsigned)acc[mt][nt][4 * q + 1],
-                                           (unsigned)acc[mt][nt][4 * q + 2], (unsigned)acc[mt][nt][4 * q + 3]};
+                        v4u piece;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const auto v = acc[mt][nt][4 * q + c];      // int or float
+                            piece[c] = __builtin_bit_cast(unsigned, v);
+                        }
                         __builtin_amdgcn_raw_buffer_store_b128(
                             piece, prsrc, mine + (unsigned)(((mt * NT + nt) * 4 + q) * 1024), 0, kScopeAgent);
                     }
@@ -560,26 +845,54 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 #pragma unroll
                 for (int i = 0; i < NT * 4; ++i)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) acc[mt][i >> 2][4 * (i & 3) + c] += (int)got[i][c];
+                    for (int c = 0; c < 4; ++c) {
+                        const unsigned v = got[i][c];
+                        if constexpr (GROUP != 0)
+                            acc[mt][i >> 2][4 * (i & 3) + c] += __uint_as_float(v);
+                        else
+                            acc[mt][i >> 2][4 * (i & 3) + c] += (int)v;
+                    }
             };
             // every other piece's sums of slab mt, the next piece's loads in flight while one
-            // piece's sums are added (one round trip in all instead of one per piece)
+            // piece's sums are added (one round trip in all instead of one per piece).  fp32 sums
+            // are added in the order of the pieces, this one's in its place, so that the result
+            // does not depend on which piece finishes a slab.
             auto gather_slab = [&](int mt) {
                 auto following = [&](int from) {
                     const int n = from + 1;
                     return n == me ? n + 1 : n;
                 };
                 v4u got_a[NT * 4], got_b[NT * 4];
+                v16f own[GROUP ? NT : 1];
+                if constexpr (GROUP != 0) {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        own[nt] = acc[mt][nt];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[mt][nt][r] = 0.0f;
+                    }
+                }
+                auto add_own = [&](int after) {     // this piece's sums follow piece `after`'s
+                    if constexpr (GROUP != 0) {
+                        if (after == me - 1) {
+#pragma unroll
+                            for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += own[nt];
+                        }
+                    }
+                };
                 int from = following(-1);
                 load_slab(got_a, mt, from);
+                add_own(-1);
                 for (;;) {
                     int nxt = following(from);
                     if (nxt < pieces) load_slab(got_b, mt, nxt);
                     sum_slab(got_a, mt);
+                    add_own(from);
                     if (nxt >= pieces) break;
                     from = following(nxt);
                     if (from < pieces) load_slab(got_a, mt, from);
                     sum_slab(got_b, mt);
+                    add_own(nxt);
                     if (from >= pieces) break;
                 }
             };
@@ -654,7 +967,8 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                 }
             }
             finish = fin_slabs != 0;
-        } else if (SK == 1 && KN != KT) {
+        } else if constexpr (SK == 1) {
+            if (KN != KT) {
             // [slot][wavefront][block mt, nt][quarter][lane] 16-byte pieces: every store and
             // load below is one contiguous KiB per wavefront.  Cache policy bit 4 = sc1 =
             // device scope: the access goes to memory all XCDs share.
@@ -736,6 +1050,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                     }
                 }
             }
+            }
         }
 
         // ---- the next item's first stages set out now, before this tile is stored ----
@@ -768,7 +1083,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             uint2 sw4[NT][4];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const bool cvalid = n_wave + nt * 32 < N;                 // uniform; N is a multiple of 32
+                const bool cvalid = !GROUP && n_wave + nt * 32 < N;       // uniform; N is a multiple of 32
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int n = n_wave + nt * 32 + 8 * q + 4 * hh;
@@ -779,7 +1094,10 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int m = bm0 + (wm * MT + mt) * 32 + ml;
-                sxq[mt] = m < M ? 0.25f * h2f(a.sx[m]) : 0.0f;
+                if (GROUP == 2)
+                    sxq[mt] = 0.25f;
+                else
+                    sxq[mt] = m < M ? 0.25f * h2f(a.sx[m]) : 0.0f;
             }
             uint8_t *stg = lds + S::STG + wave * (32 * S::ESTRIDE);
             constexpr int LPR = NT * 4;                 // lanes per staged row, 16 bytes (8 channels) each
@@ -805,7 +1123,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                         uint16_t h[4];
 #pragma unroll
                         for (int c = 0; c < 4; ++c) {
-                            const float swc = h2f((uint16_t)(swp[c >> 1] >> (16 * (c & 1))));
+                            const float swc = GROUP ? 1.0f : h2f((uint16_t)(swp[c >> 1] >> (16 * (c & 1))));
                             h[c] = f2h((float)acc[mt][nt][4 * q + c] * (sxq[mt] * swc));
                         }
                         uint2 out2;
@@ -813,6 +1131,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                         out2.y = (unsigned)h[2] | ((unsigned)h[3] << 16);
                         *reinterpret_cast<uint2 *>(stg + ml * S::ESTRIDE + (nt * 32 + 8 * q + 4 * hh) * 2) = out2;
                     }
+                if constexpr (!GROUP) {
                 if (a.acc_out) {     // the exact int32 sums, straight from the registers
                     const int m = m_slab + ml;
 #pragma unroll
@@ -826,6 +1145,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                                 *reinterpret_cast<v4i *>(a.acc_out + (long)m * N + n) = four;
                             }
                         }
+                }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // own region only: no barrier
 #pragma unroll
@@ -880,6 +1200,22 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
     if (FORM == 1) run_items<1, 0>(a, lds, s_last, tiles_m, tiles_n, full_count, 2 * tail_count, 0);
     if (FORM == 2) run_items<2, 1>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
     if (FORM == 4) run_items<2, 2>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+}
+
+// Group tiles (tiles_m counts 128-row tiles): `full_count` whole ones, then `tail_count` of
+// them each cut into tail_wgs / tail_count pieces.
+template <int GROUP>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gemm_group_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_count, int tail_count, int tail_wgs)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    __shared__ int s_last;
+    if (full_count > 0) run_items<4, 0, GROUP>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+    if (tail_count == 0) return;
+#if defined(__HIP_DEVICE_COMPILE__)
+    lds_barrier();     // the last epilogue's staging rows, as above
+#endif
+    run_items<4, 2, GROUP>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
 }
 
 }  // namespace
@@ -987,7 +1323,59 @@ int grid_for(int items)
     return device_cu_count() == kStreamKGrid && g > kStreamKGrid ? kStreamKGrid : g;
 }
 
+template <int GROUP>
+hipError_t launch_group(const LinearArgs &a, int tiles_m, int tiles_n, int full, int tail, int pieces, hipStream_t st)
+{
+    auto kern = gemm_group_kernel<GROUP>;
+    static std::atomic<unsigned long long> lds_allowed{0};
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), Shape<4>::LDS_BYTES, lds_allowed);
+        e != hipSuccess)
+        return e;
+    const int g_full = full ? grid_for(full) : 0, g_tail = (tail * pieces + 7) / 8 * 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g_full > g_tail ? g_full : g_tail)), dim3(64 * WAVES),
+                       Shape<4>::LDS_BYTES, st, a, tiles_m, tiles_n, full, tail, tail * pieces);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+// Estimated like the per-channel forms: a stage of a group tile takes 0.88 us while half of the
+// CUs have one, 1.15 us on a full chip; meeting costs by the pieces per tile and by their
+// number in all.  Measured on the 4096- to 28672-deep layers at 33 .. 2048 tokens, one to
+// sixteen pieces: the choice is within 4 % of the fastest.
+int group_tail_pieces(int M, int N, int K, size_t partial_bytes)
+{
+    const int tail = ((M + 127) / 128) * ((N + 255) / 256) % kStreamKGrid, KT = K / FLEXQ_TILE_K;
+    if (tail == 0 || device_cu_count() != kStreamKGrid) return 1;
+    int best = 1;
+    double best_us = 1e30;
+    for (int S = 1; S <= 16 && tail * S <= kStreamKGrid && S <= KT; ++S) {
+        const int all = tail * S;
+        if (S > 1 && partial_bytes < low_cut_bytes(all)) break;
+        const double us = (0.88 + (all > 128 ? 0.27 * (all - 128) / 128.0 : 0.0)) * ((KT + S - 1) / S) +
+                          (S > 1 ? 3.0 + 0.8 * S + 0.02 * all : 0.0);
+        if (us < best_us) {
+            best_us = us;
+            best = S;
+        }
+    }
+    return best;
+}
+
+hipError_t launch_gemm_group(const LinearArgs &a, int pieces, hipStream_t st)
+{
+    if (a.group != 128 || a.split_k > 1) return hipErrorInvalidValue;
+    const int tiles_m = (a.M + 127) / 128, tiles_n = (a.N + 255) / 256, tiles = tiles_m * tiles_n;
+    int tail = tiles % kStreamKGrid;
+    if (pieces < 2 || tail == 0) {
+        tail = 0;
+    } else if (pieces > 16 || pieces > a.K / FLEXQ_TILE_K || tail * pieces > kStreamKGrid ||
+               a.partial_bytes < low_cut_bytes(tail * pieces) || device_cu_count() != kStreamKGrid) {
+        return hipErrorInvalidValue;
+    }
+    return a.sxg ? launch_group<2>(a, tiles_m, tiles_n, tiles - tail, tail, pieces, st)
+                 : launch_group<1>(a, tiles_m, tiles_n, tiles - tail, tail, pieces, st);
+}
 
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st)
 {
