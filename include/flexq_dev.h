@@ -62,8 +62,8 @@ typedef struct {
  * 12: 256x256 with both operands through LDS, at most one workgroup per CU,
  * 13: the same with the tiles beyond the last whole round of 256 cut along K,
  * 14: with those tiles run as 256x128 half tiles, 15: 128x256 tiles of the same kernel,
- * for up to 128 tokens on very wide layers, 16: those tiles each cut along K into
- * split_k pieces -- 65 to 128 tokens on narrower layers; 17, forced only: 13 with the
+ * 16: with the tiles beyond the last whole round of 256 each cut along K into split_k
+ * pieces (for fewer than 256 tiles: all of them); 17, forced only: 13 with the
  * tail cut into 256 runs that cross tile borders; 18: group-128 scales, persistent 128x256
  * tiles, those beyond the last whole round of 256 each cut along K into split_k pieces),
  * s = the number of K splits

@@ -107,7 +107,8 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
 // into tail_wgs equal runs of 128-k stages, whose partial sums meet in the partial-sum
 // area (it must hold streamk_plan().partial_bytes; with less, and on a device that is not
 // 256 CUs wide, form 0 runs instead).  tail_form 3: 128x256 tiles and nothing else; 5:
-// those, each cut along K into tail_wgs / tiles pieces (the area must hold
+// those, the ones beyond the last whole round of 256 each cut along K into equal pieces,
+// tail_wgs in all (the area must hold
 // low_cut_bytes(tail_wgs); an error, not another form, if that or the piece count does not
 // fit).  Every launch is persistent: at most one workgroup per CU.
 constexpr int kStreamKGrid = 256;   // workgroups of the persistent form: one per CU of an MI355X
@@ -125,6 +126,7 @@ struct WldsChoice {
     int tail_form, tail_wgs;
 };
 WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut);
+WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes);   // tail_form 3 or 5
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st);
 // Group-128 scales (on both operands with a.sxg): 128x256 tiles of the same kernel, persistent,
 // the tiles beyond the last whole round of 256 each cut along K into `pieces` (1: run whole;

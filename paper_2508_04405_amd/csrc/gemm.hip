@@ -687,6 +687,17 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
             // a cut tail must promise 5 % (it adds workspace traffic the estimate is unsure
             // of); else the best form that leaves the workspace alone
             if (c.tail_form == 2 && c.us >= 0.95 * t_best) c = gemm_wlds_choose(a.M, a.N, a.K, false);
+            const WldsChoice low = gemm_low_choose(a.M, a.N, a.K, a.partial_bytes);
+            // (against 256-row tiles cut along K the low
+            // tiles must promise 12 %: the two estimates are good to about 6 % each, and
+            // at 256 tokens of a 10240 x 8192 layer 36 against 33 us is where the line falls)
+            if (low.us < t_best && low.us < (c.tail_form == 2 ? 0.88 : 1.0) * c.us) {
+                LinearArgs b = a;
+                b.split_k = 1;
+                *chosen = low.tail_form == 5 ? 16 : 15;
+                *tail_runs = low.tail_wgs;
+                return launch_gemm_wlds(b, low.tail_form, low.tail_wgs, st);
+            }
             if (c.us < t_best) {
                 LinearArgs b = a;
                 b.split_k = 1;
@@ -723,8 +734,8 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
         return launch_gemm_wlds(a, 2, tail_wgs, st);
     }
     if (cfg == 15 && a.split_k == 1) return launch_gemm_wlds(a, 3, 0, st);
-    if (cfg == 16) {   // 128x256 tiles, each cut into split_k pieces
-        const int tail_wgs = (int)(((a.M + 127) / 128) * ((a.N + 255) / 256)) * a.split_k;
+    if (cfg == 16) {   // 128x256 tiles, those beyond the last whole round cut into split_k pieces
+        const int tail_wgs = ((a.M + 127) / 128) * ((a.N + 255) / 256) % kStreamKGrid * a.split_k;
         LinearArgs b = a;
         b.split_k = 1;
         *tail_runs = tail_wgs;

@@ -1170,7 +1170,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 }
 
 // FORM 3: `full_count` low tiles (tiles_m counts 128-row tiles) and nothing else.  FORM 5:
-// `tail_count` low tiles, each cut along K into tail_wgs / tail_count pieces.
+// `full_count` low tiles, then `tail_count`, each cut along K into tail_wgs / tail_count pieces.
 // FORM 0: `full_count` whole tiles.  FORM 1: then the `tail_count` tiles that follow them as
 // 2 * tail_count half tiles.  FORM 2: then those tiles cut along K into `tail_wgs` runs
 // across tile borders.  FORM 4: then those tiles each cut into tail_wgs / tail_count pieces.
@@ -1187,8 +1187,14 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
         run_items<3, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
     }
-    if (FORM == 5) {   // every low tile cut evenly along K
-        run_items<3, 2>(a, lds, s_last, tiles_m, tiles_n, 0, tail_count, tail_wgs);
+    if (FORM == 5) {   // whole rounds of low tiles, then the rest cut evenly along K
+        if (full_count > 0) {
+            run_items<3, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+#if defined(__HIP_DEVICE_COMPILE__)
+            lds_barrier();     // as below: the last epilogue's staging rows
+#endif
+        }
+        run_items<3, 2>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
         return;
     }
     if (full_count > 0) run_items<2, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
@@ -1296,6 +1302,31 @@ WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut)
     return best;
 }
 
+// The same for 128x256 tiles above 128 tokens, where half the height fills the chip more
+// evenly: whole (form 3), or those beyond the last whole round of 256 each cut into equal pieces
+// (form 5).  A stage takes 0.60 us while at most half of the CUs have a tile and 0.91 us on a
+// full chip -- 30 % more for the same work than a 256x256 tile's, which pays for itself where
+// that would leave CUs idle.  Fitted on eighteen layers (512 .. 57344 wide, 512 .. 28672 deep)
+// at 129 .. 2048 tokens; taken there it gains 5 to 45 % between 129 and 700 tokens (8192 x
+// 8192 at 300 tokens: 44.5 -> 34.9 us, 4096 x 4096 at 220: 23.8 -> 16.4).
+WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes)
+{
+    const int tiles = ((M + 127) / 128) * ((N + 255) / 256), KT = K / FLEXQ_TILE_K;
+    const int tail = tiles % kStreamKGrid;
+    auto stage_us = [](int n) { return 0.60 + (n > 128 ? 0.31 * (n - 128) / 128.0 : 0.0); };
+    const double rounds = tiles / kStreamKGrid * (stage_us(kStreamKGrid) * KT + 5.0);
+    WldsChoice best{rounds + (tail ? stage_us(tail) * KT + 6.5 : 1.5), 3, 0};
+    if (tail == 0 || device_cu_count() != kStreamKGrid) return best;
+    for (int S = 2; S <= 16 && tail * S <= kStreamKGrid && S <= KT; ++S) {
+        const int wgs = tail * S;
+        if (partial_bytes < low_cut_bytes(wgs)) break;
+        const double meet = 3.0 + 0.4 * S + 0.015 * wgs + (wgs > 192 ? 0.05 * (wgs - 192) : 0.0);
+        const double t = rounds + stage_us(wgs) * ((KT + S - 1) / S) + 4.0 + meet;
+        if (t < best.us) best = WldsChoice{t, 5, wgs};
+    }
+    return best;
+}
+
 namespace {
 
 constexpr int kLdsMax(int a, int b) { return a > b ? a : b; }
@@ -1384,14 +1415,16 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
         const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256;
         return launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
     }
-    if (tail_form == 5) {   // low tiles, each cut into tail_wgs / tiles pieces
-        const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256, tiles = low_m * cols;
-        const int pieces = tail_wgs / tiles;
-        if (tail_wgs % tiles != 0 || pieces < 2 || pieces > 16 || pieces > a.K / FLEXQ_TILE_K ||
+    if (tail_form == 5) {   // low tiles, those beyond the last whole round cut into equal pieces
+        const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256, all = low_m * cols;
+        const int tiles = all % kStreamKGrid, full = all - tiles;
+        const int pieces = tiles ? tail_wgs / tiles : 0;
+        if (pieces < 2 || tail_wgs % tiles != 0 || pieces > 16 || pieces > a.K / FLEXQ_TILE_K ||
             tail_wgs > kStreamKGrid || a.partial_bytes < low_cut_bytes(tail_wgs) ||
             device_cu_count() != kStreamKGrid)
             return hipErrorInvalidValue;
-        return launch_form<5>(a, low_m, cols, 0, tiles, tail_wgs, (tail_wgs + 7) / 8 * 8, st);
+        const int g = (tail_wgs + 7) / 8 * 8, g_full = full ? grid_for(full) : 0;
+        return launch_form<5>(a, low_m, cols, full, tiles, tail_wgs, g > g_full ? g : g_full, st);
     }
     const int tiles_m = (a.M + 256 - 1) / 256, tiles_n = (a.N + 255) / 256;
     const StreamKPlan p = streamk_plan(a.M, a.N, a.K);

@@ -1,0 +1,51 @@
+"""GPU parity of 128x256 tiles above 128 tokens: a whole round of 256 of them followed by tiles
+cut along K in the same launch, and the sizes at which the library itself takes them."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2508_04405_amd as fq
+from paper_2508_04405_amd import dev, synth
+
+from gpu_helpers import assert_y_close, prepare, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def check(M, K, N, dispatch, want, spin=0):
+    w = synth.weights(N, K, 0.02, seed=K)
+    x = synth.activations(M, K, seed=M, outlier_frac=0.02)
+    packed, _, _ = prepare(w)
+    ref = oracle.linear(x, w, 6)
+    ws = fq.make_workspace(M, N, K, extra=64 << 20)
+    dev.set_dispatch(*dispatch)
+    dev.set_spin(spin)
+    try:
+        for _ in range(2):
+            y, acc = dev.gemm_w6a6(packed, N, K, x_fp16=to_dev(x), workspace=ws, want_acc=True)
+            assert dev.last_dispatch() == want
+            assert np.array_equal(acc.cpu().numpy().astype(np.int64), ref["acc"])
+            assert_y_close(y.cpu().numpy(), ref["y"])
+        assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+    finally:
+        dev.set_dispatch()
+        dev.set_spin(0)
+
+
+# 256 tiles whole, then the remaining 14 (270 in all) or 1 cut in two or more
+@pytest.mark.parametrize("spin", [0, -1])
+@pytest.mark.parametrize("M,K,N,pieces,tail", [(1029, 256, 7680, 2, 14), (1029, 640, 7456, 5, 14), (33 * 128, 384, 1824, 3, 8)])
+def test_round_then_cut(M, K, N, pieces, tail, spin):
+    say(f"low tiles, a round then {tail} cut into {pieces}: M={M} K={K} N={N} spin={spin}")
+    check(M, K, N, (2, pieces, 0, 16), (16, tail * pieces), spin)
+
+
+@pytest.mark.parametrize("M,K,N,want", [(129, 2048, 2048, 16), (300, 4096, 1056, 16), (600, 4096, 12288, 15)])
+def test_own_choice(M, K, N, want):
+    say(f"low tiles by choice: M={M} K={K} N={N}")
+    dev.gemm_w6a6(torch.zeros(fq.packed_bytes(N, K), dtype=torch.uint8, device="cuda"), N, K,
+                  x_fp16=torch.zeros((M, K), dtype=torch.float16, device="cuda"))
+    launched = dev.last_dispatch()
+    assert launched[0] == want, launched
+    check(M, K, N, (), launched)
