@@ -97,11 +97,14 @@ def _check(status):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # The raw handle of torch.cuda.current_stream(), the way torch's own generated code takes it:
+    # building the Stream object costs 2.9 us, a third of a small call (8.3 us a call for one
+    # token through a 4096 x 4096 layer, whose kernel takes 6.3).
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t, dtype):
