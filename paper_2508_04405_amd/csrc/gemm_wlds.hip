@@ -159,21 +159,26 @@ struct Item {
 // That is two (three) vector operations per accumulator and stage beside a quarter of an MFMA:
 // the vector unit bounds this mode, and what the kernel can do is to keep it busy from the
 // first stage to the last and to use cheap operations.  Eight wavefronts side by side, 128 x 32
-// each, expand a weight operand once for four MFMAs (64 x 64 each would expand twice as often).  A block's four MFMAs are slots 4b .. 4b + 3, and quarter q
-// of block c is scaled in slot 4c + q + 5, when its last MFMA has surely finished; three block
-// buffers rotate.  Activation operands are read one block ahead, the next stage's weights and
-// scales after the hand-over that opens the last block; the weight operand of a k-step is
-// overwritten as soon as the last block has used it.
+// each, expand a weight operand once for four MFMAs (64 x 64 each would expand twice as
+// often).  A block's four MFMAs are slots 4b .. 4b + 3, and quarter q of block c is scaled in
+// slot 4c + q + 5, when its last MFMA has surely finished; three block buffers rotate (two, and
+// a slot earlier, with scales on both operands, which need the registers).  Activation
+// operands are read one block ahead, the next stage's weights and scales after the hand-over
+// that opens the last block; the weight operand of a k-step is overwritten as soon as the last
+// block has used it.
 // The scaling avoids the slower operations of this machine: int -> float conversions, mixed-
 // precision multiply-adds and any operand from a scalar register take twice the time of plain
 // fp32 adds and multiply-adds on vector registers.  So the MFMA chain starts from the bits of
 // 1.5 * 2^23 instead of zero -- the sum, read as a float, is then that constant plus the exact
 // integer (at most 2^21 in magnitude), and one add takes the constant off -- and the weight
-// scales are converted once per stage and wavefront, through LDS.
+// scales are converted once per stage and wavefront, through LDS.  With scales on both
+// operands the constant comes off inside the multiplication, fma(bits, sw, -constant * sw):
+// that product has thirteen significant bits, so it is exact and the result rounds once, as
+// float(sum) * sw does; two operations instead of three (6 % less time).
 // Measured against 128 x 128 tiles of four wavefronts, two workgroups a CU (conversions and
 // mixed multiply-adds): 4096 x 8192 x 8192 297 us against 336, LLaMA-2-13B's down projection at
-// 2048 tokens 170 against 219 us, with scales on both operands 209 against 293, at 700 tokens
-// 85 against 146.  Without any DMA the first takes 268 us: the instruction stream and the
+// 2048 tokens 170 against 219 us, with scales on both operands 188 against 293, at 700 tokens
+// 77 against 146.  Without any DMA the first takes 268 us: the instruction stream and the
 // clock it runs at are the bound.
 template <int GROUP, class DmaX, class DmaW, class DmaS>
 __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int KN, int wave, int lane,
@@ -187,8 +192,11 @@ __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int
 
     PackedTile w;                      // the packed planes whose operands are not all expanded yet
     v4i bf[4], af[2][4];               // weight operands of the stage; activation operands of two blocks
-    v16i part[3];                      // int32 sums of the block in flight and the two before
+    // int32 sums of the block in flight and of those before it that are not folded in yet
+    constexpr int PB = GROUP == 2 ? 2 : 3;
+    v16i part[PB];
     v4f sw[4];                         // this lane's sixteen channels' scales
+    v4f off[GROUP == 2 ? 4 : 1];       // GROUP == 2: minus the constant times each, exact
     uint16_t sx_next[MT];              // GROUP == 2: this lane's token's scale of each block
     float sx[MT];
     // Constants in vector registers: an operand from a scalar register halves the rate.
@@ -232,14 +240,14 @@ __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int
     auto scale = [&](const v16i &p, int mt, int q) {
         float f[4], t[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) f[r] = __int_as_float(p[4 * q + r]) + minus_magic;
+        for (int r = 0; r < 4; ++r) {
+            const float v = __int_as_float(p[4 * q + r]);
+            // (with both scales the constant comes off in the multiplication: its product with
+            // a scale is exact, so this rounds once, like float(sum) * sw)
+            f[r] = GROUP == 2 ? __builtin_fmaf(v, sw[q][r], off[GROUP == 2 ? q : 0][r]) : v + minus_magic;
+        }
         // (all four before the first is used: a dependent pair back to back waits)
         asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
-        if (GROUP == 2) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) f[r] *= sw[q][r];
-            asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
-        }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             t[r] = __builtin_fmaf(f[r], GROUP == 2 ? sx[mt] : sw[q][r], facc[mt][0][4 * q + r]);
@@ -256,12 +264,12 @@ __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int
     bf[0] = w.q0 & top6;
     bf[1] = w.q1 & top6;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < PB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) part[i][r] = 0;
     // "the stage before the first": finite sums times zero
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sw[q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int q = 0; q < 4; ++q) sw[q] = off[GROUP == 2 ? q : 0] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) sx[mt] = 0.0f;
 
@@ -291,7 +299,7 @@ __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int
                 if (more1) read_planes(NXT);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const int buf = (CUR * NB + b) % 3;
+            const int buf = (CUR * NB + b) % PB;
             part[buf] = mfma_i8(bf[j], af[b & 1][j], j == 0 ? magic : part[buf]);
             if (s == 0 && more2) dma_x(kb + 2, NXT2);
             if (s == 3 && more2) {
@@ -312,14 +320,20 @@ __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int
             // before.  Its scales serve up to slot 4; behind the last use of a quarter's the
             // new ones are read, due four slots later.
             {
-                const int c = j == 0 ? b - 2 : b - 1, q = j == 0 ? 3 : j - 1;
-                scale(part[(CUR * NB + c + 3) % 3], (c + NB) % NB, q);
+                const int c = PB == 2 || j != 0 ? b - 1 : b - 2, q = PB == 2 ? j : j == 0 ? 3 : j - 1;
+                scale(part[(CUR * NB + c + 3 * PB) % PB], (c + NB) % NB, q);
             }
-            if (s >= 1 && s <= 4)
-                sw[s - 1] = *reinterpret_cast<const v4f *>(sw32 + 8 * (s - 1) + 4 * ahalf);
+            constexpr int S0 = PB == 2 ? 0 : 1;        // the slot of the last use of the first quarter's
+            if (s >= S0 && s < S0 + 4) {
+                sw[s - S0] = *reinterpret_cast<const v4f *>(sw32 + 8 * (s - S0) + 4 * ahalf);
+            }
+            if (GROUP == 2 && s >= 3 && s < 7) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) off[s - 3][r] = minus_magic * sw[s - 3][r];
+            }
             if (GROUP == 2) {
                 if (s == 1) read_sx(kb);
-                if (s == 4) {
+                if (s == 3) {
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) sx[mt] = h2f(sx_next[mt]);
                 }
@@ -354,13 +368,13 @@ __device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int
     if (kb + 2 < KN) stage(kb + 2, c2, std::false_type{});
     if (kb + 3 < KN) stage(kb + 3, c0, std::false_type{});
     // still unscaled: the last quarter of the block before the last, and the last block
-    const int last = (KN * NB - 1) % 3, before = (KN * NB - 2) % 3;
+    const int last = (KN * NB - 1) % PB, before = (KN * NB - 2) % PB;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        if (i == before) scale(part[i], NB - 2, 3);
+    for (int i = 0; i < PB; ++i) {
+        if (PB == 3 && i == before) scale(part[i], NB - 2, 3);
     }
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < PB; ++i) {
         if (i == last) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) scale(part[i], NB - 1, q);
