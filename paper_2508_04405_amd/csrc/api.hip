@@ -35,6 +35,13 @@ size_t scale_count(int N, int K, int group) { return group == 0 ? (size_t)N : (s
 // further only adds hand-offs.  So split just enough to reach 128 workgroups,
 // keep at least two tiles per wavefront, and keep the partial-sum traffic (8 bytes
 // per split, token and column) under a ninth of the weight stream.
+//
+// From a dozen tokens on a workgroup's time is long enough for whole rounds of 256 to count:
+// up to four splits where they fill the chip that much better and leave each workgroup a run
+// of 30 tiles (4096 x 11008 as 256 workgroups instead of 128: 15.8 -> 13.8 us at 12 tokens,
+// 18.6 -> 16.4 at 32; 2048 x 16384 as 256: 18.1 -> 15.1 at 24; 5120 x 13824 as 480 instead of
+// 160: 22.9 -> 21.5 at 32, but 18.5 -> 19.1 at 12; 6144 x 16384 as 768 instead of 192, a gain
+// of a third in filling only, loses 6 %, and 4800 x 9216 as 450 runs of 24 tiles 2-5 %).
 int choose_split(int M, int N, int K, int forced = 0)
 {
     const int kt = K / 128;
@@ -47,6 +54,18 @@ int choose_split(int M, int N, int K, int forced = 0)
         const int by_traffic = (int)((long)K / (96L * M));
         if (ks > by_traffic) ks = by_traffic;
         if (ks > kt / 16) ks = kt / 16;
+        if (ks < 1) ks = 1;
+        if (M >= 12 && M <= 32) {
+            auto filled = [&](int splits) {
+                const int wgs = row_blocks * splits;
+                return (double)wgs / ((wgs + 255) / 256 * 256);
+            };
+            const double worth = (M < 16 ? 1.8 : 1.4) * filled(ks);
+            int best = ks;
+            for (int s = ks + 1; s <= 4 && s <= by_traffic && s <= kt / 30; ++s)
+                if (filled(s) >= worth && filled(s) > filled(best)) best = s;
+            ks = best;
+        }
     }
     if (ks > kt) ks = kt;
     if (ks > 64) ks = 64;
@@ -82,8 +101,8 @@ int choose_gemm_split(int M, int N, int K, int forced = 0)
     return ks < 1 ? 1 : ks;
 }
 
-// Wavefronts per workgroup of the streaming kernel.
-int choose_waves(int M, int N, int K, int ks, int forced = 0)
+// Wavefronts per workgroup of the streaming kernel; `xt`: activations in tile order.
+int choose_waves(int M, int N, int K, int ks, int xt, int forced = 0)
 {
     if (forced > 0) return forced;
     const int tiles = K / 128 / ks;
@@ -91,17 +110,22 @@ int choose_waves(int M, int N, int K, int ks, int forced = 0)
     // sixteen wavefronts per workgroup keep more of the chip streaming (measured: 10-20 %)
     if (M <= 4 && (long)(N / 32) * ks < 256 && tiles >= 64) return 16;
     // between one and two workgroups per CU (LLaMA-2-70B's 10240-wide QKV: 320 row blocks)
-    // workgroups of eight wavefronts run in one and a quarter rounds; from 16 tokens on,
-    // where a workgroup's time is long enough to matter, four wavefronts per workgroup let
-    // every row block start at once (measured: 19 vs 21 us at 16 tokens, 26 vs 27 at 32)
+    // workgroups of eight wavefronts run in one and a quarter rounds; where the activations
+    // do not fit LDS and each lane loads its token's, a workgroup's time is long enough to
+    // matter, and four wavefronts per workgroup let every row block start at once (measured:
+    // 19 vs 21 us at 16 tokens, 26 vs 27 at 32; 15360 x 5120 at 14 tokens 16.1 vs 16.9; with
+    // the activations in LDS, 12288 x 4096 at 16 tokens, eight are faster, 15.3 vs 17.1)
     const long wgs = (long)(N / 32) * ks;
-    if (M >= 16 && wgs > 256 && wgs < 512 && tiles >= 16) return 4;
-    // wide layers with short rows at one to four tokens (the gate+up projections of
-    // LLaMA-2-7B and 13B: 688 and 864 row blocks of 32 and 40 tiles): with four wavefronts
-    // per workgroup every row block is resident from the start (measured at 640 to 1792
-    // row blocks: 13-20 % faster up to 32 tiles per row at one to four tokens, 17-20 % at
-    // 40 to 56 tiles at one token, 3 % at four; no gain from 64 tiles on or from 8 tokens)
-    if (wgs >= 640 && ((tiles <= 32 && M <= 4) || (tiles < 64 && M <= 2))) return 4;
+    const bool staged = xt == 0 && flexq::skinny_slice_fits(M, K, ks);
+    if (M > 8 && ks == 1 && wgs > 256 && wgs < 512 && tiles >= 16 && !staged) return 4;
+    // wide layers with short rows (the gate+up projections of LLaMA-2-7B and 13B: 688 and 864
+    // row blocks of 32 and 40 tiles): with four wavefronts per workgroup every row block is
+    // resident from the start (measured at 640 to 1792 row blocks: 13-20 % faster up to 32
+    // tiles per row at one to four tokens, 20.7 -> 17.1 us at six, 21.0 -> 18.7 at eight, 3 %
+    // at twelve; 17-20 % at 40 to 56 tiles at one token, 3 % at four; no gain from 64 tiles on;
+    // from tile-ordered activations 20.8 -> 19.4 us at 32 tokens and 32 tiles, 1 % at 40)
+    if (wgs >= 640 && xt != 0 && tiles <= 40) return 4;
+    if (wgs >= 640 && xt == 0 && ((tiles <= 32 && M <= 12) || (tiles < 64 && M <= 2))) return 4;
     return tiles >= 16 ? 8 : 4;
 }
 
@@ -204,10 +228,17 @@ bool streams_by_choice(int M, int N, int K, int group, bool packed_tiles = false
 // always carries 32 token rows, so the time no longer depends on the token count
 // (measured on the LLaMA-2-70B layers, quantize + GEMV from fp16: 25 / 19 / 46 us on
 // qkv / o / down for any count up to 32, against 30 / 21 / 52 us row-major at 32 tokens
-// and 23 / 17 / 38 us at 16).
+// and 23 / 17 / 38 us at 16).  Below that, where the slice fits but fills so much of a CU's
+// LDS that only two workgroups share it (12288 x 4096 at 16 tokens: 14.3 / 14.7 us at 6 / 8
+// bits against 15.3, 22016 x 4096 18.7 / 19.9 against 21.4; 15360 x 5120 at 12: 17.0 against
+// 17.4; no gain at 48 KB).
 bool tiles_pay(int act_bits, int M, int K, int split_k)
 {
-    return M <= 32 && M >= (act_bits == 6 ? 17 : 24) && !flexq::skinny_slice_fits(M, K, split_k);
+    if (flexq::skinny_slice_fits(M, K, split_k)) {
+        const int max_tiles = (K / 128 + split_k - 1) / split_k;
+        return M >= 11 && M * max_tiles * 128 >= (act_bits == 6 ? 52 : 60) * 1024;
+    }
+    return M <= 32 && M >= (act_bits == 6 ? 17 : 24);
 }
 
 }  // namespace
@@ -340,7 +371,7 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
         if ((size_t)a.split_k * per_split > ws.partial_capacity)
             a.split_k = (int)(ws.partial_capacity / per_split);
         if (a.split_k < 1) a.split_k = 1;
-        if (flexq::launch_skinny(a, choose_waves(rows, N, K, a.split_k, tune.waves), st) != hipSuccess)
+        if (flexq::launch_skinny(a, choose_waves(rows, N, K, a.split_k, xt, tune.waves), st) != hipSuccess)
             return FLEXQ_EHIP;
         if (dispatched) *dispatched = 1000 + a.split_k + (xt != 0 ? 500 : 0);
     }
