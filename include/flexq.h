@@ -230,8 +230,10 @@ flexq_status flexq_gemv_w6a8(const void *packed, int group, const int8_t *xq,
  * fetches a scattered 128-byte line per token and k-step; from tiles it is
  * three or four coalesced KiB per tile, whatever the token count (a tile always
  * carries 32 token rows).  Measured break-even: about 17 tokens (6-bit), 24
- * (8-bit); the calls that take x_fp16 go this way by themselves from there on,
- * and below it the row-major calls are the faster ones.
+ * (8-bit), and earlier (13 and 15 tokens of a 4096-deep layer) where the staged
+ * activations would take 52 or 60 KB of LDS; the calls that take x_fp16 go this
+ * way by themselves from there on, and below it the row-major calls are the
+ * faster ones.
  */
 size_t flexq_act_tiles_bytes(int act_bits, int M, int K);
 flexq_status flexq_quant_act_tiles(const uint16_t *x, int M, int K, int act_bits,

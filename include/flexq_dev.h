@@ -40,7 +40,8 @@ extern "C" {
  *   tiles     fp16 activations of up to 32 tokens quantized into tile order (packed at 6
  *             bits for act_bits 6) for the streaming kernel: 1 = always, 2 = never (the
  *             library's own choice: 17 to 32 tokens, 24 to 32 with 8-bit activations,
- *             whose activation slice does not fit the kernel's LDS staging)
+ *             whose activation slice does not fit the kernel's LDS staging, and slices
+ *             that would take 52, 60 KB of it or more)
  *   spin      gemm_cfg 13 with every tile cut into the same number of pieces: how many
  *             times a piece polls its tile's counter for the other pieces' sums before
  *             it gives up and leaves its slabs to the piece that completes the count

@@ -47,7 +47,8 @@
 //   for a k-step in turn or for part of a stage (-1 % to -40 %: a wavefront alone does not
 //   keep the pipe busy, the two must interleave).
 //
-// Per-channel scales only: this is the kernel for large M and N.
+// Scales per channel; group-128 scales, on the weights or on both operands, run 128x256 tiles
+// of their own (group_item below).
 //
 // A launch is PERSISTENT: at most one workgroup per CU, each taking its items
 // (tiles) one after the other, and the operands of the next item's first stages
@@ -77,7 +78,9 @@
 // And low tiles, 128x256, on their own: up to 128 tokens on a layer wide enough
 // for them to fill the chip in one round, where the time is the one pass over
 // the weights (about 37 GB/s per CU come through the DMA path, here as in the
-// whole tiles); on narrower layers, from 65 tokens, each cut evenly along K.
+// whole tiles); on narrower layers, from 65 tokens, each cut evenly along K; and
+// above 128 tokens where they fill the chip more evenly than 256-row tiles
+// (gemm_low_choose), those beyond the last whole round cut evenly.
 #include "flexq_device.h"
 #include "flexq_kernels.h"
 #include "gemm_common.h"
