@@ -35,42 +35,14 @@ size_t scale_count(int N, int K, int group) { return group == 0 ? (size_t)N : (s
 // further only adds hand-offs.  So split just enough to reach 128 workgroups,
 // keep at least two tiles per wavefront, and keep the partial-sum traffic (8 bytes
 // per split, token and column) under a ninth of the weight stream.
-//
-// From a dozen tokens on a workgroup's time is long enough for whole rounds of 256 to count:
-// up to four splits where they fill the chip that much better and leave each workgroup a run
-// of 30 tiles (4096 x 11008 as 256 workgroups instead of 128: 15.8 -> 13.8 us at 12 tokens,
-// 18.6 -> 16.4 at 32; 2048 x 16384 as 256: 18.1 -> 15.1 at 24; 5120 x 13824 as 480 instead of
-// 160: 22.9 -> 21.5 at 32, but 18.5 -> 19.1 at 12; 6144 x 16384 as 768 instead of 192, a gain
-// of a third in filling only, loses 6 %, and 4800 x 9216 as 450 runs of 24 tiles 2-5 %).
-int choose_split(int M, int N, int K, int forced = 0)
+int fewest_splits(int M, int N, int K)
 {
-    const int kt = K / 128;
-    int ks;
-    if (forced > 0) {
-        ks = forced;
-    } else {
-        const int row_blocks = N / 32;
-        ks = (128 + row_blocks - 1) / row_blocks;
-        const int by_traffic = (int)((long)K / (96L * M));
-        if (ks > by_traffic) ks = by_traffic;
-        if (ks > kt / 16) ks = kt / 16;
-        if (ks < 1) ks = 1;
-        if (M >= 12 && M <= 32) {
-            auto filled = [&](int splits) {
-                const int wgs = row_blocks * splits;
-                return (double)wgs / ((wgs + 255) / 256 * 256);
-            };
-            const double worth = (M < 16 ? 1.8 : 1.4) * filled(ks);
-            int best = ks;
-            for (int s = ks + 1; s <= 4 && s <= by_traffic && s <= kt / 30; ++s)
-                if (filled(s) >= worth && filled(s) > filled(best)) best = s;
-            ks = best;
-        }
-    }
-    if (ks > kt) ks = kt;
-    if (ks > 64) ks = 64;
-    if (ks < 1) ks = 1;
-    return ks;
+    const int kt = K / 128, row_blocks = N / 32;
+    int ks = (128 + row_blocks - 1) / row_blocks;
+    const int by_traffic = (int)((long)K / (96L * M));
+    if (ks > by_traffic) ks = by_traffic;
+    if (ks > kt / 16) ks = kt / 16;
+    return ks < 1 ? 1 : ks > 64 ? 64 : ks;
 }
 
 // K splits of the tiled kernel for mid-size M: with fewer than one 128x128 output
@@ -99,6 +71,60 @@ int choose_gemm_split(int M, int N, int K, int forced = 0)
     }
     if (ks > kt) ks = kt;
     return ks < 1 ? 1 : ks;
+}
+
+// Bytes of partial sums a call may need, in units of the workspace's alignment.
+size_t partial_bytes_for(int M, int N, int K)
+{
+    size_t partial = 0;
+    const int top = M < kSkinnyMaxM ? M : kSkinnyMaxM;
+    for (int m = 1; m <= top; ++m) {
+        const int ks = fewest_splits(m, N, K);
+        const size_t b = ks > 1 ? (size_t)ks * m * N * 4 : 0;
+        if (b > partial) partial = b;
+    }
+    {
+        const int gs = choose_gemm_split(M, N, K);
+        const size_t b = gs > 1 ? (size_t)gs * M * N * 4 : 0;
+        if (b > partial) partial = b;
+    }
+    if (const int pieces = flexq::low_cut_pieces(M, N, K); pieces != 0) {   // 128x256 tiles cut along K
+        const size_t b = flexq::low_cut_bytes((N + 255) / 256 * pieces);
+        if (b > partial) partial = b;
+    }
+    if (M > kSkinnyMaxM) {   // the 256x256 kernel's tail cut along K
+        const size_t b = flexq::streamk_plan(M, N, K).partial_bytes;
+        if (b > partial) partial = b;
+    }
+    return round_up(partial, 256);
+}
+
+// From a dozen tokens on a workgroup's time is long enough for whole rounds of 256 to count:
+// up to four splits where they fill the chip that much better and leave each workgroup a run
+// of 30 tiles (4096 x 11008 as 256 workgroups instead of 128: 15.8 -> 13.8 us at 12 tokens,
+// 18.6 -> 16.4 at 32; 2048 x 16384 as 256: 18.1 -> 15.1 at 24; 5120 x 13824 as 480 instead of
+// 160: 22.9 -> 21.5 at 32, but 18.5 -> 19.1 at 12; 6144 x 16384 as 768 instead of 192, a gain
+// of a third in filling only, loses 6 %, and 4800 x 9216 as 450 runs of 24 tiles 2-5 %).
+// The extra splits never make a call need a larger workspace: they have to fit the area that
+// flexq_workspace_bytes asks for without them.
+int choose_split(int M, int N, int K, int forced = 0)
+{
+    const int kt = K / 128;
+    if (forced > 0) return forced > kt ? kt : forced > 64 ? 64 : forced;
+    const int ks = fewest_splits(M, N, K);
+    if (M < 12 || M > 32) return ks;
+    const int row_blocks = N / 32;
+    auto filled = [&](int splits) {
+        const int wgs = row_blocks * splits;
+        return (double)wgs / ((wgs + 255) / 256 * 256);
+    };
+    const int by_traffic = (int)((long)K / (96L * M));
+    const double worth = (M < 16 ? 1.8 : 1.4) * filled(ks);
+    int best = ks;
+    for (int s = ks + 1; s <= 4 && s <= by_traffic && s <= kt / 30; ++s)
+        if (filled(s) >= worth && filled(s) > filled(best) && (size_t)s * M * N * 4 <= partial_bytes_for(M, N, K))
+            best = s;
+    return best;
 }
 
 // Wavefronts per workgroup of the streaming kernel; `xt`: activations in tile order.
@@ -168,27 +194,7 @@ Workspace carve(void *ws, size_t bytes, int M, int K)
 size_t workspace_bytes_for(int M, int N, int K)
 {
     if (M < 1 || check_shape(N, K, 0) != FLEXQ_OK) return 0;
-    size_t partial = 0;
-    const int top = M < kSkinnyMaxM ? M : kSkinnyMaxM;
-    for (int m = 1; m <= top; ++m) {
-        const int ks = choose_split(m, N, K);
-        const size_t b = ks > 1 ? (size_t)ks * m * N * 4 : 0;
-        if (b > partial) partial = b;
-    }
-    {
-        const int gs = choose_gemm_split(M, N, K);
-        const size_t b = gs > 1 ? (size_t)gs * M * N * 4 : 0;
-        if (b > partial) partial = b;
-    }
-    if (const int pieces = flexq::low_cut_pieces(M, N, K); pieces != 0) {   // 128x256 tiles cut along K
-        const size_t b = flexq::low_cut_bytes((N + 255) / 256 * pieces);
-        if (b > partial) partial = b;
-    }
-    if (M > kSkinnyMaxM) {   // the 256x256 kernel's tail cut along K
-        const size_t b = flexq::streamk_plan(M, N, K).partial_bytes;
-        if (b > partial) partial = b;
-    }
-    return fixed_bytes(M, K) + round_up(partial, 256);
+    return fixed_bytes(M, K) + partial_bytes_for(M, N, K);
 }
 
 }  // namespace

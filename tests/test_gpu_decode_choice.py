@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,bits,want", [
     (11, 7680, 4096, 8, 1), (12, 7680, 4096, 8, 2), (16, 7680, 4096, 6, 502), (20, 7680, 4096, 6, 502),
     (32, 7680, 4096, 8, 502), (15, 11520, 5120, 6, 1), (16, 11520, 5120, 6, 503), (32, 11520, 5120, 8, 503),
-    (12, 4096, 4096, 6, 1), (13, 4096, 4096, 6, 501), (16, 4096, 4096, 8, 501), (12, 2048, 20512, 8, 1),
+    (12, 4096, 4096, 6, 1), (13, 4096, 4096, 6, 501), (16, 4096, 4096, 8, 501), (12, 2048, 20512, 8, 1), (32, 15360, 10240, 8, 503),
     (32, 2048, 20512, 6, 501)])
 def test_own_choice(M, K, N, bits, want):
     say(f"own choice: M={M} K={K} N={N} A{bits}")
