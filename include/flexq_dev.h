@@ -66,12 +66,13 @@ typedef struct {
  * 16: with the tiles beyond the last whole round of 256 each cut along K into split_k
  * pieces (for fewer than 256 tiles: all of them); 17, forced only: 13 with the
  * tail cut into 256 runs that cross tile borders; 18: group-128 scales, persistent 128x256
- * tiles, those beyond the last whole round of 256 each cut along K into split_k pieces),
- * s = the number of K splits
- * (for 13, 16, 17: the number of runs in all; for 14: of half tiles; for 18: of pieces
+ * tiles, those beyond the last whole round of 256 each cut along K into split_k pieces; 19:
+ * with those run at half the height, 64x256), s = the number of K splits
+ * (for 13, 16, 17: the number of runs in all; for 14: of half tiles; for 18, 19: of pieces
  * per cut tile; 500 more
  * when the streaming kernel read its activations in tile order).  Results are the same
- * whatever the overrides.
+ * whatever the overrides, but for group-128 scales, whose fp32 sums round by where K is cut:
+ * there the same bits go with the same K splits.
  */
 flexq_status flexq_dev_linear(const flexq_dev_tuning *tuning, int act_bits, const void *packed,
                               int group, const int8_t *xq, const uint16_t *sx,

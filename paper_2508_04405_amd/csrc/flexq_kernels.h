@@ -128,11 +128,13 @@ struct WldsChoice {
 WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut);
 WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes);   // tail_form 3 or 5
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st);
-// Group-128 scales (on both operands with a.sxg): 128x256 tiles of the same kernel, persistent,
-// the tiles beyond the last whole round of 256 each cut along K into `pieces` (1: run whole;
-// the area must hold low_cut_bytes(their number in all)).
-hipError_t launch_gemm_group(const LinearArgs &a, int pieces, hipStream_t st);
-// Pieces of a tail tile estimated to be fastest, within that many bytes of workspace.
-int group_tail_pieces(int M, int N, int K, size_t partial_bytes);
+// Group-128 scales (on both operands with a.sxg): 128x256 tiles of the same kernel, persistent;
+// the tiles beyond the last whole round of 256 run at half the height with `half`, and each is
+// cut along K into `pieces` (the area must hold low_cut_bytes(their number in all), with `half`
+// half as much).
+hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStream_t st);
+// Which of these forms is taken for `split_k` K splits, as the code that flexq_dev_linear
+// reports: 18, 19 (half height), or 0 for the 128x128 tiles.
+int group_form(int M, int N, int split_k, size_t partial_bytes);
 
 }  // namespace flexq

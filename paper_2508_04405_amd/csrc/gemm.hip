@@ -591,19 +591,17 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
     // by the vector unit.  128x128 tiles with two workgroups per CU keep the int32 sums out of the AGPR half
     // of the register file (which vector instructions cannot read directly).
     if (a.group != 0) {
-        // Above 128 tokens the persistent group tiles, faster by 10 to 50 % at every size
-        // measured.  From 65 tokens on where the workspace lets their pieces cover enough of the
-        // chip (97 tokens: 5120 x 13824 31 us as 160 pieces against 35, 57344 x 8192 88 as 224
-        // against 100, with token scales per group 15360 x 5120 35 as 120 against 40; but 5120 x
-        // 5120 25 as 60 against 21, and 15360 x 5120 at 65 tokens 31 as 120 against 29).
-        const int pieces = cfg == 18 ? a.split_k : group_tail_pieces(a.M, a.N, a.K, a.partial_bytes);
-        const long low_tiles = (long)((a.M + 127) / 128) * ((a.N + 255) / 256);
-        if (cfg == 18 || (cfg == 0 && (a.M > 128 || (a.M > 64 && low_tiles * pieces >= (a.sxg ? 112 : 150))))) {
+        // The sums over the groups are fp32, so where K is cut shows in the last bits.  Every
+        // form cuts it as choose_gemm_split says, for all rows alike, and adds the pieces in
+        // their order: which one runs is a matter of speed alone.
+        int form = cfg == 18 || cfg == 19 ? cfg : 0;
+        if (cfg == 0) form = group_form(a.M, a.N, a.split_k, a.partial_bytes);
+        if (form != 0) {
             LinearArgs b = a;
             b.split_k = 1;
-            *chosen = 18;
-            *tail_runs = pieces;
-            return launch_gemm_group(b, pieces, st);
+            *chosen = form;
+            *tail_runs = a.split_k;
+            return launch_gemm_group(b, form == 19, a.split_k, st);
         }
         if (a.sxg) return launch_cfg<1, 4, 4, 1, 2, 2>(a, st);          // scales per group on both operands
 #ifdef FLEXQ_DEV

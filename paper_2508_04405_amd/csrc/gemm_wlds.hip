@@ -103,17 +103,18 @@ constexpr int SLOT_BYTES = 256 * 256 * 4;      // one workgroup's int32 sums of 
 // activation reads: measured 2-5 % slower on every layer.)
 // TILE names the shape: 2 the whole tile (256 x 256), 1 the half tile (256 x 128), 3 the
 // low tile (128 x 256, 2 x 4 wavefronts of 64 x 64: for up to 128 tokens on wide layers),
-// 4 the group tile (128 x 256, eight wavefronts side by side of 128 x 32: group-128 scales)
+// 4 the group tile (128 x 256, eight wavefronts side by side of 128 x 32: group-128 scales),
+// 5 the same at half the height (64 x 256)
 template <int TILE>
 struct Shape {
-    static_assert(TILE >= 1 && TILE <= 4, "half, whole, low or group tiles");
-    static constexpr int WN = TILE == 1 ? 2 : TILE == 4 ? 8 : 4;
+    static_assert(TILE >= 1 && TILE <= 5, "half, whole, low or group tiles");
+    static constexpr int WN = TILE == 1 ? 2 : TILE >= 4 ? 8 : 4;
     static constexpr int MT = TILE == 2 || TILE == 4 ? 4 : 2;
-    static constexpr int NT = TILE == 4 ? 1 : 2;
+    static constexpr int NT = TILE >= 4 ? 1 : 2;
     static constexpr int BN = WN * NT * 32;
     static constexpr int BM = WAVES / WN * MT * 32;
     static_assert(BN == 256 || BN == 128, "whole or half width");
-    static_assert(BM == 256 || BM == 128, "whole or half height");
+    static_assert(BM == 256 || BM == 128 || (BM == 64 && TILE == 5), "whole, half or quarter height");
     static constexpr int XSTAGE = BM * 128;               // bytes of one activation stage
     static constexpr int XDMA = BM / 8 / WAVES;           // 1 KiB activation DMA loads per wavefront and stage
     static constexpr int WTILES = BN / 32;                        // packed tiles per stage
@@ -143,9 +144,9 @@ struct Shape {
     static constexpr int STG_END = STG + WAVES * 32 * ESTRIDE;
     // Group tiles: the scales of a stage follow everything else, a ring of four slots.
     static constexpr int SRING = STG_END > WBASE + 3 * WSTAGE ? STG_END : WBASE + 3 * WSTAGE;
-    static constexpr int SSLOT = BN * 2 + BM * 2;                 // weight scales, token scales
+    static constexpr int SSLOT = BN * 2 + 256;                    // weight scales, 128 token scales
     static constexpr int SF32 = SRING + 4 * SSLOT;                // the current stage's weight scales in fp32
-    static constexpr int LDS_BYTES = TILE == 4 ? SF32 + BN * 4 : SRING;
+    static constexpr int LDS_BYTES = TILE >= 4 ? SF32 + BN * 4 : SRING;
     static_assert(LDS_BYTES + 1024 <= 160 * 1024, "LDS of one CU (plus the static part)");
 };
 
@@ -179,17 +180,23 @@ struct Item {
 // that product has thirteen significant bits, so it is exact and the result rounds once, as
 // float(sum) * sw does; two operations instead of three (6 % less time).
 // Measured against 128 x 128 tiles of four wavefronts, two workgroups a CU (conversions and
-// mixed multiply-adds): 4096 x 8192 x 8192 297 us against 336, LLaMA-2-13B's down projection at
-// 2048 tokens 170 against 219 us, with scales on both operands 188 against 293, at 700 tokens
-// 77 against 146.  Without any DMA the first takes 268 us: the instruction stream and the
-// clock it runs at are the bound.
-template <int GROUP, class DmaX, class DmaW, class DmaS>
-__device__ __forceinline__ void group_item(v16f (&facc)[4][1], uint8_t *lds, int KN, int wave, int lane,
+// mixed multiply-adds): 4096 x 8192 x 8192 297 us against 336; without any DMA it takes 268:
+// the instruction stream and the clock it runs at are the bound.
+//
+// The half height, 64 x 256 with two blocks a stage and the same slots, is for layers that leave
+// the chip short of items: it takes three quarters of a whole item's time (the expansion and
+// the hand-over stay), but cuts the tokens, not the sums.  Cutting K of the last round's tiles
+// instead was up to a quarter faster still (13824 x 5120 at 700 tokens with both operands'
+// scales 74 us against 95, at 2048 tokens 172 against 202), but then rows of one call were summed
+// in one chain or in pieces by where they lay.  LLaMA-2-13B's down projection at 2048 tokens 202
+// us against 218, with scales on both operands 235 against 272, at 700 tokens 95 against 124.
+template <int TILE, int GROUP, class DmaX, class DmaW, class DmaS>
+__device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uint8_t *lds, int KN, int wave, int lane,
                                            const DmaX &dma_x, const DmaW &dma_w, const DmaS &dma_s)
 {
-    using S = Shape<4>;
+    using S = Shape<TILE>;
     constexpr int MT = S::MT, NB = S::MT;
-    static_assert(S::NT == 1 && MT == 4 && S::XBUFS == 3, "the slot tables below are written for this blocking");
+    static_assert(S::NT == 1 && (MT == 4 || MT == 2) && S::XBUFS == 3, "the slot tables below are written for these");
     const int arow = lane & 31, ahalf = lane >> 5;
     const int wfrag = S::WBASE + wave * FLEXQ_TILE_BYTES + lane * 16;
 
@@ -399,7 +406,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     constexpr int MT = S::MT, NT = S::NT;
     constexpr bool WHOLE = S::BN == 256;
     static_assert(!SK || WHOLE, "the tail is cut in whole-width tiles");
-    static_assert((GROUP != 0) == (TILE == 4) && !(GROUP && SK == 1), "group scales run group tiles");
+    static_assert((GROUP != 0) == (TILE >= 4) && !(GROUP && SK == 1), "group scales run group tiles");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -469,8 +476,8 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     auto locate = [&](const Item &it, Where &w) {
         int lane_l = lane;        // (opaque: recomputed per item rather than kept live, see the epilogue)
         asm volatile("" : "+v"(lane_l));
-        // super-block: 4 tiles along m (8 of half the height), then next n
-        constexpr int SUP_M = GROUP ? 8 : 4;
+        // super-block: 4 tiles along m (8 of half the height, 16 of a quarter), then next n
+        constexpr int SUP_M = TILE == 5 ? 16 : GROUP ? 8 : 4;
         const int bid = it.t256;
         const int sup = bid / (SUP_M * tiles_n);
         const int first_m = sup * SUP_M;
@@ -600,7 +607,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                 for (int r = 0; r < 16; ++r) acc[mt][nt][r] = 0;
 
         if constexpr (GROUP != 0) {
-            group_item<GROUP>(acc, lds, KN, wave, lane, [&](int kb, int buf) { dma_x(at, ks, kb, buf); },
+            group_item<TILE, GROUP>(acc, lds, KN, wave, lane, [&](int kb, int buf) { dma_x(at, ks, kb, buf); },
                               [&](int kb, int buf) { dma_w(at, ks, kb, buf); },
                               [&](int kb) { dma_s(at, ks, kb); });
         } else {
@@ -1226,8 +1233,9 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
 }
 
 // Group tiles (tiles_m counts 128-row tiles): `full_count` whole ones, then `tail_count` of
-// them each cut into tail_wgs / tail_count pieces.
-template <int GROUP>
+// shape TAIL: as many of the same (4), or those that follow at half the height (5).  Each of them
+// is cut into tail_wgs / tail_count pieces.
+template <int GROUP, int TAIL>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_group_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_count, int tail_count, int tail_wgs)
 {
@@ -1238,7 +1246,11 @@ void gemm_group_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_c
 #if defined(__HIP_DEVICE_COMPILE__)
     lds_barrier();     // the last epilogue's staging rows, as above
 #endif
-    run_items<4, 2, GROUP>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+    if constexpr (TAIL == 5)   // tile t is tiles 2 t and 2 t + 1 of half the height, in the same super-block order
+        run_items<5, 2, GROUP>(a, lds, s_last, full_count > 0 ? 2 * tiles_m : (a.M + 63) / 64, tiles_n, 2 * full_count,
+                               tail_count, tail_wgs);
+    else
+        run_items<4, 2, GROUP>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
 }
 
 }  // namespace
@@ -1371,58 +1383,66 @@ int grid_for(int items)
     return device_cu_count() == kStreamKGrid && g > kStreamKGrid ? kStreamKGrid : g;
 }
 
-template <int GROUP>
-hipError_t launch_group(const LinearArgs &a, int tiles_m, int tiles_n, int full, int tail, int pieces, hipStream_t st)
+template <int GROUP, int TAIL>
+hipError_t launch_group(const LinearArgs &a, int tiles_m, int tiles_n, int full, int tail, int tail_wgs, hipStream_t st)
 {
-    auto kern = gemm_group_kernel<GROUP>;
+    auto kern = gemm_group_kernel<GROUP, TAIL>;
+    constexpr int lds_bytes = kLdsMax(Shape<4>::LDS_BYTES, Shape<TAIL>::LDS_BYTES);
     static std::atomic<unsigned long long> lds_allowed{0};
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), Shape<4>::LDS_BYTES, lds_allowed);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds_bytes, lds_allowed);
         e != hipSuccess)
         return e;
-    const int g_full = full ? grid_for(full) : 0, g_tail = (tail * pieces + 7) / 8 * 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(g_full > g_tail ? g_full : g_tail)), dim3(64 * WAVES),
-                       Shape<4>::LDS_BYTES, st, a, tiles_m, tiles_n, full, tail, tail * pieces);
+    const int g_full = full ? grid_for(full) : 0, g_tail = (tail_wgs + 7) / 8 * 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g_full > g_tail ? g_full : g_tail)), dim3(64 * WAVES), lds_bytes, st, a,
+                       tiles_m, tiles_n, full, tail, tail_wgs);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// Estimated like the per-channel forms: a stage of a group tile takes 0.88 us while half of the
-// CUs have one, 1.15 us on a full chip; meeting costs by the pieces per tile and by their
-// number in all.  Measured on the 4096- to 28672-deep layers at 33 .. 2048 tokens, one to
-// sixteen pieces: the choice is within 4 % of the fastest.
-int group_tail_pieces(int M, int N, int K, size_t partial_bytes)
+// Whole items for one K split.  Measured at 65 .. 2048 tokens on twenty layers (512 .. 28672
+// deep, 1024 .. 57344 wide) against the 128x128 tiles: the half height takes 0.65 to 0.85 us a
+// stage where the whole one takes 0.9 to 1.15, so it is the faster one wherever its items fit a
+// round (13824 x 5120 at 97 tokens, 240 items in six splits: 24.4 us against 33.7; at 700, 220 whole
+// items, 78.9 against 92.2, with both operands' scales 94.8 against 124.2; a tail of 128 behind a
+// round, 2048 tokens, 202 against 218).  Else 128-row tiles: above 128 tokens always (8192 x
+// 28672 at 333 tokens, two splits, 121 against 145), up to there unsplit (57344 x 8192 at 97:
+// 84.5 against 102.5; with splits neither is ahead).  The choice is within 2 % of the fastest.
+int group_form(int M, int N, int split_k, size_t partial_bytes)
 {
-    const int tail = ((M + 127) / 128) * ((N + 255) / 256) % kStreamKGrid, KT = K / FLEXQ_TILE_K;
-    if (tail == 0 || device_cu_count() != kStreamKGrid) return 1;
-    int best = 1;
-    double best_us = 1e30;
-    for (int S = 1; S <= 16 && tail * S <= kStreamKGrid && S <= KT; ++S) {
-        const int all = tail * S;
-        if (S > 1 && partial_bytes < low_cut_bytes(all)) break;
-        const double us = (0.88 + (all > 128 ? 0.27 * (all - 128) / 128.0 : 0.0)) * ((KT + S - 1) / S) +
-                          (S > 1 ? 3.0 + 0.8 * S + 0.02 * all : 0.0);
-        if (us < best_us) {
-            best_us = us;
-            best = S;
-        }
-    }
-    return best;
+    if (M <= 64 || split_k > 16) return 0;
+    const int tiles_n = (N + 255) / 256, tiles = (M + 127) / 128 * tiles_n, tail = tiles % kStreamKGrid;
+    const bool whole_chip = device_cu_count() == kStreamKGrid, rounds = tiles >= kStreamKGrid;
+    if (split_k > 1 && (rounds || !whole_chip)) return 0;
+    const int halves = rounds ? 2 * tail : (M + 63) / 64 * tiles_n;
+    auto fits = [&](int items, size_t bytes) {
+        return items * split_k <= kStreamKGrid && (split_k == 1 || bytes <= partial_bytes);
+    };
+    if (whole_chip && halves > 0 && fits(halves, low_cut_bytes(halves * split_k) / 2)) return 19;
+    if (split_k == 1 || (M > 128 && fits(tiles, low_cut_bytes(tiles * split_k)))) return 18;
+    return 0;
 }
 
-hipError_t launch_gemm_group(const LinearArgs &a, int pieces, hipStream_t st)
+hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStream_t st)
 {
     if (a.group != 128 || a.split_k > 1) return hipErrorInvalidValue;
     const int tiles_m = (a.M + 127) / 128, tiles_n = (a.N + 255) / 256, tiles = tiles_m * tiles_n;
     int tail = tiles % kStreamKGrid;
-    if (pieces < 2 || tail == 0) {
-        tail = 0;
-    } else if (pieces > 16 || pieces > a.K / FLEXQ_TILE_K || tail * pieces > kStreamKGrid ||
-               a.partial_bytes < low_cut_bytes(tail * pieces) || device_cu_count() != kStreamKGrid) {
+    const int full = tiles - tail;
+    if (pieces < 1) pieces = 1;
+    if (half) tail = full ? 2 * tail : (a.M + 63) / 64 * tiles_n;
+    if (tail == 0 || (pieces == 1 && !half))
+        return a.sxg ? launch_group<2, 4>(a, tiles_m, tiles_n, tiles, 0, 0, st)
+                     : launch_group<1, 4>(a, tiles_m, tiles_n, tiles, 0, 0, st);
+    if (pieces > 16 || pieces > a.K / FLEXQ_TILE_K || tail * pieces > kStreamKGrid ||
+        (pieces > 1 && a.partial_bytes < low_cut_bytes(tail * pieces) / (half ? 2 : 1)) ||
+        device_cu_count() != kStreamKGrid)
         return hipErrorInvalidValue;
-    }
-    return a.sxg ? launch_group<2>(a, tiles_m, tiles_n, tiles - tail, tail, pieces, st)
-                 : launch_group<1>(a, tiles_m, tiles_n, tiles - tail, tail, pieces, st);
+    if (half)
+        return a.sxg ? launch_group<2, 5>(a, tiles_m, tiles_n, full, tail, tail * pieces, st)
+                     : launch_group<1, 5>(a, tiles_m, tiles_n, full, tail, tail * pieces, st);
+    return a.sxg ? launch_group<2, 4>(a, tiles_m, tiles_n, full, tail, tail * pieces, st)
+                 : launch_group<1, 4>(a, tiles_m, tiles_n, full, tail, tail * pieces, st);
 }
 
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st)

@@ -1,0 +1,98 @@
+"""Group-128 scales: the fp32 sums over the groups are taken in one order, whichever tiled kernel
+runs.  The library's own choice gives the bits of the 128x128 tiles with the same K splits, for
+every row of a call and with any workspace; the 64x256 tiles are compared with the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2508_04405_amd as fq
+from paper_2508_04405_amd import dev, synth
+
+from gpu_helpers import assert_y_close, group_slack, say, to_dev
+from test_gpu_xgroup import assert_close, reference
+
+pytestmark = pytest.mark.gpu
+
+
+def operands(M, K, N, both, bits=8, x16=None):
+    w = synth.weights(N, K, 0.02, seed=K + N)
+    x16 = synth.activations(M, K, seed=M, outlier_frac=0.02) if x16 is None else x16
+    packed = fq.pack_w6(*fq.quant_w6(to_dev(w), 128), 128)
+    codes = (fq.quant_act_g128 if both else fq.quant_act)(to_dev(x16), bits)
+    return w, x16, packed, codes
+
+
+def call(packed, N, K, codes, both, bits, ws):
+    if both:
+        return dev.linear_g128(packed, N, K, *codes, workspace=ws).cpu().numpy()
+    fn = dev.gemm_w6a6 if bits == 6 else dev.gemm_w6a8
+    return fn(packed, N, K, 128, xq=codes[0], sx=codes[1], workspace=ws).cpu().numpy()
+
+
+# want: the form and its K splits -- split or whole, at half the height or not, one round or
+# several, a tail of one tile, columns and rows that end inside a tile
+@pytest.mark.parametrize("both", [False, True])
+@pytest.mark.parametrize("M,K,N,want", [
+    (65, 4096, 5120, (8, 5)), (97, 8192, 8192, (19, 4)), (97, 2048, 16384, (19, 1)), (97, 8192, 10240, (19, 3)),
+    (100, 1536, 40960, (18, 1)), (129, 2048, 4096, (19, 1)), (200, 4480, 1056, (19, 2)), (200, 16384, 8192, (18, 4)),
+    (333, 1024, 13664, (18, 1)), (700, 4096, 5120, (19, 1)), (2048, 3200, 5120, (19, 1)), (1029, 256, 7456, (19, 1)),
+    (33 * 128, 384, 1824, (19, 1))])
+def test_same_bits_in_every_form(M, K, N, want, both):
+    say(f"group order: M={M} K={K} N={N} both={both}")
+    _, _, packed, codes = operands(M, K, N, both)
+    exact = fq.make_workspace(M, N, K)
+    roomy = fq.make_workspace(M, N, K, extra=64 << 20)
+    y = call(packed, N, K, codes, both, 8, exact)
+    launched = [dev.last_dispatch()]
+    again = call(packed, N, K, codes, both, 8, roomy)
+    launched.append(dev.last_dispatch())
+    dev.set_dispatch(2, 0, 0, 8)
+    try:
+        tiles = call(packed, N, K, codes, both, 8, exact)
+        launched.append(dev.last_dispatch())
+    finally:
+        dev.set_dispatch()
+    assert np.array_equal(y.view(np.uint16), tiles.view(np.uint16))
+    assert np.array_equal(again.view(np.uint16), tiles.view(np.uint16))
+    assert launched == [want, want, (8, want[1])]
+    assert int(exact[:16384].view(torch.int32).abs().sum()) == 0
+
+
+@pytest.mark.parametrize("both", [False, True])
+def test_equal_tokens_give_equal_rows(both):
+    """A round of whole tiles and a tail behind it: the second half of the tokens is the first again."""
+    M, K, N = 2048, 5120, 5120
+    say(f"group order, equal tokens, both={both}")
+    x16 = np.tile(synth.activations(M // 2, K, seed=7, outlier_frac=0.02), (2, 1))
+    _, _, packed, codes = operands(M, K, N, both, x16=x16)
+    y = call(packed, N, K, codes, both, 8, fq.make_workspace(M, N, K)).view(np.uint16)
+    assert np.array_equal(y[:M // 2], y[M // 2:])
+
+
+# (M, K, N, pieces): stage counts around the unrolled loop, tile edges; as in the 128-row form
+@pytest.mark.parametrize("spin", [0, -1])
+@pytest.mark.parametrize("both,bits", [(False, 6), (True, 8)])
+@pytest.mark.parametrize("M,K,N,pieces", [
+    (1, 128, 32, 1), (33, 256, 288, 2), (64, 384, 256, 3), (65, 512, 544, 1), (300, 640, 288, 5), (40, 768, 96, 6),
+    (129, 896, 320, 7), (131, 1024, 256, 4), (96, 1408, 640, 11), (200, 2048, 32, 16)])
+def test_half_height_tiles(M, K, N, pieces, both, bits, spin):
+    say(f"64x256 group tiles M={M} K={K} N={N} pieces={pieces} both={both} A{bits} spin={spin}")
+    w, x16, packed, codes = operands(M, K, N, both, bits)
+    ws = fq.make_workspace(M, N, K, extra=((M + 63) // 64) * ((N + 255) // 256) * pieces << 16)
+    dev.set_dispatch(2, pieces, 0, 19)
+    dev.set_spin(spin)
+    try:
+        out = [call(packed, N, K, codes, both, bits, ws) for _ in range(2)]    # the counters are left zero
+        assert dev.last_dispatch() == (19, pieces)
+        assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+    finally:
+        dev.set_dispatch()
+        dev.set_spin(0)
+    assert np.array_equal(out[0].view(np.uint16), out[1].view(np.uint16))
+    if both:
+        _, _, ry, slack = reference(x16, w, bits)
+        assert_close(out[0], ry, slack, "half height:")
+    else:
+        ref = oracle.linear(x16, w, bits, 128)
+        assert_y_close(out[0], ref["y"], group_slack(ref))
