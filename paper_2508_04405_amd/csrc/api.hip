@@ -127,8 +127,11 @@ int choose_split(int M, int N, int K, int forced = 0)
     return best;
 }
 
-// Wavefronts per workgroup of the streaming kernel; `xt`: activations in tile order.
-int choose_waves(int M, int N, int K, int ks, int xt, int forced = 0)
+// Wavefronts per workgroup of the streaming kernel; `xt`: activations in tile order.  With
+// group-128 scales the wavefronts' sums are fp32 and their number shows in the last bits: there
+// it depends on the shape alone, so that a call gives the same bits from fp16 activations (which
+// may go through tile order) and from their codes.
+int choose_waves(int M, int N, int K, int ks, int group, int xt, int forced = 0)
 {
     if (forced > 0) return forced;
     const int tiles = K / 128 / ks;
@@ -142,6 +145,11 @@ int choose_waves(int M, int N, int K, int ks, int xt, int forced = 0)
     // 19 vs 21 us at 16 tokens, 26 vs 27 at 32; 15360 x 5120 at 14 tokens 16.1 vs 16.9; with
     // the activations in LDS, 12288 x 4096 at 16 tokens, eight are faster, 15.3 vs 17.1)
     const long wgs = (long)(N / 32) * ks;
+    if (group != 0) {
+        if (M >= 16 && wgs > 256 && wgs < 512 && tiles >= 16) return 4;
+        if (wgs >= 640 && ((tiles <= 32 && M <= 4) || (tiles < 64 && M <= 2))) return 4;
+        return tiles >= 16 ? 8 : 4;
+    }
     const bool staged = xt == 0 && flexq::skinny_slice_fits(M, K, ks);
     if (M > 8 && ks == 1 && wgs > 256 && wgs < 512 && tiles >= 16 && !staged) return 4;
     // wide layers with short rows (the gate+up projections of LLaMA-2-7B and 13B: 688 and 864
@@ -379,7 +387,7 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
         if ((size_t)a.split_k * per_split > ws.partial_capacity)
             a.split_k = (int)(ws.partial_capacity / per_split);
         if (a.split_k < 1) a.split_k = 1;
-        if (flexq::launch_skinny(a, choose_waves(rows, N, K, a.split_k, xt, tune.waves), st) != hipSuccess)
+        if (flexq::launch_skinny(a, choose_waves(rows, N, K, a.split_k, group, xt, tune.waves), st) != hipSuccess)
             return FLEXQ_EHIP;
         if (dispatched) *dispatched = 1000 + a.split_k + (xt != 0 ? 500 : 0);
     }

@@ -96,3 +96,20 @@ def test_half_height_tiles(M, K, N, pieces, both, bits, spin):
     else:
         ref = oracle.linear(x16, w, bits, 128)
         assert_y_close(out[0], ref["y"], group_slack(ref))
+
+
+# tile order because the codes do not fit LDS, or would crowd it; one or several rounds of workgroups
+@pytest.mark.parametrize("bits", [6, 8])
+@pytest.mark.parametrize("K,N", [(4096, 12288), (5120, 15360), (4096, 22016), (7680, 4096), (2048, 20512)])
+def test_decode_from_fp16_and_from_codes(K, N, bits):
+    say(f"group order, decode: K={K} N={N} A{bits}")
+    w = synth.weights(N, K, 0.02, seed=K + N)
+    packed = fq.pack_w6(*fq.quant_w6(to_dev(w), 128), 128)
+    fn = fq.gemv_w6a6 if bits == 6 else fq.gemv_w6a8
+    for M in (1, 2, 6, 11, 13, 16, 17, 24, 32):
+        say(f"    {M} tokens")
+        x = to_dev(synth.activations(M, K, seed=M, outlier_frac=0.02))
+        xq, sx = fq.quant_act(x, bits)
+        a = fn(packed, N, K, 128, x_fp16=x).cpu().numpy()
+        b = fn(packed, N, K, 128, xq=xq, sx=sx).cpu().numpy()
+        assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), M
