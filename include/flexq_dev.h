@@ -48,6 +48,7 @@ extern "C" {
  *             (0 = the library's 128; -1 = never wait, every piece gives up at once:
  *             the path a busy or smaller device takes; at most 1 << 20)
  * With gemm_cfg 13, split_k > 1 asks for that many pieces per tile of the last round.
+ * gemm_cfg 12 to 17 with group-128 scales, and 18 or 19 without, return FLEXQ_EINVAL.
  */
 typedef struct {
     int kernel, split_k, waves, gemm_cfg, ablate, fuse, tiles, spin;

@@ -362,10 +362,13 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
         if ((size_t)a.split_k * per_split >= ((size_t)1 << 32)) a.split_k = 1;   // 32-bit buffer offsets
         if (a.split_k < 2) a.split_k = 1;
         int cfg = tune.gemm_cfg;
-        const int kt_max = K / 128;
         if (cfg == 0 && tune.split_k > 0 && a.split_k > 1) cfg = 8;   // a forced split is honoured
-        // (13: a forced split is the number of pieces per cut tile; the bounds above do not apply)
-        if (cfg == 13 || cfg == 16 || cfg == 18 || cfg == 19) a.split_k = tune.split_k > 1 ? (tune.split_k < kt_max ? tune.split_k : kt_max) : 1;
+        // (forms that cut tiles: a forced split is the number of pieces per cut tile; the bounds
+        // above do not apply, the launch checks its own)
+        if (group == 0 ? cfg == 13 || cfg == 16 : cfg == 18 || cfg == 19) {
+            a.split_k = tune.split_k < K / 128 ? tune.split_k : K / 128;
+            if (a.split_k < 1) a.split_k = 1;
+        }
         // room for the pieces by the shape, not by what this caller happens to bring
         if (group != 0 && cfg == 0 && a.split_k > 1) a.partial_bytes = partial_bytes_for(M, N, K);
         int chosen = 0, tail_runs = 0;

@@ -318,6 +318,11 @@ def test_dev_entry_points_argument_errors():
                 dict(ablate=-1), dict(kernel=-1), dict(fuse=3), dict(tiles=3), dict(spin=-2),
                 dict(spin=(1 << 20) + 1)):
         assert call(dict(zero, **bad)) == -1, bad
+    # tile forms that the call's scales do not have: their forced splits pass the clamp to the
+    # workspace, which only the form itself makes good
+    for cfg, group in [(18, 0), (19, 0)] + [(c, 128) for c in range(12, 18)]:
+        force = dict(zero, kernel=2, split_k=64, gemm_cfg=cfg)
+        assert call(force, group=group, M=128, N=4096, K=8192) == -1, (cfg, group)
     assert call(zero, bits=7) == -1
     assert call(zero, y=None) == -1              # the same checks as the product call, host side
     assert call(None, N=100) == -2
