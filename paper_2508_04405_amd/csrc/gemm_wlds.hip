@@ -175,10 +175,10 @@ struct Item {
 // fp32 adds and multiply-adds on vector registers.  So the MFMA chain starts from the bits of
 // 1.5 * 2^23 instead of zero -- the sum, read as a float, is then that constant plus the exact
 // integer (at most 2^21 in magnitude), and one add takes the constant off -- and the weight
-// scales are converted once per stage and wavefront, through LDS.  With scales on both
-// operands the constant comes off inside the multiplication, fma(bits, sw, -constant * sw):
-// that product has thirteen significant bits, so it is exact and the result rounds once, as
-// float(sum) * sw does; two operations instead of three (6 % less time).
+// scales are converted once per stage and wavefront, through LDS.  (With scales on both
+// operands the constant could come off inside the multiplication, fma(bits, sw, -constant * sw),
+// which is exact and saves one operation, 4 to 9 % on whole tiles, nothing on half ones: but an
+// infinite scale then meets its own product, and the result is NaN instead of that infinity.)
 // Measured against 128 x 128 tiles of four wavefronts, two workgroups a CU (conversions and
 // mixed multiply-adds): 4096 x 8192 x 8192 297 us against 336; without any DMA it takes 268:
 // the instruction stream and the clock it runs at are the bound.
@@ -189,7 +189,7 @@ struct Item {
 // instead was up to a quarter faster still (13824 x 5120 at 700 tokens with both operands'
 // scales 74 us against 95, at 2048 tokens 172 against 202), but then rows of one call were summed
 // in one chain or in pieces by where they lay.  LLaMA-2-13B's down projection at 2048 tokens 202
-// us against 218, with scales on both operands 235 against 272, at 700 tokens 95 against 124.
+// us against 218, with scales on both operands 231 against 272, at 700 tokens 93 against 124.
 template <int TILE, int GROUP, class DmaX, class DmaW, class DmaS>
 __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uint8_t *lds, int KN, int wave, int lane,
                                            const DmaX &dma_x, const DmaW &dma_w, const DmaS &dma_s)
@@ -206,7 +206,6 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
     constexpr int PB = GROUP == 2 ? 2 : 3;
     v16i part[PB];
     v4f sw[4];                         // this lane's sixteen channels' scales
-    v4f off[GROUP == 2 ? 4 : 1];       // GROUP == 2: minus the constant times each, exact
     uint16_t sx_next[MT];              // GROUP == 2: this lane's token's scale of each block
     float sx[MT];
     // Constants in vector registers: an operand from a scalar register halves the rate.
@@ -250,14 +249,14 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
     auto scale = [&](const v16i &p, int mt, int q) {
         float f[4], t[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float v = __int_as_float(p[4 * q + r]);
-            // (with both scales the constant comes off in the multiplication: its product with
-            // a scale is exact, so this rounds once, like float(sum) * sw)
-            f[r] = GROUP == 2 ? __builtin_fmaf(v, sw[q][r], off[GROUP == 2 ? q : 0][r]) : v + minus_magic;
-        }
+        for (int r = 0; r < 4; ++r) f[r] = __int_as_float(p[4 * q + r]) + minus_magic;
         // (all four before the first is used: a dependent pair back to back waits)
         asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
+        if (GROUP == 2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f[r] *= sw[q][r];
+            asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]));
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             t[r] = __builtin_fmaf(f[r], GROUP == 2 ? sx[mt] : sw[q][r], facc[mt][0][4 * q + r]);
@@ -279,7 +278,7 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
         for (int r = 0; r < 16; ++r) part[i][r] = 0;
     // "the stage before the first": finite sums times zero
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sw[q] = off[GROUP == 2 ? q : 0] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int q = 0; q < 4; ++q) sw[q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) sx[mt] = 0.0f;
 
@@ -336,10 +335,6 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
             constexpr int S0 = PB == 2 ? 0 : 1;        // the slot of the last use of the first quarter's
             if (s >= S0 && s < S0 + 4) {
                 sw[s - S0] = *reinterpret_cast<const v4f *>(sw32 + 8 * (s - S0) + 4 * ahalf);
-            }
-            if (GROUP == 2 && s >= 3 && s < 7) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) off[s - 3][r] = minus_magic * sw[s - 3][r];
             }
             if (GROUP == 2) {
                 if (s == 1) read_sx(kb);

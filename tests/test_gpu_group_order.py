@@ -113,3 +113,34 @@ def test_decode_from_fp16_and_from_codes(K, N, bits):
         a = fn(packed, N, K, 128, x_fp16=x).cpu().numpy()
         b = fn(packed, N, K, 128, xq=xq, sx=sx).cpu().numpy()
         assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), M
+
+
+@pytest.mark.parametrize("both", [False, True])
+@pytest.mark.parametrize("cfg", [8, 18, 19])
+def test_scales_that_are_not_finite(cfg, both):
+    """A packed weight scale may be infinite or NaN: a group whose sum is not zero gives that
+    sign's infinity, a zero sum NaN, and no other channel notices."""
+    M, K, N = 130, 640, 288
+    say(f"group scales not finite: form {cfg}, both={both}")
+    wq, sw = oracle.quantize(synth.weights(N, K, 0.02, seed=3), 6, 128)
+    sw[3, 1] = sw[200] = np.inf
+    sw[17, 0], sw[17, 4] = np.inf, -np.inf
+    sw[50, 2] = np.nan
+    x16 = synth.activations(M, K, seed=4, outlier_frac=0.02)
+    x16[5] = 0.0
+    x16[6, 128:256] = 0.0
+    packed = fq.pack_w6(to_dev(wq), to_dev(sw), 128)
+    xq, sx = oracle.quantize(x16.astype(np.float32), 8, 128 if both else 0)
+    acc_g = oracle.matmul(xq, wq, 128)
+    want = oracle.dequant_xgroup(acc_g, sx if both else np.repeat(sx.reshape(M, 1), K // 128, 1), sw).astype(np.float64)
+    codes = (fq.quant_act_g128 if both else fq.quant_act)(to_dev(x16), 8)
+    dev.set_dispatch(2, 1, 0, cfg)
+    try:
+        got = call(packed, N, K, codes, both, 8, None).astype(np.float64)
+    finally:
+        dev.set_dispatch()
+    assert np.isposinf(want).any() and np.isneginf(want).any() and np.isnan(want).sum() >= M
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    fine = np.isfinite(want)
+    assert np.allclose(got[fine], want[fine], rtol=2e-3, atol=2e-3)
