@@ -119,7 +119,9 @@ __device__ __forceinline__ uint16_t f2h(float f)
 // the fused remainder v - q * s is exact, and adding remainder * r rounds to
 // the correctly rounded quotient (Markstein's correction; it needs the
 // significand of s not to be all ones, and s is an fp16 value here).  Checked
-// over every pair of finite fp16 values v and s > 0 by tests/check_exact_division.c.
+// over every pair of finite fp16 values v and s > 0 (activations) by
+// tests/check_exact_division.c, and for fp32 v (weights) around every boundary
+// between two codes, and at random, by tests/check_weight_division.c.
 __device__ __forceinline__ float div_by(float v, float s, float r)
 {
     const float q = v * r;

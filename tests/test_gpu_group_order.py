@@ -144,3 +144,61 @@ def test_scales_that_are_not_finite(cfg, both):
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     fine = np.isfinite(want)
     assert np.allclose(got[fine], want[fine], rtol=2e-3, atol=2e-3)
+
+
+# more than a round of 128-row tiles: several items per workgroup, then the 14 (8) behind the round,
+# whole or cut, 128 rows high (18) or 64 (19), at one to five stages and unequal pieces
+@pytest.mark.parametrize("both,spin", [(False, 0), (False, -1), (True, 0), (True, -1)])
+@pytest.mark.parametrize("M,K,N,cfg,pieces", [
+    (1029, 128, 7680, 18, 1), (1029, 256, 7680, 18, 2), (1029, 640, 7456, 18, 3), (33 * 128, 384, 1824, 18, 3),
+    (1029, 128, 7680, 19, 1), (1029, 256, 7456, 19, 1), (1029, 640, 7456, 19, 4), (33 * 128, 384, 1824, 19, 2)])
+def test_rounds_then_a_tail(M, K, N, cfg, pieces, both, spin):
+    say(f"group tiles, a round and a tail: form {cfg} M={M} K={K} N={N} pieces={pieces} both={both} spin={spin}")
+    w, x16, packed, codes = operands(M, K, N, both)
+    ws = fq.make_workspace(M, N, K, extra=8 << 20)
+    dev.set_dispatch(2, pieces, 0, cfg)
+    dev.set_spin(spin)
+    try:
+        out = [call(packed, N, K, codes, both, 8, ws) for _ in range(2)]
+        assert dev.last_dispatch() == (cfg, pieces)
+        assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+    finally:
+        dev.set_dispatch()
+        dev.set_spin(0)
+    assert np.array_equal(out[0].view(np.uint16), out[1].view(np.uint16))
+    if both:
+        _, _, ry, slack = reference(x16, w, 8)
+        assert_close(out[0], ry, slack, "a round and a tail:")
+    else:
+        ref = oracle.linear(x16, w, 8, 128)
+        assert_y_close(out[0], ref["y"], group_slack(ref))
+
+
+@pytest.mark.parametrize("cfg", [18, 19])
+@pytest.mark.parametrize("both", [False, True])
+def test_soak_of_the_fp32_hand_off(cfg, both):
+    """1000 back-to-back calls on one workspace, every result compared bit for bit with the first,
+    stopping at the first mismatch; the counters end at zero."""
+    M, K, N, pieces = 100, 2304, 1120, 3
+    say(f"soak: group tiles, form {cfg}, both={both}")
+    _, _, packed, codes = operands(M, K, N, both)
+    ws = fq.make_workspace(M, N, K, extra=8 << 20)
+
+    def enqueue(out=None):
+        if both:
+            return dev.linear_g128(packed, N, K, *codes, workspace=ws, out=out)
+        return dev.gemm_w6a8(packed, N, K, 128, xq=codes[0], sx=codes[1], workspace=ws, out=out)
+
+    dev.set_dispatch(2, pieces, 0, cfg)
+    try:
+        first, y = enqueue(), torch.empty((M, N), dtype=torch.float16, device="cuda")
+        assert dev.last_dispatch() == (cfg, pieces)
+        differs = torch.zeros(1, dtype=torch.int32, device="cuda")
+        for rep in range(1000):
+            enqueue(y)
+            differs += (y != first).any()
+            if rep % 100 == 99:
+                assert int(differs.item()) == 0, ("a call among", rep - 99, "..", rep, "differs")
+    finally:
+        dev.set_dispatch()
+    assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
