@@ -587,9 +587,9 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
     if (!tail_runs) tail_runs = &unused_runs;
     *tail_runs = 0;
     *chosen = 8;   // the group modes run 128x128 tiles
-    // Group-128 scales cost two vector operations per accumulator and group: that mode is bound
-    // by the vector unit.  128x128 tiles with two workgroups per CU keep the int32 sums out of the AGPR half
-    // of the register file (which vector instructions cannot read directly).
+    // Group-128 scales cost two or three vector operations per accumulator and group: that mode
+    // is bound by the vector unit.  128x128 tiles with two workgroups per CU keep the int32 sums
+    // out of the AGPR half of the register file (which vector instructions cannot read directly).
     if (a.group != 0) {
         // The sums over the groups are fp32, so where K is cut shows in the last bits.  Every
         // form cuts it as choose_gemm_split says, for all rows alike, and adds the pieces in
@@ -686,9 +686,9 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
             // of); else the best form that leaves the workspace alone
             if (c.tail_form == 2 && c.us >= 0.95 * t_best) c = gemm_wlds_choose(a.M, a.N, a.K, false);
             const WldsChoice low = gemm_low_choose(a.M, a.N, a.K, a.partial_bytes);
-            // (against 256-row tiles cut along K the low
-            // tiles must promise 12 %: the two estimates are good to about 6 % each, and
-            // at 256 tokens of a 10240 x 8192 layer 36 against 33 us is where the line falls)
+            // (against 256-row tiles cut along K the low tiles must promise 12 %: the two
+            // estimates are good to about 6 % each, and at 256 tokens of a 10240 x 8192 layer
+            // 36 against 33 us is where the line falls)
             if (low.us < t_best && low.us < (c.tail_form == 2 ? 0.88 : 1.0) * c.us) {
                 LinearArgs b = a;
                 b.split_k = 1;

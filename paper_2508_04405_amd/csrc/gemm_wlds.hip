@@ -538,11 +538,10 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     // Group tiles: the stage's scales, two bytes each, by 4-byte DMA loads into a ring of four
     // slots: the eight weight tiles' 32 scales each (wavefronts 4 and 5, four tiles a load)
     // and, with group-wise token scales, the 128 rows' (wavefront 6).
-    const int KTs = KT;
     const __amdgpu_buffer_rsrc_t srsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)a.scales, 0, GROUP ? (unsigned)((long)N * KTs * 2) : 0u, 0x00020000);
+        (void *)a.scales, 0, GROUP ? (unsigned)((long)N * KT * 2) : 0u, 0x00020000);
     const __amdgpu_buffer_rsrc_t xsrsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(GROUP == 2 ? a.sxg : a.scales), 0, GROUP == 2 ? (unsigned)((long)KTs * a.sxg_stride * 2) : 0u,
+        (void *)(GROUP == 2 ? a.sxg : a.scales), 0, GROUP == 2 ? (unsigned)((long)KT * a.sxg_stride * 2) : 0u,
         0x00020000);
     auto dma_s = [&](const Where &w, int ks, int kb) {
         if constexpr (GROUP != 0) {
@@ -606,200 +605,200 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                               [&](int kb, int buf) { dma_w(at, ks, kb, buf); },
                               [&](int kb) { dma_s(at, ks, kb); });
         } else {
-        // operands that live across stages: the stage's packed tiles, the activation
-        // operands of two consecutive k-steps, the first weight operand of a stage
-        PackedTile wreg[NT];
-        v4i af[2][MT];
+            // operands that live across stages: the stage's packed tiles, the activation
+            // operands of two consecutive k-steps, the first weight operand of a stage
+            PackedTile wreg[NT];
+            v4i af[2][MT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const v4i *t = reinterpret_cast<const v4i *>(lds + wfrag + nt * FLEXQ_TILE_BYTES);
-            wreg[nt].q0 = t[0];          // the other two planes follow at the start of the stage
-        }
+            for (int nt = 0; nt < NT; ++nt) {
+                const v4i *t = reinterpret_cast<const v4i *>(lds + wfrag + nt * FLEXQ_TILE_BYTES);
+                wreg[nt].q0 = t[0];          // the other two planes follow at the start of the stage
+            }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            af[0][mt] = *reinterpret_cast<const v4i *>(lds + lds_off(arow + 32 * mt, ahalf));
-        v4i bf_first = unpack_kstep(wreg[0], 0);
+            for (int mt = 0; mt < MT; ++mt)
+                af[0][mt] = *reinterpret_cast<const v4i *>(lds + lds_off(arow + 32 * mt, ahalf));
+            v4i bf_first = unpack_kstep(wreg[0], 0);
 
-        // One 128-k stage.  CUR = kb % XBUFS names the activation buffer (a constant, so that
-        // the operand reads use immediate offsets), wcur = kb % 3 the weight buffer.
-        // The MFMA takes the WEIGHT fragment as its row operand: the accumulators hold D^T.
-        int wcur = 0;
-        auto stage = [&](int kb, auto cur_tag) {
-            constexpr int CUR = decltype(cur_tag)::value;
-            const bool more1 = kb + 1 < KN, more2 = kb + 2 < KN;
-            const int wnext = wcur == 2 ? 0 : wcur + 1, wnext2 = wcur == 0 ? 2 : wcur - 1;
-            // First what the hand-over waits for (with everything older, the weights of
-            // stage kb + 1 among it): the activations of stage kb + 1, where they run one
-            // stage ahead.  Then, during step 3, what may stay in flight across it: the
-            // loads for stage kb + 2.  All targets are free: an activation buffer was
-            // last read before the previous stage's barrier, and the weight buffer is that
-            // of stage kb - 1, whose last plane went to registers during that stage's first
-            // k-step, before its barrier.
-            if (S::XA == 1 && more1) dma_x(at, ks, kb + 1, (CUR + 1) % S::XBUFS);
-            if (S::XA == 2 && more2) dma_x(at, ks, kb + 2, (CUR + 2) % S::XBUFS);
+            // One 128-k stage.  CUR = kb % XBUFS names the activation buffer (a constant, so that
+            // the operand reads use immediate offsets), wcur = kb % 3 the weight buffer.
+            // The MFMA takes the WEIGHT fragment as its row operand: the accumulators hold D^T.
+            int wcur = 0;
+            auto stage = [&](int kb, auto cur_tag) {
+                constexpr int CUR = decltype(cur_tag)::value;
+                const bool more1 = kb + 1 < KN, more2 = kb + 2 < KN;
+                const int wnext = wcur == 2 ? 0 : wcur + 1, wnext2 = wcur == 0 ? 2 : wcur - 1;
+                // First what the hand-over waits for (with everything older, the weights of
+                // stage kb + 1 among it): the activations of stage kb + 1, where they run one
+                // stage ahead.  Then, during step 3, what may stay in flight across it: the
+                // loads for stage kb + 2.  All targets are free: an activation buffer was
+                // last read before the previous stage's barrier, and the weight buffer is that
+                // of stage kb - 1, whose last plane went to registers during that stage's first
+                // k-step, before its barrier.
+                if (S::XA == 1 && more1) dma_x(at, ks, kb + 1, (CUR + 1) % S::XBUFS);
+                if (S::XA == 2 && more2) dma_x(at, ks, kb + 2, (CUR + 2) % S::XBUFS);
 
-            const uint8_t *xs = lds + CUR * S::XSTAGE;
-            const uint8_t *xn = lds + ((CUR + 1) % S::XBUFS) * S::XSTAGE;
-            const uint8_t *wcb = lds + wfrag + wcur * S::WSTAGE;
-            const uint8_t *wnb = lds + wfrag + wnext * S::WSTAGE;
-            wcur = wnext;
-            // The packed planes of this stage's tiles not yet in registers: only plane 0 (the
-            // first k-step) is fetched after the hand-over, plane 1 during step 0 and plane 2
-            // during step 1, well before the steps that expand them.
-            auto rest_of_tiles = [&](int plane) {
-#pragma unroll
-                for (int n2 = 0; n2 < NT; ++n2) {
-                    const v4i *t = reinterpret_cast<const v4i *>(wcb + n2 * FLEXQ_TILE_BYTES);
-                    if (plane == 1) wreg[n2].q1 = t[64];
-                    if (plane == 2) wreg[n2].q2 = t[128];
-                }
-            };
-            // At the hand-over stage kb + 1 (weights and activations, every wavefront's
-            // share) must have landed; the loads for stage kb + 2 may be in flight.
-            auto hand_over = [&] {
-                constexpr int XFLY = S::XA == 2 ? S::XDMA : 0;
-                if (!more2)
-                    wait_vmcnt<0>();
-                else if (wave < S::WDMA_SPLIT)
-                    wait_vmcnt<XFLY + S::WDMA_LOW>();
-                else
-                    wait_vmcnt<XFLY + S::WDMA_HIGH>();
-                lds_barrier();
-                if (more1) {
+                const uint8_t *xs = lds + CUR * S::XSTAGE;
+                const uint8_t *xn = lds + ((CUR + 1) % S::XBUFS) * S::XSTAGE;
+                const uint8_t *wcb = lds + wfrag + wcur * S::WSTAGE;
+                const uint8_t *wnb = lds + wfrag + wnext * S::WSTAGE;
+                wcur = wnext;
+                // The packed planes of this stage's tiles not yet in registers: only plane 0 (the
+                // first k-step) is fetched after the hand-over, plane 1 during step 0 and plane 2
+                // during step 1, well before the steps that expand them.
+                auto rest_of_tiles = [&](int plane) {
 #pragma unroll
                     for (int n2 = 0; n2 < NT; ++n2) {
-                        const v4i *t = reinterpret_cast<const v4i *>(wnb + n2 * FLEXQ_TILE_BYTES);
-                        wreg[n2].q0 = t[0];
+                        const v4i *t = reinterpret_cast<const v4i *>(wcb + n2 * FLEXQ_TILE_BYTES);
+                        if (plane == 1) wreg[n2].q1 = t[64];
+                        if (plane == 2) wreg[n2].q2 = t[128];
                     }
+                };
+                // At the hand-over stage kb + 1 (weights and activations, every wavefront's
+                // share) must have landed; the loads for stage kb + 2 may be in flight.
+                auto hand_over = [&] {
+                    constexpr int XFLY = S::XA == 2 ? S::XDMA : 0;
+                    if (!more2)
+                        wait_vmcnt<0>();
+                    else if (wave < S::WDMA_SPLIT)
+                        wait_vmcnt<XFLY + S::WDMA_LOW>();
+                    else
+                        wait_vmcnt<XFLY + S::WDMA_HIGH>();
+                    lds_barrier();
+                    if (more1) {
+#pragma unroll
+                        for (int n2 = 0; n2 < NT; ++n2) {
+                            const v4i *t = reinterpret_cast<const v4i *>(wnb + n2 * FLEXQ_TILE_BYTES);
+                            wreg[n2].q0 = t[0];
+                        }
+                    }
+                };
+                static_assert((MT == 4 || MT == 2) && NT == 2, "the step tables below are written for these blockings");
+                if constexpr (MT == 2) {
+                    // 64 x 64 per wavefront: eight steps of two MFMAs, two dwords of the next
+                    // step's operand expanded per MFMA; the dearer operands of the fourth k-step
+                    // (steps 6 and 7) are spread over steps 2..5, one dword per MFMA
+                    v4i bfc = bf_first, bf6 = {0, 0, 0, 0}, bf7 = {0, 0, 0, 0};
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) {
+                        const int j = s >> 1, nt = s & 1;
+                        if (nt == 0) {
+                            if (j < 3) {
+#pragma unroll
+                                for (int mt = 0; mt < MT; ++mt)
+                                    af[(j + 1) & 1][mt] = *reinterpret_cast<const v4i *>(
+                                        xs + lds_off(arow + 32 * mt, 2 * (j + 1) + ahalf));
+                                if (j == 0) rest_of_tiles(1);
+                            } else {
+                                hand_over();
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (s == 1) {
+                            rest_of_tiles(2);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (s == 3 && more2) {
+                            dma_w(at, ks, kb + 2, wnext2);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (s == 7 && more1) {   // the next stage's first activation operands
+#pragma unroll
+                            for (int mt = 0; mt < MT; ++mt)
+                                af[0][mt] = *reinterpret_cast<const v4i *>(xn + lds_off(arow + 32 * mt, ahalf));
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        const v4i cur_b = s == 6 ? bf6 : s == 7 ? bf7 : bfc;
+                        v4i nxt = bfc;
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) {
+                            acc[mt][nt] = mfma_i8(cur_b, af[j & 1][mt], acc[mt][nt]);
+#pragma unroll
+                            for (int d = 2 * mt; d < 2 * mt + 2; ++d) {
+                                if (s < 5) nxt[d] = unpack_kstep_dword(wreg[(s + 1) & 1], (s + 1) >> 1, d);
+                                if (s == 7) nxt[d] = unpack_kstep_dword(wreg[0], 0, d);   // the next stage's first
+                            }
+                            if (s == 2) bf6[mt] = unpack_kstep_dword(wreg[0], 3, mt);
+                            if (s == 3) bf6[2 + mt] = unpack_kstep_dword(wreg[0], 3, 2 + mt);
+                            if (s == 4) bf7[mt] = unpack_kstep_dword(wreg[1], 3, mt);
+                            if (s == 5) bf7[2 + mt] = unpack_kstep_dword(wreg[1], 3, 2 + mt);
+                            {
+                                int p0 = nxt[2 * mt], p1 = nxt[2 * mt + 1], p2 = bf6[(s & 1) * 2 + mt],
+                                    p3 = bf7[(s & 1) * 2 + mt];
+                                asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3));   // pins the expansion here
+                                nxt[2 * mt] = p0;
+                                nxt[2 * mt + 1] = p1;
+                                bf6[(s & 1) * 2 + mt] = p2;
+                                bf7[(s & 1) * 2 + mt] = p3;
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        bfc = nxt;
+                    }
+                    bf_first = bfc;
+                } else {
+                    v4i bfc = bf_first, bf6, bf7;
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) {
+                        const int j = s >> 1, nt = s & 1;
+                        if (nt == 0) {
+                            if (j < 3) {
+#pragma unroll
+                                for (int mt = 0; mt < MT; ++mt)
+                                    af[(j + 1) & 1][mt] = *reinterpret_cast<const v4i *>(
+                                        xs + lds_off(arow + 32 * mt, 2 * (j + 1) + ahalf));
+                                if (j == 0) rest_of_tiles(1);
+                            } else {
+                                hand_over();
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (s == 1) {
+                            rest_of_tiles(2);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (s == 3 && more2) {
+                            dma_w(at, ks, kb + 2, wnext2);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (s == 7 && more1) {   // the next stage's first activation operands
+#pragma unroll
+                            for (int mt = 0; mt < MT; ++mt)
+                                af[0][mt] = *reinterpret_cast<const v4i *>(xn + lds_off(arow + 32 * mt, ahalf));
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        const v4i cur_b = s == 6 ? bf6 : s == 7 ? bf7 : bfc;
+                        v4i nxt = bfc;
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) {
+                            acc[mt][nt] = mfma_i8(cur_b, af[j & 1][mt], acc[mt][nt]);
+                            // shadow work of this MFMA: one dword of an operand that is due later
+                            if (s < 5) nxt[mt] = unpack_kstep_dword(wreg[(s + 1) & 1], (s + 1) >> 1, mt);
+                            if (s == 3) bf6[mt] = unpack_kstep_dword(wreg[0], 3, mt);
+                            if (s == 4) bf7[mt] = unpack_kstep_dword(wreg[1], 3, mt);
+                            if (s == 7) nxt[mt] = unpack_kstep_dword(wreg[0], 0, mt);   // the next stage's first
+                            {
+                                int p0 = nxt[mt], p1 = bf6[mt], p2 = bf7[mt];
+                                asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2));   // pins the expansion here
+                                nxt[mt] = p0;
+                                bf6[mt] = p1;
+                                bf7[mt] = p2;
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        bfc = nxt;
+                    }
+                    bf_first = bfc;
                 }
             };
-            static_assert((MT == 4 || MT == 2) && NT == 2, "the step tables below are written for these blockings");
-            if constexpr (MT == 2) {
-                // 64 x 64 per wavefront: eight steps of two MFMAs, two dwords of the next
-                // step's operand expanded per MFMA; the dearer operands of the fourth k-step
-                // (steps 6 and 7) are spread over steps 2..5, one dword per MFMA
-                v4i bfc = bf_first, bf6 = {0, 0, 0, 0}, bf7 = {0, 0, 0, 0};
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const int j = s >> 1, nt = s & 1;
-                    if (nt == 0) {
-                        if (j < 3) {
-#pragma unroll
-                            for (int mt = 0; mt < MT; ++mt)
-                                af[(j + 1) & 1][mt] = *reinterpret_cast<const v4i *>(
-                                    xs + lds_off(arow + 32 * mt, 2 * (j + 1) + ahalf));
-                            if (j == 0) rest_of_tiles(1);
-                        } else {
-                            hand_over();
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (s == 1) {
-                        rest_of_tiles(2);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (s == 3 && more2) {
-                        dma_w(at, ks, kb + 2, wnext2);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (s == 7 && more1) {   // the next stage's first activation operands
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            af[0][mt] = *reinterpret_cast<const v4i *>(xn + lds_off(arow + 32 * mt, ahalf));
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    const v4i cur_b = s == 6 ? bf6 : s == 7 ? bf7 : bfc;
-                    v4i nxt = bfc;
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        acc[mt][nt] = mfma_i8(cur_b, af[j & 1][mt], acc[mt][nt]);
-#pragma unroll
-                        for (int d = 2 * mt; d < 2 * mt + 2; ++d) {
-                            if (s < 5) nxt[d] = unpack_kstep_dword(wreg[(s + 1) & 1], (s + 1) >> 1, d);
-                            if (s == 7) nxt[d] = unpack_kstep_dword(wreg[0], 0, d);   // the next stage's first
-                        }
-                        if (s == 2) bf6[mt] = unpack_kstep_dword(wreg[0], 3, mt);
-                        if (s == 3) bf6[2 + mt] = unpack_kstep_dword(wreg[0], 3, 2 + mt);
-                        if (s == 4) bf7[mt] = unpack_kstep_dword(wreg[1], 3, mt);
-                        if (s == 5) bf7[2 + mt] = unpack_kstep_dword(wreg[1], 3, 2 + mt);
-                        {
-                            int p0 = nxt[2 * mt], p1 = nxt[2 * mt + 1], p2 = bf6[(s & 1) * 2 + mt],
-                                p3 = bf7[(s & 1) * 2 + mt];
-                            asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2), "+v"(p3));   // pins the expansion here
-                            nxt[2 * mt] = p0;
-                            nxt[2 * mt + 1] = p1;
-                            bf6[(s & 1) * 2 + mt] = p2;
-                            bf7[(s & 1) * 2 + mt] = p3;
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    bfc = nxt;
-                }
-                bf_first = bfc;
-            } else {
-                v4i bfc = bf_first, bf6, bf7;
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    const int j = s >> 1, nt = s & 1;
-                    if (nt == 0) {
-                        if (j < 3) {
-#pragma unroll
-                            for (int mt = 0; mt < MT; ++mt)
-                                af[(j + 1) & 1][mt] = *reinterpret_cast<const v4i *>(
-                                    xs + lds_off(arow + 32 * mt, 2 * (j + 1) + ahalf));
-                            if (j == 0) rest_of_tiles(1);
-                        } else {
-                            hand_over();
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (s == 1) {
-                        rest_of_tiles(2);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (s == 3 && more2) {
-                        dma_w(at, ks, kb + 2, wnext2);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (s == 7 && more1) {   // the next stage's first activation operands
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            af[0][mt] = *reinterpret_cast<const v4i *>(xn + lds_off(arow + 32 * mt, ahalf));
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    const v4i cur_b = s == 6 ? bf6 : s == 7 ? bf7 : bfc;
-                    v4i nxt = bfc;
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        acc[mt][nt] = mfma_i8(cur_b, af[j & 1][mt], acc[mt][nt]);
-                        // shadow work of this MFMA: one dword of an operand that is due later
-                        if (s < 5) nxt[mt] = unpack_kstep_dword(wreg[(s + 1) & 1], (s + 1) >> 1, mt);
-                        if (s == 3) bf6[mt] = unpack_kstep_dword(wreg[0], 3, mt);
-                        if (s == 4) bf7[mt] = unpack_kstep_dword(wreg[1], 3, mt);
-                        if (s == 7) nxt[mt] = unpack_kstep_dword(wreg[0], 0, mt);   // the next stage's first
-                        {
-                            int p0 = nxt[mt], p1 = bf6[mt], p2 = bf7[mt];
-                            asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2));   // pins the expansion here
-                            nxt[mt] = p0;
-                            bf6[mt] = p1;
-                            bf7[mt] = p2;
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    bfc = nxt;
-                }
-                bf_first = bfc;
-            }
-        };
 
-        int kb = 0;
-        for (; kb + S::XBUFS <= KN; kb += S::XBUFS) {
-            stage(kb, std::integral_constant<int, 0>{});
-            stage(kb + 1, std::integral_constant<int, 1>{});
-            if constexpr (S::XBUFS == 3) stage(kb + 2, std::integral_constant<int, 2>{});
-        }
-        if (kb < KN) stage(kb, std::integral_constant<int, 0>{});
-        if (S::XBUFS == 3 && kb + 1 < KN) stage(kb + 1, std::integral_constant<int, 1>{});
+            int kb = 0;
+            for (; kb + S::XBUFS <= KN; kb += S::XBUFS) {
+                stage(kb, std::integral_constant<int, 0>{});
+                stage(kb + 1, std::integral_constant<int, 1>{});
+                if constexpr (S::XBUFS == 3) stage(kb + 2, std::integral_constant<int, 2>{});
+            }
+            if (kb < KN) stage(kb, std::integral_constant<int, 0>{});
+            if (S::XBUFS == 3 && kb + 1 < KN) stage(kb + 1, std::integral_constant<int, 1>{});
         }
         // (every wavefront has passed the last stage's barrier with its LDS reads done: the
         // stage buffers are free)
@@ -933,8 +932,9 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                 s_last = all ? 1 + completed : 0;
             }
             lds_barrier();
-            int state = __builtin_amdgcn_readfirstlane(s_last);   // 0 gave up, 1 all sums there, 2 and this piece completed the count
-            lds_barrier();                                        // (read by all before it is written again)
+            // 0 gave up, 1 all sums there, 2 and this piece completed the count
+            int state = __builtin_amdgcn_readfirstlane(s_last);
+            lds_barrier();                       // (read by all before it is written again)
             if (state == 0) {
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
@@ -988,87 +988,87 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             finish = fin_slabs != 0;
         } else if constexpr (SK == 1) {
             if (KN != KT) {
-            // [slot][wavefront][block mt, nt][quarter][lane] 16-byte pieces: every store and
-            // load below is one contiguous KiB per wavefront.  Cache policy bit 4 = sc1 =
-            // device scope: the access goes to memory all XCDs share.
-            constexpr int kScopeAgent = 16;
-            const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
-                a.partial, 0, (unsigned)(2 * tail_wgs) * (unsigned)SLOT_BYTES, 0x00020000);
-            const unsigned in_slot = (unsigned)(wave * (SLOT_BYTES / WAVES) + lane * 16);
-            const int tj = cur.tj;
-            const long tile_begin = (long)tj * KT;
-            // a run leaves at most two partial tiles: slot 2 vt for the one it begins in,
-            // 2 vt + 1 for the one it ends in
-            const unsigned mine = (unsigned)(2 * vt + (run_begin < tile_begin ? 1 : 0)) * SLOT_BYTES + in_slot;
-            // The tile a run ends in is begun by this workgroup and finished by its successor,
-            // which reached it first thing: by now it has most likely arrived, and so has
-            // everybody else.  One look at the counter tells (it only ever grows until the
-            // last arrival; a workgroup adds to it after its stores are acknowledged): then
-            // this workgroup is the last without storing its own sums first.
-            int early = 0;
-            if (run_begin < tile_begin) {
-                if (tid == 0) {
-                    const unsigned seen = __hip_atomic_load(&a.counters[tj], __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT);
-                    s_last = (seen + (unsigned)KN == (unsigned)KT);
-                    if (s_last)
-                        __hip_atomic_store(&a.counters[tj], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                // [slot][wavefront][block mt, nt][quarter][lane] 16-byte pieces: every store and
+                // load below is one contiguous KiB per wavefront.  Cache policy bit 4 = sc1 =
+                // device scope: the access goes to memory all XCDs share.
+                constexpr int kScopeAgent = 16;
+                const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
+                    a.partial, 0, (unsigned)(2 * tail_wgs) * (unsigned)SLOT_BYTES, 0x00020000);
+                const unsigned in_slot = (unsigned)(wave * (SLOT_BYTES / WAVES) + lane * 16);
+                const int tj = cur.tj;
+                const long tile_begin = (long)tj * KT;
+                // a run leaves at most two partial tiles: slot 2 vt for the one it begins in,
+                // 2 vt + 1 for the one it ends in
+                const unsigned mine = (unsigned)(2 * vt + (run_begin < tile_begin ? 1 : 0)) * SLOT_BYTES + in_slot;
+                // The tile a run ends in is begun by this workgroup and finished by its successor,
+                // which reached it first thing: by now it has most likely arrived, and so has
+                // everybody else.  One look at the counter tells (it only ever grows until the
+                // last arrival; a workgroup adds to it after its stores are acknowledged): then
+                // this workgroup is the last without storing its own sums first.
+                int early = 0;
+                if (run_begin < tile_begin) {
+                    if (tid == 0) {
+                        const unsigned seen = __hip_atomic_load(&a.counters[tj], __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT);
+                        s_last = (seen + (unsigned)KN == (unsigned)KT);
+                        if (s_last)
+                            __hip_atomic_store(&a.counters[tj], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    lds_barrier();
+                    early = __builtin_amdgcn_readfirstlane(s_last);
                 }
-                lds_barrier();
-                early = __builtin_amdgcn_readfirstlane(s_last);
-            }
-            if (!early) {
+                if (!early) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+                    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
+                        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const v4u piece = {(unsigned)acc[mt][nt][4 * q], (unsigned)acc[mt][nt][4 * q + 1],
-                                               (unsigned)acc[mt][nt][4 * q + 2], (unsigned)acc[mt][nt][4 * q + 3]};
-                            __builtin_amdgcn_raw_buffer_store_b128(
-                                piece, prsrc, mine + (unsigned)(((mt * NT + nt) * 4 + q) * 1024), 0, kScopeAgent);
+                            for (int q = 0; q < 4; ++q) {
+                                const v4u piece = {(unsigned)acc[mt][nt][4 * q], (unsigned)acc[mt][nt][4 * q + 1],
+                                                   (unsigned)acc[mt][nt][4 * q + 2], (unsigned)acc[mt][nt][4 * q + 3]};
+                                __builtin_amdgcn_raw_buffer_store_b128(
+                                    piece, prsrc, mine + (unsigned)(((mt * NT + nt) * 4 + q) * 1024), 0, kScopeAgent);
+                            }
+                    // Once the stores are acknowledged (vmcnt 0) they are visible device-wide; the
+                    // barrier plus one relaxed device-scope add to the tile's stage count publishes
+                    // them.  Whoever brings the count to KT is the last and resets it.
+                    wait_vmcnt<0>();
+                    lds_barrier();
+                    if (tid == 0) {
+                        const unsigned prev = __hip_atomic_fetch_add(&a.counters[tj], (unsigned)KN, __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT);
+                        s_last = (prev + (unsigned)KN == (unsigned)KT);
+                        if (s_last)
+                            __hip_atomic_store(&a.counters[tj], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                    lds_barrier();
+                    finish = __builtin_amdgcn_readfirstlane(s_last) != 0;   // wavefront-uniform
+                }
+                if (finish) {
+                    // the runs that meet this tile: the one holding its first stage through the one
+                    // holding its last (run w is [w U / W, (w + 1) U / W))
+                    const long W = tail_wgs;
+                    const int va = (int)(((tile_begin + 1) * W + U - 1) / U) - 1;
+                    const int vb = (int)(((tile_begin + KT) * W + U - 1) / U) - 1;
+                    for (int w2 = va; w2 <= vb; ++w2) {
+                        if (w2 == vt) continue;
+                        const long begin2 = (long)w2 * U / W;
+                        const unsigned theirs =
+                            (unsigned)(2 * w2 + (begin2 < tile_begin ? 1 : 0)) * SLOT_BYTES + in_slot;
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) {
+                            v4u got[NT * 4];
+#pragma unroll
+                            for (int i = 0; i < NT * 4; ++i)
+                                got[i] = __builtin_amdgcn_raw_buffer_load_b128(
+                                    prsrc, theirs + (unsigned)((mt * NT * 4 + i) * 1024), 0, kScopeAgent);
+#pragma unroll
+                            for (int i = 0; i < NT * 4; ++i)
+#pragma unroll
+                                for (int c = 0; c < 4; ++c) acc[mt][i >> 2][4 * (i & 3) + c] += (int)got[i][c];
                         }
-                // Once the stores are acknowledged (vmcnt 0) they are visible device-wide; the
-                // barrier plus one relaxed device-scope add to the tile's stage count publishes
-                // them.  Whoever brings the count to KT is the last and resets it.
-                wait_vmcnt<0>();
-                lds_barrier();
-                if (tid == 0) {
-                    const unsigned prev = __hip_atomic_fetch_add(&a.counters[tj], (unsigned)KN, __ATOMIC_RELAXED,
-                                                                 __HIP_MEMORY_SCOPE_AGENT);
-                    s_last = (prev + (unsigned)KN == (unsigned)KT);
-                    if (s_last)
-                        __hip_atomic_store(&a.counters[tj], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                lds_barrier();
-                finish = __builtin_amdgcn_readfirstlane(s_last) != 0;   // wavefront-uniform
-            }
-            if (finish) {
-                // the runs that meet this tile: the one holding its first stage through the one
-                // holding its last (run w is [w U / W, (w + 1) U / W))
-                const long W = tail_wgs;
-                const int va = (int)(((tile_begin + 1) * W + U - 1) / U) - 1;
-                const int vb = (int)(((tile_begin + KT) * W + U - 1) / U) - 1;
-                for (int w2 = va; w2 <= vb; ++w2) {
-                    if (w2 == vt) continue;
-                    const long begin2 = (long)w2 * U / W;
-                    const unsigned theirs =
-                        (unsigned)(2 * w2 + (begin2 < tile_begin ? 1 : 0)) * SLOT_BYTES + in_slot;
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        v4u got[NT * 4];
-#pragma unroll
-                        for (int i = 0; i < NT * 4; ++i)
-                            got[i] = __builtin_amdgcn_raw_buffer_load_b128(
-                                prsrc, theirs + (unsigned)((mt * NT * 4 + i) * 1024), 0, kScopeAgent);
-#pragma unroll
-                        for (int i = 0; i < NT * 4; ++i)
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) acc[mt][i >> 2][4 * (i & 3) + c] += (int)got[i][c];
                     }
                 }
-            }
             }
         }
 
@@ -1151,20 +1151,20 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                         *reinterpret_cast<uint2 *>(stg + ml * S::ESTRIDE + (nt * 32 + 8 * q + 4 * hh) * 2) = out2;
                     }
                 if constexpr (!GROUP) {
-                if (a.acc_out) {     // the exact int32 sums, straight from the registers
-                    const int m = m_slab + ml;
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int n = n_wave + nt * 32 + 8 * q + 4 * hh;
-                            if (m < M && n < N) {
-                                const v4i four = {acc[mt][nt][4 * q] >> 2, acc[mt][nt][4 * q + 1] >> 2,
-                                                  acc[mt][nt][4 * q + 2] >> 2, acc[mt][nt][4 * q + 3] >> 2};
-                                *reinterpret_cast<v4i *>(a.acc_out + (long)m * N + n) = four;
+                    if (a.acc_out) {     // the exact int32 sums, straight from the registers
+                        const int m = m_slab + ml;
+    #pragma unroll
+                        for (int nt = 0; nt < NT; ++nt)
+    #pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const int n = n_wave + nt * 32 + 8 * q + 4 * hh;
+                                if (m < M && n < N) {
+                                    const v4i four = {acc[mt][nt][4 * q] >> 2, acc[mt][nt][4 * q + 1] >> 2,
+                                                      acc[mt][nt][4 * q + 2] >> 2, acc[mt][nt][4 * q + 3] >> 2};
+                                    *reinterpret_cast<v4i *>(a.acc_out + (long)m * N + n) = four;
+                                }
                             }
-                        }
-                }
+                    }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // own region only: no barrier
 #pragma unroll

@@ -87,7 +87,7 @@ flexq_status flexq_layer_linears(const flexq_layer *L, int M, const flexq_layer_
         return flexq::linear_impl(automatic, bits, w, L->group, xq, sx, x_fp16, M, N, K, y, nullptr, c.gemm,
                                   c.gemm_bytes, stream, nullptr, 0, nullptr, xt);
     };
-    // batches of 17 to 32 tokens: the producers write their codes in tile order (packed at
+    // batches of 11 to 32 tokens: the producers write their codes in tile order (packed at
     // 6 bits) where the streaming kernel reads them faster that way
     auto layout = [&](int bits, int N, int K) {
         return flexq::linear_wants_tiles(bits, M, N, K, L->group) ? bits : 0;
