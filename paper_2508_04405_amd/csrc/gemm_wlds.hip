@@ -47,8 +47,8 @@
 //   for a k-step in turn or for part of a stage (-1 % to -40 %: a wavefront alone does not
 //   keep the pipe busy, the two must interleave).
 //
-// Scales per channel; group-128 scales, on the weights or on both operands, run 128x256 tiles
-// of their own (group_item below).
+// Scales per channel; group-128 scales, on the weights or on both operands, run tiles of their
+// own, 128x256 and 64x256 (group_item below).
 //
 // A launch is PERSISTENT: at most one workgroup per CU, each taking its items
 // (tiles) one after the other, and the operands of the next item's first stages
@@ -186,10 +186,10 @@ struct Item {
 // The half height, 64 x 256 with two blocks a stage and the same slots, is for layers that leave
 // the chip short of items: it takes three quarters of a whole item's time (the expansion and
 // the hand-over stay), but cuts the tokens, not the sums.  Cutting K of the last round's tiles
-// instead was up to a quarter faster still (13824 x 5120 at 700 tokens with both operands'
-// scales 74 us against 95, at 2048 tokens 172 against 202), but then rows of one call were summed
-// in one chain or in pieces by where they lay.  LLaMA-2-13B's down projection at 2048 tokens 202
-// us against 218, with scales on both operands 231 against 272, at 700 tokens 93 against 124.
+// instead was up to a fifth faster still (13824 x 5120 at 700 tokens with both operands'
+// scales 74 us against 93, at 2048 tokens 172 against 193), but then rows of one call were summed
+// in one chain or in pieces by where they lay.  LLaMA-2-13B's down projection at 2048 tokens 193
+// us against 211, with scales on both operands 229 against 266, at 700 tokens 93 against 124.
 template <int TILE, int GROUP, class DmaX, class DmaW, class DmaS>
 __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uint8_t *lds, int KN, int wave, int lane,
                                            const DmaX &dma_x, const DmaW &dma_w, const DmaS &dma_s)
@@ -1399,10 +1399,11 @@ hipError_t launch_group(const LinearArgs &a, int tiles_m, int tiles_n, int full,
 // deep, 1024 .. 57344 wide) against the 128x128 tiles: the half height takes 0.65 to 0.85 us a
 // stage where the whole one takes 0.9 to 1.15, so it is the faster one wherever its items fit a
 // round (13824 x 5120 at 97 tokens, 240 items in six splits: 24.4 us against 33.7; at 700, 220 whole
-// items, 78.9 against 92.2, with both operands' scales 94.8 against 124.2; a tail of 128 behind a
-// round, 2048 tokens, 202 against 218).  Else 128-row tiles: above 128 tokens always (8192 x
+// items, 78.9 against 92.2, with both operands' scales 93 against 124; a tail of 128 behind a
+// round, 2048 tokens, 193 against 211).  Else 128-row tiles: above 128 tokens always (8192 x
 // 28672 at 333 tokens, two splits, 121 against 145), up to there unsplit (57344 x 8192 at 97:
-// 84.5 against 102.5; with splits neither is ahead).  The choice is within 2 % of the fastest.
+// 84.5 against 102.5; with splits neither is ahead).  Of the forms that the workspace has room
+// for, the choice is within 2 % of the fastest.
 int group_form(int M, int N, int split_k, size_t partial_bytes)
 {
     if (M <= 64 || split_k > 16) return 0;
