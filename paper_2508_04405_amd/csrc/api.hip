@@ -146,7 +146,7 @@ int choose_waves(int M, int N, int K, int ks, int group, int xt, int forced = 0)
     // the activations in LDS, 12288 x 4096 at 16 tokens, eight are faster, 15.3 vs 17.1)
     const long wgs = (long)(N / 32) * ks;
     if (group != 0) {
-        if (M >= 16 && wgs > 256 && wgs < 512 && tiles >= 16) return 4;
+        if (M >= 16 && ks == 1 && wgs > 256 && wgs < 512 && tiles >= 16) return 4;
         if (wgs >= 640 && ((tiles <= 32 && M <= 4) || (tiles < 64 && M <= 2))) return 4;
         return tiles >= 16 ? 8 : 4;
     }
