@@ -202,3 +202,44 @@ def test_soak_of_the_fp32_hand_off(cfg, both):
     finally:
         dev.set_dispatch()
     assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+
+
+@pytest.mark.parametrize("both", [False, True])
+def test_graph_replay_of_the_half_height_tiles(both):
+    """The quantizer and the library's own choice, tiles cut along K and a round with a tail,
+    captured in one graph: three replays with fresh inputs, eager work in between."""
+    say(f"group tiles, graph capture / replay, both={both}")
+    cases = []
+    for M, K, N, want in ((200, 4480, 1056, (19, 2)), (1029, 256, 7456, (19, 1))):
+        w, _, packed, _ = operands(M, K, N, both)
+        x = to_dev(synth.activations(M, K, seed=M))
+        cases.append((M, K, N, want, w, packed, x, fq.make_workspace(M, N, K),
+                      torch.empty((M, N), dtype=torch.float16, device="cuda")))
+
+    def enqueue():
+        for M, K, N, want, w, packed, x, ws, y in cases:
+            if both:
+                dev.linear_g128(packed, N, K, *fq.quant_act_g128(x, 8), workspace=ws, out=y)
+            else:
+                dev.gemm_w6a8(packed, N, K, 128, x_fp16=x, workspace=ws, out=y)
+            assert dev.last_dispatch() == want
+
+    enqueue()
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            enqueue()
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for M, K, *_, x, ws, y in cases:
+            x.copy_(to_dev(synth.activations(M, K, seed=100 * rep + M)))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [c[-1].clone() for c in cases]
+        enqueue()
+        torch.cuda.synchronize()
+        for c, g in zip(cases, got):
+            assert torch.equal(c[-1], g), rep
+    for c in cases:
+        assert int(c[-2][:16384].view(torch.int32).abs().sum()) == 0
