@@ -28,22 +28,9 @@
 // in the place of output channels (6-bit activations: 0.75 byte per value).
 #include "flexq_device.h"
 #include "flexq_kernels.h"
+#include "producer_math.h"
 
 namespace {
-
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
-__device__ __forceinline__ float wave_sum(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
 
 // Wave results meet in LDS and are combined in a fixed order.
 template <bool SUM, int WAVES>
@@ -57,20 +44,6 @@ __device__ __forceinline__ float block_reduce(float v, float *red)
     for (int i = 1; i < WAVES; ++i) r = SUM ? r + red[i] : fmaxf(r, red[i]);
     __syncthreads();
     return r;
-}
-
-__device__ __forceinline__ unsigned pack_h2(float lo, float hi)
-{
-    return (unsigned)f2h(lo) | ((unsigned)f2h(hi) << 16);
-}
-
-// g / (1 + e^-g) through v_exp_f32 and v_rcp_f32: each is good to an ulp of
-// fp32 and the product g * log2(e) to |g| * 2^-24 in the exponent, orders of
-// magnitude inside the half ulp of the fp16 result.  e^-g overflowing to
-// infinity gives g * 0 = -0, the correctly rounded value there.
-__device__ __forceinline__ float silu(float g)
-{
-    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.44269504088896341f));
 }
 
 template <int MODE, int CH, int T>
@@ -92,15 +65,6 @@ __global__ __launch_bounds__(T) void producer_kernel(const uint16_t *__restrict_
     float inv = 0.0f;
     if (MODE == 0) {
         float ss = 0.0f;
-        auto squares = [&](const uint4 &v) {
-            unsigned w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float a = h2f((uint16_t)(w4[i] & 0xffffu)), b = h2f((uint16_t)(w4[i] >> 16));
-                ss += a * a;
-                ss += b * b;
-            }
-        };
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int c = threadIdx.x + T * i;
@@ -114,37 +78,12 @@ __global__ __launch_bounds__(T) void producer_kernel(const uint16_t *__restrict_
         }
 #pragma unroll
         for (int i = 0; i < CH; ++i)
-            if (threadIdx.x + T * i < chunks) squares(held[i]);
+            if (threadIdx.x + T * i < chunks) add_squares(held[i], ss);
         ss = block_reduce<true, T / 64>(ss, red);
         inv = 1.0f / sqrtf(ss / (float)L + eps);
     }
 
-    // eight h values of a chunk from its first operand (x, or the gate half) and its second
-    auto make_h = [&](const uint4 &a, const uint4 &b) -> uint4 {
-        if (MODE == 2) return a;
-        unsigned a4[4] = {a.x, a.y, a.z, a.w}, b4[4] = {b.x, b.y, b.z, b.w}, o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float alo = h2f((uint16_t)(a4[i] & 0xffffu)), ahi = h2f((uint16_t)(a4[i] >> 16));
-            const float blo = h2f((uint16_t)(b4[i] & 0xffffu)), bhi = h2f((uint16_t)(b4[i] >> 16));
-            if (MODE == 0)
-                o[i] = pack_h2((alo * inv) * blo, (ahi * inv) * bhi);
-            else
-                o[i] = pack_h2(silu(alo) * blo, silu(ahi) * bhi);
-        }
-        return make_uint4(o[0], o[1], o[2], o[3]);
-    };
-
-    // fp16 magnitudes of finite values order like their bit patterns
     unsigned best = 0;
-    auto scan = [&](const uint4 &v) {
-        unsigned w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            best = max(best, w4[i] & 0x7fffu);
-            best = max(best, (w4[i] >> 16) & 0x7fffu);
-        }
-    };
     if (MODE != 0) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
@@ -158,19 +97,14 @@ __global__ __launch_bounds__(T) void producer_kernel(const uint16_t *__restrict_
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         if (threadIdx.x + T * i < chunks) {
-            held[i] = make_h(held[i], other[i]);
-            scan(held[i]);
+            held[i] = produce_h<MODE>(held[i], other[i], inv);
+            best = max_bits(held[i], best);
         }
     }
     const float amax = block_reduce<false, T / 64>(h2f((uint16_t)best), red);
 
-    float s32 = amax / qmax;
-    uint16_t bits = f2h(s32);
-    float sf = h2f(bits);
-    if (amax == 0.0f || sf == 0.0f) {
-        bits = 0x3c00;
-        sf = 1.0f;
-    }
+    const uint16_t bits = token_scale(amax, qmax);
+    const float sf = h2f(bits);
     if (threadIdx.x == 0) sx[row] = bits;
     const float qmin = -qmax - 1.0f;
 
