@@ -83,6 +83,18 @@ flexq_status flexq_dev_linear(const flexq_dev_tuning *tuning, int act_bits, cons
                               int *dispatched);
 
 /*
+ * flexq_layer_linears with overrides: tuning->fuse 1 = one launch for all the stages wherever its
+ * conditions allow (up to 16 tokens; buffers that do not overlap; no optional outputs), 2 =
+ * never; tuning->spin = polls before one of its workgroups stops waiting for the others and does
+ * what is missing itself (0 = the library's, -1 = at once).  *launched (may be NULL) receives 1
+ * for the one launch, else 0.  Results are the same either way.
+ */
+flexq_status flexq_dev_layer_linears(const flexq_dev_tuning *tuning, const flexq_layer *layer, int M,
+                                     const flexq_layer_io *io, int first_stage, int last_stage,
+                                     void *workspace, size_t workspace_bytes, void *stream,
+                                     int *launched);
+
+/*
  * Measurement helpers (no arithmetic of the method): the ceilings a roofline
  * fraction can be read against on the machine at hand.
  *

@@ -385,10 +385,8 @@ class Layer:
         return ws
 
 
-def layer_linears(layer, M, workspace, first_stage=0, last_stage=3, **buffers):
-    """flexq_layer_linears: `buffers` are the fp16 tensors of flexq_layer_io by name (x, qkv, attn,
-    o, x_ffn, gate_up, down, and the optional h_attn_norm, h_ffn_norm, h_swiglu); only those the
-    requested stages touch are needed."""
+def layer_io(layer, M, buffers):
+    """The flexq_layer_io of these fp16 tensors, by name."""
     shapes = dict(x=layer.H, qkv=layer.QKV, attn=layer.H, o=layer.H, x_ffn=layer.H, gate_up=2 * layer.F,
                   down=layer.H, h_attn_norm=layer.H, h_ffn_norm=layer.H, h_swiglu=layer.F)
     io = _LayerIO()
@@ -396,5 +394,13 @@ def layer_linears(layer, M, workspace, first_stage=0, last_stage=3, **buffers):
         _dev(t, torch.float16)
         assert t.shape == (M, shapes[name]), (name, tuple(t.shape))
         setattr(io, name, t.data_ptr())
+    return io
+
+
+def layer_linears(layer, M, workspace, first_stage=0, last_stage=3, **buffers):
+    """flexq_layer_linears: `buffers` are the fp16 tensors of flexq_layer_io by name (x, qkv, attn,
+    o, x_ffn, gate_up, down, and the optional h_attn_norm, h_ffn_norm, h_swiglu); only those the
+    requested stages touch are needed."""
+    io = layer_io(layer, M, buffers)
     _check(load().flexq_layer_linears(ctypes.byref(layer.c), M, ctypes.byref(io), first_stage, last_stage,
                                       _ptr(workspace), workspace.numel(), _stream()))

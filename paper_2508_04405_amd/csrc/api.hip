@@ -257,6 +257,12 @@ bool tiles_pay(int act_bits, int M, int K, int split_k)
 
 }  // namespace
 
+bool streams_as_eight(int M, int N, int K)
+{
+    const int ks = choose_split(M, N, K);
+    return ks == 1 && choose_waves(M, N, K, ks, 128, 0) == 8;
+}
+
 bool linear_wants_tiles(int act_bits, int M, int N, int K, int group)
 {
     return streams_by_choice(M, N, K, group, act_bits == 6) && tiles_pay(act_bits, M, K, choose_split(M, N, K));

@@ -38,4 +38,12 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
 // that runs a fused producer itself makes it write tiles then, and passes xt.
 bool linear_wants_tiles(int act_bits, int M, int N, int K, int group);
 
+// Group-128 scales: true where the streaming kernel sums in the order of eight wavefronts and one K split.
+bool streams_as_eight(int M, int N, int K);
+
+// flexq_layer_linears with overrides: fuse 1 = one launch wherever its conditions allow, 2 = never;
+// spin as above, for its waits.  *launched (may be null): 1 for the one launch, else 0.
+flexq_status layer_impl(const Tuning &tune, const flexq_layer *L, int M, const flexq_layer_io *io, int first_stage,
+                        int last_stage, void *workspace, size_t workspace_bytes, void *stream, int *launched);
+
 }  // namespace flexq

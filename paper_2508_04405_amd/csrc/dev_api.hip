@@ -40,5 +40,18 @@ flexq_status flexq_dev_linear(const flexq_dev_tuning *tuning, int act_bits, cons
                               workspace_bytes, stream, sxg, sxg_stride, dispatched);
 }
 
+flexq_status flexq_dev_layer_linears(const flexq_dev_tuning *tuning, const flexq_layer *layer, int M,
+                                     const flexq_layer_io *io, int first_stage, int last_stage, void *workspace,
+                                     size_t workspace_bytes, void *stream, int *launched)
+{
+    flexq::Tuning t;
+    if (tuning) {
+        if (tuning->fuse < 0 || tuning->fuse > 2 || tuning->spin < -1 || tuning->spin > (1 << 20)) return FLEXQ_EINVAL;
+        t.fuse = tuning->fuse;
+        t.spin = tuning->spin;
+    }
+    return flexq::layer_impl(t, layer, M, io, first_stage, last_stage, workspace, workspace_bytes, stream, launched);
+}
+
 }  // extern "C"
 #pragma GCC visibility pop

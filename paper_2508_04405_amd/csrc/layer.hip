@@ -3,6 +3,7 @@
 // activation width chosen per linear (Section 4.1.2: 8 bits for the down projection,
 // 6 bits elsewhere).  Host code only: it strings together the library's own launches.
 #include "api_internal.h"
+#include "decode_block.h"
 #include "flexq_kernels.h"
 
 namespace {
@@ -30,23 +31,105 @@ size_t gemm_ws_bytes(const flexq_layer *L, int M)
     return need;
 }
 
+struct Range {
+    const uint8_t *p;
+    size_t n;
+};
+inline bool overlap(const Range &a, const Range &b) { return a.p < b.p + b.n && b.p < a.p + a.n; }
+
 }  // namespace
 
-#pragma GCC visibility push(default)
-extern "C" {
+namespace flexq {
 
-size_t flexq_layer_workspace_bytes(const flexq_layer *L, int M)
+namespace {
+
+// The one-launch form of the call (decode_block.hip), where it applies: fills its arguments.  What it
+// gains is the launches between linears that do not wait for each other, so it is taken for calls
+// that hold stages 0 and 1 (measured on seven models of hidden size 512 .. 8192 at 1 .. 16 tokens,
+// stages 0 to 3: 0.82 .. 1.00 of the launches' time, LLaMA-2-7B's block at 8 tokens 56.4 -> 47.9 us,
+// 13B's 71.7 -> 61.6, 70B's at one token 125.5 -> 114.7; stages 0 and 1 alone 0.56 .. 0.88).  A wait
+// for another linear's outputs costs as much inside as two launches do (stages 2 and 3: 0.86 .. 1.17,
+// 1 and 2: 0.88 .. 1.27, one stage 0.73 .. 1.26): those keep the launches.
+bool one_launch(const flexq_layer *L, int M, const flexq_layer_io *io, int first, int last, void *workspace,
+                size_t room, bool forced, DecodeArgs &a, int &lds_bytes)
 {
-    if (!L || M < 1 || L->H < 1 || L->F < 1 || L->QKV < 1) return 0;
-    const size_t g = gemm_ws_bytes(L, M);
-    if (g == 0) return 0;
-    const int widest = L->H > L->F ? L->H : L->F;
-    // (fewer than 32 tokens: room for one block of 32-token tiles)
-    return g + round_up((size_t)(M < 32 ? 32 : M) * widest, 256) + round_up((size_t)M * 2, 256);
+    if (!forced && (first > 0 || last < 1)) return false;
+    if (M > 16 || L->H > 8192 || L->F > 32768 || device_cu_count() != kDecodeGrid) return false;
+    struct Stage {
+        const void *w;
+        const uint16_t *in, *gamma, *h;
+        uint16_t *y;
+        int N, K, row, bits, mode;
+    };
+    const Stage stages[4] = {
+        {L->w_qkv, io->x, L->gamma_attn, io->h_attn_norm, io->qkv, L->QKV, L->H, L->H, L->bits_qkv, 0},
+        {L->w_o, io->attn, nullptr, nullptr, io->o, L->H, L->H, L->H, L->bits_o, 2},
+        {L->w_gate_up, io->x_ffn, L->gamma_ffn, io->h_ffn_norm, io->gate_up, 2 * L->F, L->H, L->H, L->bits_gate_up, 0},
+        {L->w_down, io->gate_up, nullptr, io->h_swiglu, io->down, L->H, L->F, 2 * L->F, L->bits_down, 1}};
+    a.n = last - first + 1;
+    a.M = M;
+    a.group = L->group;
+    a.eps = L->eps;
+    a.words = (unsigned *)workspace;
+    a.spin = 256;
+    // every linear's codes and token scales in a place of its own, behind the counters
+    uint8_t *p = (uint8_t *)workspace + FLEXQ_WORKSPACE_COUNTER_BYTES, *const end = (uint8_t *)workspace + room;
+    Range in[4], out[4];
+    int taken = 0, pieces = 0;
+    lds_bytes = 0;
+    for (int i = 0; i < a.n; ++i) {
+        const Stage &s = stages[first + i];
+        const size_t tiles = (size_t)(s.N / 32) * (s.K / 128);
+        if (s.h || tiles * 3072 > 0xFFFFF000u) return false;
+        if (L->group != 0 && !streams_as_eight(M, s.N, s.K)) return false;
+        DecodePhase &ph = a.ph[i];
+        ph.packed = s.w;
+        ph.scales = (const uint16_t *)((const uint8_t *)s.w + tiles * 3072);
+        ph.y = s.y;
+        ph.nb = s.N / 32;
+        ph.kt = s.K / 128;
+        ph.off = taken % kDecodeGrid;      // the next linear's row blocks begin where this one's ended
+        taken += ph.nb;
+        ph.inv = (unsigned)((1ull << 32) / (unsigned)(ph.kt * 8) + 1);
+        ph.xq = (const int8_t *)p;
+        p += round_up((size_t)M * s.K, 256);
+        ph.sx = (uint16_t *)p;
+        p += 256;
+        const int lds = decode_block_lds(M, s.K);
+        if (lds > lds_bytes) lds_bytes = lds;
+        DecodeProducer &pr = a.pr[i];
+        pr.in = s.in;
+        pr.gamma = s.gamma;
+        pr.xq = (int8_t *)ph.xq;
+        pr.sx = ph.sx;
+        pr.L = s.K;
+        pr.mode = s.mode;
+        pr.qmax = s.bits == 6 ? 31.0f : 127.0f;
+        in[i] = Range{(const uint8_t *)s.in, (size_t)M * s.row * 2};
+        out[i] = Range{(const uint8_t *)s.y, (size_t)M * s.N * 2};
+        // an input is one of the outputs, all of it, or touches none
+        pr.dep = -1;
+        for (int q = 0; q < i; ++q) {
+            if (overlap(out[q], out[i])) return false;
+            if (in[i].p == out[q].p && in[i].n == out[q].n)
+                pr.dep = q;
+            else if (overlap(in[i], out[q]))
+                return false;
+        }
+        for (int q = 0; q <= i; ++q)
+            if (overlap(in[q], out[i])) return false;
+        if (pr.dep >= 0 && pr.dep != i - 1) return false;
+        pr.first = pr.dep < 0 ? pieces : 0;
+        if (pr.dep < 0) pieces += M * decode_pieces(pr.mode, pr.L);
+    }
+    if (p > end || lds_bytes > kDecodeLds) return false;
+    return true;
 }
 
-flexq_status flexq_layer_linears(const flexq_layer *L, int M, const flexq_layer_io *io, int first_stage,
-                                 int last_stage, void *workspace, size_t workspace_bytes, void *stream)
+}  // namespace
+
+flexq_status layer_impl(const Tuning &tune, const flexq_layer *L, int M, const flexq_layer_io *io, int first_stage,
+                        int last_stage, void *workspace, size_t workspace_bytes, void *stream, int *launched)
 {
     if (!L || !io || M < 1) return FLEXQ_EINVAL;
     if (first_stage < 0 || last_stage > 3 || first_stage > last_stage) return FLEXQ_EINVAL;
@@ -81,7 +164,16 @@ flexq_status flexq_layer_linears(const flexq_layer *L, int M, const flexq_layer_
     c.sx = (uint16_t *)(p + round_up((size_t)(M < 32 ? 32 : M) * widest, 256));
 
     hipStream_t st = (hipStream_t)stream;
-    const flexq::Tuning automatic{};
+    DecodeArgs one;
+    int lds_bytes = 0;
+    const bool block = tune.fuse != 2 && one_launch(L, M, io, first_stage, last_stage, workspace, need,
+                                                    tune.fuse == 1, one, lds_bytes);
+    if (launched) *launched = block ? 1 : 0;
+    if (block) {
+        if (tune.spin != 0) one.spin = tune.spin < 0 ? 0 : tune.spin;
+        return launch_decode_block(one, lds_bytes, st) == hipSuccess ? FLEXQ_OK : FLEXQ_EHIP;
+    }
+    const Tuning automatic{};
     auto gemm = [&](int bits, const void *w, const int8_t *xq, const uint16_t *sx, const uint16_t *x_fp16,
                     int N, int K, uint16_t *y, int xt) {
         return flexq::linear_impl(automatic, bits, w, L->group, xq, sx, x_fp16, M, N, K, y, nullptr, c.gemm,
@@ -119,6 +211,28 @@ flexq_status flexq_layer_linears(const flexq_layer *L, int M, const flexq_layer_
         if (r != FLEXQ_OK) return r;
     }
     return FLEXQ_OK;
+}
+
+}  // namespace flexq
+
+#pragma GCC visibility push(default)
+extern "C" {
+
+size_t flexq_layer_workspace_bytes(const flexq_layer *L, int M)
+{
+    if (!L || M < 1 || L->H < 1 || L->F < 1 || L->QKV < 1) return 0;
+    const size_t g = gemm_ws_bytes(L, M);
+    if (g == 0) return 0;
+    const int widest = L->H > L->F ? L->H : L->F;
+    // (fewer than 32 tokens: room for one block of 32-token tiles)
+    return g + round_up((size_t)(M < 32 ? 32 : M) * widest, 256) + round_up((size_t)M * 2, 256);
+}
+
+flexq_status flexq_layer_linears(const flexq_layer *L, int M, const flexq_layer_io *io, int first_stage,
+                                 int last_stage, void *workspace, size_t workspace_bytes, void *stream)
+{
+    return flexq::layer_impl(flexq::Tuning{}, L, M, io, first_stage, last_stage, workspace, workspace_bytes, stream,
+                             nullptr);
 }
 
 }  // extern "C"

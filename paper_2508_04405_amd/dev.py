@@ -38,6 +38,9 @@ def load():
     lib.flexq_dev_linear.argtypes = [ctypes.POINTER(Tuning), c_int, vp, c_int, vp, vp, vp, vp, c_int,
                                      c_int, c_int, c_int, vp, vp, vp, c_size, vp,
                                      ctypes.POINTER(c_int)]
+    lib.flexq_dev_layer_linears.restype = c_int
+    lib.flexq_dev_layer_linears.argtypes = [ctypes.POINTER(Tuning), vp, c_int, vp, c_int, c_int, vp, c_size, vp,
+                                            ctypes.POINTER(c_int)]
     lib.flexq_dev_probe_hbm_read.restype = c_int
     lib.flexq_dev_probe_hbm_read.argtypes = [vp, c_size, vp, vp]
     lib.flexq_dev_probe_mfma_i8.restype = c_int
@@ -124,6 +127,17 @@ def linear_g128(packed, N, K, xq, sxg, workspace=None, out=None):
     _dev(sxg, torch.float16)
     assert sxg.shape[0] == K // 128 and sxg.shape[1] >= xq.shape[0]
     return _linear(8, packed, N, K, 128, xq, None, None, sxg, workspace, False, out)
+
+
+def layer_linears(layer, M, workspace, first_stage=0, last_stage=3, **buffers):
+    """binding.layer_linears with this module's fuse and spin overrides; True if it was one launch."""
+    io = binding.layer_io(layer, M, buffers)
+    t = Tuning(**_tuning)
+    got = ctypes.c_int(0)
+    _check(load().flexq_dev_layer_linears(ctypes.byref(t), ctypes.byref(layer.c), M, ctypes.byref(io), first_stage,
+                                          last_stage, _ptr(workspace), workspace.numel(), _stream(),
+                                          ctypes.byref(got)))
+    return got.value == 1
 
 
 def probe_hbm_read(buf, sink):

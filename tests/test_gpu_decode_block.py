@@ -1,0 +1,180 @@
+"""A decoder block's linears in one launch (decode_block.hip) against the separate launches, which
+test_gpu_layer.py holds against the CPU oracle: the same bits for every stage, whoever does the
+work -- with waits that run out at once (spin -1) every workgroup does what the others have not
+finished, the way out on a busy or smaller device."""
+import pytest
+import torch
+
+import paper_2508_04405_amd as fq
+from paper_2508_04405_amd import dev, synth
+
+from gpu_helpers import DEV, build_packed, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("qkv", "o", "gate_up", "down")
+
+
+class Block:
+    """Packed weights of a small block, its layer descriptor for given activation widths, and buffers."""
+
+    def __init__(self, H, F, QKV, group, seed=1):
+        self.H, self.F, self.QKV, self.group = H, F, QKV, group
+        shapes = ((QKV, H), (H, H), (2 * F, H), (H, F))
+        self.packed = [build_packed(n, k, 0.02, seed + i, group) for i, (n, k) in enumerate(shapes)]
+        self.gains = [to_dev(synth.norm_gain(H, seed=seed + i)) for i in (10, 11)]
+
+    def layer(self, bits):
+        return fq.Layer(self.H, self.F, self.QKV, self.group, *self.packed, *self.gains, 1e-5, bits)
+
+    def inputs(self, M, seed):
+        return {k: to_dev(synth.activations(M, self.H, seed=seed + i, outlier_frac=0.02)) for i, k in enumerate(("x", "attn"))}
+
+    def outputs(self, M):
+        return {k: torch.full((M, n), float("nan"), dtype=torch.float16, device=DEV)
+                for k, n in zip(NAMES, (self.QKV, self.H, 2 * self.F, self.H))}
+
+
+def run(layer, M, ws, fuse, spin=0, first=0, last=3, **buffers):
+    dev.set_fuse(fuse)
+    dev.set_spin(spin)
+    try:
+        return dev.layer_linears(layer, M, ws, first, last, **buffers)
+    finally:
+        dev.set_fuse(0)
+        dev.set_spin(0)
+
+
+def equal(a, b):
+    return [k for k in a if not torch.equal(a[k].view(torch.int16), b[k].view(torch.int16))] == []
+
+
+# one row block per workgroup or none, several and a part; rows of one turn of tiles, of turns that do
+# not divide, of more than one piece (4096) per token; turns of four and of five tiles
+@pytest.mark.parametrize("group", [0, 128])
+@pytest.mark.parametrize("H,F,QKV", [(128, 256, 96), (640, 1152, 800), (1024, 2816, 3072), (2048, 5632, 6144),
+                                     (1280, 4224, 18464), (4224, 1152, 128), (4096, 4096, 4128)])
+def test_one_launch_equals_the_separate_ones(H, F, QKV, group):
+    block = Block(H, F, QKV, group)
+    launched = 0
+    for bits in ((6, 6, 6, 8), (8, 6, 8, 6)):
+        layer = block.layer(bits)
+        for M in (1, 2, 7, 8, 9, 16):
+            say(f"one launch: H={H} F={F} QKV={QKV} group={group} A{bits} M={M}")
+            ws, data, want = layer.make_workspace(M), block.inputs(M, 100 * M), block.outputs(M)
+            assert not run(layer, M, ws, 2, x_ffn=want["o"], **data, **want)
+            for spin in (0, -1):
+                got = block.outputs(M)
+                if not run(layer, M, ws, 1, spin, x_ffn=got["o"], **data, **got):
+                    assert group == 128          # its sums would have another order
+                    continue
+                launched += 1
+                torch.cuda.synchronize()
+                assert equal(got, want), (M, spin)
+                assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+            got = block.outputs(M)
+            fq.layer_linears(layer, M, ws, x_ffn=got["o"], **data, **got)
+            assert equal(got, want)
+    assert launched > 0 or (group == 128 and H < 4096) or QKV == 128
+
+
+@pytest.mark.parametrize("first,last", [(0, 1), (0, 2), (1, 3), (2, 3), (0, 0), (3, 3)])
+def test_ranges_of_stages_and_an_input_of_its_own(first, last):
+    block, M = Block(1024, 2816, 3072, 0), 5
+    layer = block.layer((6, 6, 6, 8))
+    ws, data = layer.make_workspace(M), block.inputs(M, 3)
+    data["x_ffn"] = to_dev(synth.activations(M, block.H, seed=9))
+    gate_up = to_dev(synth.activations(M, 2 * block.F, seed=10))
+    for spin in (0, -1):
+        outs = []
+        for fuse in (2, 1):
+            outs.append(block.outputs(M))
+            outs[-1]["gate_up"].copy_(gate_up)
+            assert run(layer, M, ws, fuse, spin, first, last, **data, **outs[-1]) == (fuse == 1)
+        assert equal(*outs), (first, last, spin)
+
+
+def test_buffers_that_overlap_keep_the_separate_launches():
+    block, M = Block(1024, 2816, 3072, 0), 2
+    layer, H = block.layer((6, 6, 6, 8)), 1024
+    ws, data = layer.make_workspace(M), block.inputs(M, 3)
+    out = block.outputs(M)
+    assert run(layer, M, ws, 1, x_ffn=out["o"], **data, **out)
+    flat = out["qkv"].view(-1)
+    inside = flat[:M * H].view(M, H)                       # of the qkv output, not all of it
+    assert not run(layer, M, ws, 1, x_ffn=out["o"], x=data["x"], attn=inside, **out)
+    assert not run(layer, M, ws, 1, x_ffn=inside, **data, **out)
+    assert not run(layer, M, ws, 1, x_ffn=out["o"], **data, **dict(out, down=data["x"]))
+    assert not run(layer, M, ws, 1, x_ffn=out["o"], **data, **dict(out, o=inside))
+    assert not run(layer, M, ws, 1, x_ffn=out["o"], h_swiglu=torch.empty((M, block.F), dtype=torch.float16, device=DEV),
+                   **data, **out)
+    assert not run(layer, 17, layer.make_workspace(17), 1, x_ffn=(o := block.outputs(17))["o"], **block.inputs(17, 1), **o)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("group", [0, 128])
+def test_fresh_inputs_on_one_workspace(group):
+    """Two hundred back-to-back calls with eight sets of inputs in turn: no value of an earlier call,
+    in the codes, the outputs or the words between workgroups, shows in a later one."""
+    block, M = Block(2048, 5632, 6144, group) if group == 0 else Block(4096, 4096, 4128, group), 6
+    layer = block.layer((6, 6, 6, 8))
+    ws = layer.make_workspace(M)
+    sets = [block.inputs(M, 50 * i) for i in range(8)]
+    wants = []
+    for data in sets:
+        wants.append(block.outputs(M))
+        run(layer, M, ws, 2, x_ffn=wants[-1]["o"], **data, **wants[-1])
+    out, differs = block.outputs(M), torch.zeros(1, dtype=torch.int32, device=DEV)
+    for rep in range(200):
+        i = (5 * rep + rep // 8) % 8
+        assert run(layer, M, ws, 1, x_ffn=out["o"], **sets[i], **out)
+        for k in NAMES:
+            differs += (out[k] != wants[i][k]).any()
+        if rep % 50 == 49:
+            assert int(differs.item()) == 0, rep
+    assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+
+
+def test_two_streams_at_once():
+    """Two blocks on two streams, each with buffers of its own: whichever workgroups are resident, both
+    give the bits they give alone."""
+    block, M = Block(1024, 2816, 3072, 0), 4
+    layer = block.layer((6, 6, 6, 8))
+    lanes = []
+    for i in range(2):
+        data, want = block.inputs(M, 70 * i), block.outputs(M)
+        ws = layer.make_workspace(M)
+        run(layer, M, ws, 2, x_ffn=want["o"], **data, **want)
+        lanes.append((torch.cuda.Stream(), ws, data, want, block.outputs(M)))
+    torch.cuda.synchronize()
+    for rep in range(20):
+        for stream, ws, data, want, out in lanes:
+            with torch.cuda.stream(stream):
+                assert run(layer, M, ws, 1, x_ffn=out["o"], **data, **out)
+    torch.cuda.synchronize()
+    for stream, ws, data, want, out in lanes:
+        assert equal(out, want)
+        assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+
+
+def test_graph_replay():
+    block, M = Block(1024, 2816, 3072, 0), 3
+    layer = block.layer((6, 6, 6, 8))
+    ws, data, out = layer.make_workspace(M), block.inputs(M, 1), block.outputs(M)
+    assert run(layer, M, ws, 1, x_ffn=out["o"], **data, **out)
+    torch.cuda.synchronize()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            assert run(layer, M, ws, 1, x_ffn=out["o"], **data, **out)
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for k, v in block.inputs(M, 200 * rep + 7).items():
+            data[k].copy_(v)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = {k: v.clone() for k, v in out.items()}
+        run(layer, M, ws, 2, x_ffn=out["o"], **data, **out)
+        torch.cuda.synchronize()
+        assert equal(got, out), rep
+    assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
