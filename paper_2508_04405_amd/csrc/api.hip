@@ -362,6 +362,8 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
         a.y = y;
         a.acc_out = acc_out;
         a.split_k = choose_gemm_split(M, N, K, tune.split_k);
+        if (group != 0 && tune.split_k == 0)
+            a.split_k = flexq::group_split(M, N, K, a.split_k, partial_bytes_for(M, N, K));
         const size_t per_split = (size_t)M * N * 4;
         if ((size_t)a.split_k * per_split > ws.partial_capacity)
             a.split_k = (int)(ws.partial_capacity / per_split);

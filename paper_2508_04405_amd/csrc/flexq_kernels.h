@@ -136,5 +136,8 @@ hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStre
 // Which of these forms is taken for `split_k` K splits, as the code that flexq_dev_linear
 // reports: 18, 19 (half height), or 0 for the 128x128 tiles.
 int group_form(int M, int N, int split_k, size_t partial_bytes);
+// K splits of a group-128 layer on tiled kernels: `ks`, or more where few tiles leave the chip idle
+// and the sums fit partial_bytes (the area by the shape).
+int group_split(int M, int N, int K, int ks, size_t partial_bytes);
 
 }  // namespace flexq

@@ -1419,6 +1419,46 @@ int group_form(int M, int N, int split_k, size_t partial_bytes)
     return 0;
 }
 
+// K splits for group-128 scales above 128 tokens: `ks` (choose_gemm_split's, which bounds the partial
+// sums by the weights' bytes), or more where that leaves most of the chip idle -- an item's chain of
+// stages is then the whole time, and the sums are cheap.  Estimated as the time of one round: a
+// stage of a 64x256 item takes 0.59 us while at most half of the CUs have one, 0.74 on a full chip,
+// of a 128x256 item 0.86 and 1.08, plus 4.4 and 6.8 us; S pieces meet in 2.5 + 0.55 S us and what their
+// number in all costs.  Measured over 150 .. 3667 tokens, 1024 .. 24448 deep, 512 .. 5120 wide: 700 tokens
+// of 8576 x 512 44 -> 18.5 us, 1101 of 13824 x 512 68 -> 24, 2000 of 24448 x 512 117 -> 46, 500 of 13824 x
+// 5120 72 -> 53; with scales on both operands 700 of 13824 x 5120, with the quantizer, 98.5 -> 87.8.  A function of the shape alone,
+// for every row alike.  The splits show in the sums' last bits, so an unsplit layer is only cut for 7 %
+// of the time, one that is cut already only cut anew for a quarter of it.
+int group_split(int M, int N, int K, int ks, size_t partial_bytes)
+{
+    const int KT = K / FLEXQ_TILE_K, tiles_n = (N + 255) / 256;
+    const int tiles = (M + 127) / 128 * tiles_n, halves = (M + 63) / 64 * tiles_n;
+    if (M <= 128 || tiles >= kStreamKGrid) return ks;
+    auto round_us = [&](int pieces) {       // in the form group_form takes; 0: neither fits
+        const bool half = halves * pieces <= kStreamKGrid;
+        if (!half && tiles * pieces > kStreamKGrid) return 0.0;
+        const int n = (half ? halves : tiles) * pieces;
+        const double busy = n > 128 ? (n - 128) / 128.0 : 0.0;
+        const double stage = half ? 0.59 + 0.15 * busy : 0.86 + 0.22 * busy;
+        const double meet = pieces > 1 ? 2.5 + 0.55 * pieces + (half ? 0.008 : 0.02) * n : 0.0;
+        return stage * ((KT + pieces - 1) / pieces) + (half ? 4.4 : 6.8) + meet;
+    };
+    const double now = round_us(ks);
+    if (now == 0.0) return ks;
+    int best = ks;
+    double t_best = (ks == 1 ? 0.93 : 0.76) * now;
+    for (int s = ks + 1; s <= 16 && s <= KT / 4 && tiles * s <= kStreamKGrid; ++s) {
+        const bool half = halves * s <= kStreamKGrid;
+        const size_t area = half ? low_cut_bytes(halves * s) / 2 : low_cut_bytes(tiles * s);
+        if (area > partial_bytes || (size_t)s * M * N * 4 > partial_bytes) break;
+        if (const double t = round_us(s); t < t_best) {
+            t_best = t;
+            best = s;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStream_t st)
 {
     if (a.group != 128 || a.split_k > 1) return hipErrorInvalidValue;
