@@ -259,6 +259,7 @@ flexq_status flexq_gemv_tiles(int act_bits, const void *packed, int group,
  *   sxg         dev, fp16 [K/128][sxg_stride], out: GROUP-major (the scales of
  *               one group for all tokens are contiguous), sxg_stride >= M;
  *               elements m >= M of a row are not written
+ * flexq_quant_act_g128_padded: the same, and elements m >= M of every row are zero.
  * flexq_linear_g128: the linear layer on such activations.
  *   packed      dev, from flexq_pack_w6 with group = 128
  *   xq, sxg     dev, as written by flexq_quant_act_g128 (A6 or A8 codes alike)
@@ -272,6 +273,9 @@ flexq_status flexq_gemv_tiles(int act_bits, const void *packed, int group,
 flexq_status flexq_quant_act_g128(const uint16_t *x, int M, int K, int act_bits,
                                   int8_t *xq, uint16_t *sxg, int sxg_stride,
                                   void *stream);
+flexq_status flexq_quant_act_g128_padded(const uint16_t *x, int M, int K, int act_bits,
+                                         int8_t *xq, uint16_t *sxg, int sxg_stride,
+                                         void *stream);
 flexq_status flexq_linear_g128(const void *packed, const int8_t *xq,
                                const uint16_t *sxg, int sxg_stride, int M,
                                int N, int K, uint16_t *y, void *workspace,

@@ -64,8 +64,9 @@ def load():
     lib.flexq_untile_act.argtypes = [vp, c_int, c_int, c_int, vp, vp]
     lib.flexq_gemv_tiles.restype = c_int
     lib.flexq_gemv_tiles.argtypes = [c_int, vp, c_int, vp, vp, c_int, c_int, c_int, vp, vp, vp, ctypes.c_size_t, vp]
-    lib.flexq_quant_act_g128.restype = c_int
-    lib.flexq_quant_act_g128.argtypes = [vp, c_int, c_int, c_int, vp, vp, c_int, vp]
+    for fn in (lib.flexq_quant_act_g128, lib.flexq_quant_act_g128_padded):
+        fn.restype = c_int
+        fn.argtypes = [vp, c_int, c_int, c_int, vp, vp, c_int, vp]
     lib.flexq_linear_g128.restype = c_int
     lib.flexq_linear_g128.argtypes = [vp, vp, vp, c_int, c_int, c_int, c_int, vp, vp, ctypes.c_size_t, vp]
     lib.flexq_rmsnorm_quant.restype = c_int
@@ -259,9 +260,9 @@ def quant_act_g128(x, act_bits):
     _dev(x, torch.float16)
     M, K = x.shape
     xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    stride = (M + 63) // 64 * 64         # even, as the tiled kernel wants; padding stays unwritten
-    sxg = torch.zeros((K // 128, stride), dtype=torch.float16, device=x.device)
-    _check(lib.flexq_quant_act_g128(_ptr(x), M, K, act_bits, _ptr(xq), _ptr(sxg), stride, _stream()))
+    stride = (M + 63) // 64 * 64         # even, as the tiled kernel wants; the padding is zero
+    sxg = torch.empty((K // 128, stride), dtype=torch.float16, device=x.device)
+    _check(lib.flexq_quant_act_g128_padded(_ptr(x), M, K, act_bits, _ptr(xq), _ptr(sxg), stride, _stream()))
     return xq, sxg
 
 

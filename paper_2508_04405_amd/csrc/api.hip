@@ -554,17 +554,29 @@ flexq_status flexq_swiglu_quant(const uint16_t *gate_up, int M, int F, int act_b
                : FLEXQ_EHIP;
 }
 
-flexq_status flexq_quant_act_g128(const uint16_t *x, int M, int K, int act_bits, int8_t *xq,
-                                  uint16_t *sxg, int sxg_stride, void *stream)
+static flexq_status quant_act_g128(const uint16_t *x, int M, int K, int act_bits, int8_t *xq, uint16_t *sxg,
+                                   int sxg_stride, bool pad, void *stream)
 {
     if (!x || !xq || !sxg || M < 1 || K < 1 || sxg_stride < M) return FLEXQ_EINVAL;
     if (act_bits != 6 && act_bits != 8) return FLEXQ_EINVAL;
     if (K % 128 != 0 || K > FLEXQ_MAX_K) return FLEXQ_ESHAPE;
     if (!aligned16(x) || !aligned16(xq)) return FLEXQ_EALIGN;
-    return flexq::launch_quant_act_g128(x, M, K, act_bits, xq, sxg, sxg_stride,
+    return flexq::launch_quant_act_g128(x, M, K, act_bits, xq, sxg, sxg_stride, pad,
                                         (hipStream_t)stream) == hipSuccess
                ? FLEXQ_OK
                : FLEXQ_EHIP;
+}
+
+flexq_status flexq_quant_act_g128(const uint16_t *x, int M, int K, int act_bits, int8_t *xq,
+                                  uint16_t *sxg, int sxg_stride, void *stream)
+{
+    return quant_act_g128(x, M, K, act_bits, xq, sxg, sxg_stride, false, stream);
+}
+
+flexq_status flexq_quant_act_g128_padded(const uint16_t *x, int M, int K, int act_bits, int8_t *xq,
+                                         uint16_t *sxg, int sxg_stride, void *stream)
+{
+    return quant_act_g128(x, M, K, act_bits, xq, sxg, sxg_stride, true, stream);
 }
 
 flexq_status flexq_linear_g128(const void *packed, const int8_t *xq, const uint16_t *sxg,

@@ -73,9 +73,10 @@ hipError_t launch_quant_w6(const float *w, int N, int K, int group, int8_t *wq, 
 hipError_t launch_quant_act(const uint16_t *x, int M, int K, int act_bits, int8_t *xq,
                             uint16_t *sx, hipStream_t st, int layout = 0);
 hipError_t launch_untile_act(const uint8_t *xt, int act_bits, int M, int K, int8_t *xq, hipStream_t st);
-// Group-wise (128 along K) activation quantizer; sxg is [K/128][stride], group-major.
+// Group-wise (128 along K) activation quantizer; sxg is [K/128][stride], group-major, columns from M
+// on zero with `pad`, else as they were.
 hipError_t launch_quant_act_g128(const uint16_t *x, int M, int K, int act_bits, int8_t *xq,
-                                 uint16_t *sxg, int stride, hipStream_t st);
+                                 uint16_t *sxg, int stride, bool pad, hipStream_t st);
 hipError_t launch_pack_w6(const int8_t *wq, const uint16_t *sw, int N, int K, int group,
                           void *packed, hipStream_t st);
 hipError_t launch_unpack_w6(const void *packed, int N, int K, int group, int8_t *wq, uint16_t *sw,

@@ -152,36 +152,36 @@ __global__ __launch_bounds__(T) void producer_kernel(const uint16_t *__restrict_
 // Group-wise activation quantizer (Section 4.1.1: the activations are cut into the same
 // groups of 128 along K as the weights).  Sixteen lanes own one (token, group): eight values
 // each, the absmax meets by four shuffles, nothing crosses a wavefront.  Scales are written
-// group-major, sxg[g][m], the order in which the linear-layer kernels consume them.
+// group-major, sxg[g][m], the order in which the linear-layer kernels consume them.  The lanes
+// behind the last group set columns M .. cols - 1 of the scales to zero, one each, which saves a
+// caller that wants them so a launch.  Bound: HBM, 3 bytes a value (4096 x 8192 19 us, 5.3 TB/s; by sixteen
+// neighbouring tokens of one or four groups, whose scales are contiguous, 24: the rows' lines are
+// then read far apart).
 __global__ __launch_bounds__(256) void quant_act_g128_kernel(const uint16_t *__restrict__ x, int M,
                                                              int K, float qmax,
                                                              int8_t *__restrict__ xq,
-                                                             uint16_t *__restrict__ sxg, int stride)
+                                                             uint16_t *__restrict__ sxg, int stride, int cols)
 {
     const long gid = (long)blockIdx.x * 256 + threadIdx.x;
     const int G = K / 128;
     const long unit = gid >> 4;
-    if (unit >= (long)M * G) return;           // the sixteen lanes of a unit leave together
+    if (unit >= (long)M * G) {                 // the sixteen lanes of a unit leave together
+        const long e = gid - 16L * M * G;
+        if (e < (long)G * (cols - M)) {
+            const int g = (int)(e / (cols - M));
+            sxg[(long)g * stride + M + (int)(e - (long)g * (cols - M))] = 0;
+        }
+        return;
+    }
     const long m = unit / G;
     const int g = (int)(unit - m * G), c = (int)(gid & 15);
     const long at = m * K + 128L * g + 8 * c;
     const uint4 v = *reinterpret_cast<const uint4 *>(x + at);
-    const unsigned w4[4] = {v.x, v.y, v.z, v.w};
-    unsigned best = 0;                         // fp16 magnitudes order like their bit patterns
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        best = max(best, w4[i] & 0x7fffu);
-        best = max(best, (w4[i] >> 16) & 0x7fffu);
-    }
+    unsigned best = max_bits(v, 0);
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) best = max(best, (unsigned)__shfl_xor((int)best, off, 64));
-    const float amax = h2f((uint16_t)best);
-    uint16_t bits = f2h(amax / qmax);
-    float sf = h2f(bits);
-    if (amax == 0.0f || sf == 0.0f) {
-        bits = 0x3c00;
-        sf = 1.0f;
-    }
+    const uint16_t bits = token_scale(h2f((uint16_t)best), qmax);
+    const float sf = h2f(bits);
     if (c == 0) sxg[(long)g * stride + m] = bits;
     *reinterpret_cast<uint2 *>(xq + at) = quant8(v, sf, 1.0f / sf, -qmax - 1.0f, qmax);
 }
@@ -238,12 +238,13 @@ hipError_t launch_quant_act(const uint16_t *x, int M, int K, int act_bits, int8_
 }
 
 hipError_t launch_quant_act_g128(const uint16_t *x, int M, int K, int act_bits, int8_t *xq,
-                                 uint16_t *sxg, int stride, hipStream_t st)
+                                 uint16_t *sxg, int stride, bool pad, hipStream_t st)
 {
     const float qmax = act_bits == 6 ? 31.0f : 127.0f;
-    const long lanes = (long)M * (K / 128) * 16;
+    const int cols = pad ? stride : M, G = K / 128;
+    const long lanes = (long)M * G * 16 + (long)G * (cols - M);
     hipLaunchKernelGGL(quant_act_g128_kernel, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st,
-                       x, M, K, qmax, xq, sxg, stride);
+                       x, M, K, qmax, xq, sxg, stride, cols);
     return hipGetLastError();
 }
 
