@@ -340,7 +340,12 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
                 if (s == 1) read_sx(kb);
                 if (s == 3) {
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) sx[mt] = h2f(sx_next[mt]);
+                    for (int mt = 0; mt < MT; ++mt) {
+                        sx[mt] = h2f(sx_next[mt]);
+                        // (opaque: else the conversion moves into the multiply-adds, mixed
+                        // precision then, at twice the time each)
+                        asm volatile("" : "+v"(sx[mt]));
+                    }
                 }
             }
             // weight operands: the fourth k-step's, dearer, over the first three slots of its
