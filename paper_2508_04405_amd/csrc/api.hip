@@ -257,6 +257,8 @@ bool tiles_pay(int act_bits, int M, int K, int split_k)
 
 }  // namespace
 
+size_t linear_codes_bytes(int M, int K) { return xq_bytes(M, K); }
+
 bool streams_as_eight(int M, int N, int K)
 {
     const int ks = choose_split(M, N, K);

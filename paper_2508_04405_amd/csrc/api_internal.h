@@ -38,6 +38,9 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
 // that runs a fused producer itself makes it write tiles then, and passes xt.
 bool linear_wants_tiles(int act_bits, int M, int N, int K, int group);
 
+// Bytes of the linear call's own codes in its workspace, behind the counters; the scales follow.
+size_t linear_codes_bytes(int M, int K);
+
 // Group-128 scales: true where the streaming kernel sums in the order of eight wavefronts and one K split.
 bool streams_as_eight(int M, int N, int K);
 

@@ -88,6 +88,10 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_rmsnorm_quant(const uint16_t *x, const uint16_t *gamma, float eps, int M, int K,
                                 int act_bits, int8_t *xq, uint16_t *sx, uint16_t *h_out,
                                 hipStream_t st, int layout = 0);
+// launch_rmsnorm_quant of x and launch_quant_act of attn, both [M,K], in one launch.
+hipError_t launch_norm_and_quant(const uint16_t *x, const uint16_t *gamma, float eps, int bits_x, int8_t *xq,
+                                 uint16_t *sx, uint16_t *h_out, int layout_x, const uint16_t *attn, int bits_attn,
+                                 int8_t *attn_q, uint16_t *attn_s, int layout_attn, int M, int K, hipStream_t st);
 hipError_t launch_swiglu_quant(const uint16_t *gate_up, int M, int F, int act_bits, int8_t *xq,
                                uint16_t *sx, uint16_t *h_out, hipStream_t st, int layout = 0);
 

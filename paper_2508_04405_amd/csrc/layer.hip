@@ -184,17 +184,33 @@ flexq_status layer_impl(const Tuning &tune, const flexq_layer *L, int M, const f
     auto layout = [&](int bits, int N, int K) {
         return flexq::linear_wants_tiles(bits, M, N, K, L->group) ? bits : 0;
     };
+    // Stages 0 and 1 do not wait for each other where the attention output is no part of what stage 0
+    // writes: both are quantized in one launch then, the attention output into the place that the
+    // linear call keeps for it (a single token is quantized by the linear itself).
+    const size_t row = (size_t)M * L->H * 2;
+    const Range attn{(const uint8_t *)io->attn, row};
+    const bool both = M > 1 && first_stage == 0 && last_stage >= 1 &&
+                      !overlap(attn, Range{(const uint8_t *)io->qkv, (size_t)M * L->QKV * 2}) &&
+                      !(io->h_attn_norm && overlap(attn, Range{(const uint8_t *)io->h_attn_norm, row}));
+    int8_t *const attn_q = (int8_t *)c.gemm + FLEXQ_WORKSPACE_COUNTER_BYTES;
+    uint16_t *const attn_s = (uint16_t *)(attn_q + linear_codes_bytes(M, L->H));
     for (int s = first_stage; s <= last_stage; ++s) {
         flexq_status r = FLEXQ_OK;
         if (s == 0) {            // RMS norm + quantize -> fused QKV
             const int lay = layout(L->bits_qkv, L->QKV, L->H);
-            if (flexq::launch_rmsnorm_quant(io->x, L->gamma_attn, L->eps, M, L->H, L->bits_qkv, c.xq, c.sx,
+            if (both) {
+                if (launch_norm_and_quant(io->x, L->gamma_attn, L->eps, L->bits_qkv, c.xq, c.sx, io->h_attn_norm, lay,
+                                          io->attn, L->bits_o, attn_q, attn_s, layout(L->bits_o, L->H, L->H), M, L->H,
+                                          st) != hipSuccess)
+                    return FLEXQ_EHIP;
+            } else if (flexq::launch_rmsnorm_quant(io->x, L->gamma_attn, L->eps, M, L->H, L->bits_qkv, c.xq, c.sx,
                                             io->h_attn_norm, st, lay) != hipSuccess)
                 return FLEXQ_EHIP;
             r = gemm(L->bits_qkv, L->w_qkv, c.xq, c.sx, nullptr, L->QKV, L->H, io->qkv, lay);
         } else if (s == 1) {     // quantize node -> attention output projection (fp16 in: decode
                                  // batches quantize inside the streaming kernel)
-            r = gemm(L->bits_o, L->w_o, nullptr, nullptr, io->attn, L->H, L->H, io->o, 0);
+            r = both ? gemm(L->bits_o, L->w_o, attn_q, attn_s, nullptr, L->H, L->H, io->o, layout(L->bits_o, L->H, L->H))
+                     : gemm(L->bits_o, L->w_o, nullptr, nullptr, io->attn, L->H, L->H, io->o, 0);
         } else if (s == 2) {     // RMS norm + quantize -> fused gate | up
             const int lay = layout(L->bits_gate_up, 2 * L->F, L->H);
             if (flexq::launch_rmsnorm_quant(io->x_ffn, L->gamma_ffn, L->eps, M, L->H, L->bits_gate_up, c.xq,

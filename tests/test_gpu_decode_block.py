@@ -112,6 +112,25 @@ def test_buffers_that_overlap_keep_the_separate_launches():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("M", [2, 20, 40])
+def test_attention_output_inside_the_qkv_buffer(M):
+    """Stage 1 then reads what stage 0 writes: one call gives what a call per stage gives, and so it does
+    with buffers apart, where both inputs are quantized in one launch."""
+    block = Block(1024, 2816, 3072, 0)
+    layer = block.layer((6, 8, 6, 8))
+    ws, data = layer.make_workspace(M), block.inputs(M, 3)
+    for inside in (True, False):
+        outs = []
+        for calls in (((0, 3),), ((0, 0), (1, 1), (2, 3))):
+            out = block.outputs(M)
+            attn = out["qkv"].view(-1)[:M * block.H].view(M, block.H) if inside else data["attn"]
+            for first, last in calls:
+                fq.layer_linears(layer, M, ws, first, last, x=data["x"], attn=attn, x_ffn=out["o"], **out)
+            outs.append(out)
+        torch.cuda.synchronize()
+        assert equal(*outs), inside
+
+
 @pytest.mark.parametrize("group", [0, 128])
 def test_fresh_inputs_on_one_workspace(group):
     """Two hundred back-to-back calls with eight sets of inputs in turn: no value of an earlier call,
