@@ -36,7 +36,8 @@ extern "C" {
  *             other calls return FLEXQ_EHIP while a choice is set)
  *   fuse      the activation-quantize prologue inside the streaming kernel (fp16 in):
  *             1 = whenever the kernel can (up to 8 tokens whose K range fits LDS; the
- *             library's own choice is one token), 2 = never (a quantize launch first)
+ *             library's own choice is one token, and more while the rows are
+ *             short), 2 = never (a quantize launch first)
  *   tiles     fp16 activations of up to 32 tokens quantized into tile order (packed at 6
  *             bits for act_bits 6) for the streaming kernel: 1 = always, 2 = never (the
  *             library's own choice: 17 to 32 tokens, 24 to 32 with 8-bit activations,

@@ -319,15 +319,18 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
     if (forced == 2) stream_kernel = false;
     if (xt != 0) stream_kernel = true;
 
-    // Single-token decode: the streaming kernel quantizes the activations itself.  (Each
-    // workgroup then scans the token's whole fp16 row, which pays off while a CU runs only
-    // a few workgroups -- measured break-even near 1024 workgroups -- and for one token
-    // only: over the four LLaMA-2-70B layers the fused form takes 120 us against 122 us for
-    // quantize launch + GEMV at one token, but 132 against 125 at two and 157 against 131
-    // at eight.  The kernel can do up to eight; tune.fuse = 1 asks for that.)
+    // The streaming kernel quantizes the activations itself where that is little work: every
+    // workgroup scans the tokens' whole fp16 rows, which for one token pays off up to about 1024
+    // workgroups (measured on sixteen layers of 512 .. 28672 deep: 0.73 .. 0.94 of the time with a
+    // quantize launch ahead, 1.00 at 1792 workgroups), for more while the values that a CU's workgroups
+    // scan one after the other stay under ten thousand (4096 x 4096 at two tokens 0.88, 1024 x 16384 at four
+    // 0.87, 512 x 1600 at eight 0.77; beyond, 4096 x 12288 at two 1.04, 2048 x 8192 at six 1.02).  The
+    // kernel can do up to eight; tune.fuse = 1 asks for that.
     const int ks0 = choose_split(M, N, K, tune.split_k);
+    const long wgs0 = (long)(N / 32) * ks0;
+    const bool little = M == 1 ? wgs0 <= 1024 : (long)M * K * ((wgs0 + 255) / 256) <= 10240;
     const bool fuse = x_fp16 && stream_kernel && tune.fuse != 2 && flexq::skinny_can_fuse(M, K, ks0) &&
-                      (tune.fuse == 1 || (M == 1 && (long)(N / 32) * ks0 <= 1024));
+                      (tune.fuse == 1 || little);
     if (may_tile && !fuse && stream_kernel && M <= 32 && (tune.tiles == 1 || tiles_pay(act_bits, M, K, ks0)))
         xt = act_bits;
     if (x_fp16 && !fuse) {

@@ -12,14 +12,13 @@ namespace {
 // one workgroup per token that is 0.3 us of a small launch's 4 to 5 (10240 x 8192 at 16 tokens behind
 // an RMS norm 21.2 -> 20.9 us, LLaMA-2-7B's block at 8 tokens 57.2 -> 56.4).
 template <class Op>
-__device__ __forceinline__ float wave_all(float v, const Op &op)
+__device__ __forceinline__ unsigned wave_all(unsigned v, const Op &op)
 {
-    const auto bits = [](float f) { return (unsigned)__float_as_int(f); };
-    auto s = __builtin_amdgcn_permlane32_swap(bits(v), bits(v), false, false);
-    v = op(__int_as_float((int)s[0]), __int_as_float((int)s[1]));
-    s = __builtin_amdgcn_permlane16_swap(bits(v), bits(v), false, false);
-    v = op(__int_as_float((int)s[0]), __int_as_float((int)s[1]));
-#define FLEXQ_DPP(ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
+    auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = op(s[0], s[1]);
+    s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = op(s[0], s[1]);
+#define FLEXQ_DPP(ctrl) (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, false)
     v = op(v, FLEXQ_DPP(0x128));      // row_ror:8
     v = op(v, FLEXQ_DPP(0x124));      // row_ror:4
     v = op(v, FLEXQ_DPP(0x4e));       // quad_perm [2, 3, 0, 1]
@@ -29,11 +28,19 @@ __device__ __forceinline__ float wave_all(float v, const Op &op)
 }
 __device__ __forceinline__ float wave_max(float v)
 {
-    return wave_all(v, [](float a, float b) { return fmaxf(a, b); });
+    return __uint_as_float(wave_all(__float_as_uint(v), [](unsigned a, unsigned b) {
+        return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+    }));
 }
 __device__ __forceinline__ float wave_sum(float v)
 {
-    return wave_all(v, [](float a, float b) { return a + b; });
+    return __uint_as_float(wave_all(__float_as_uint(v), [](unsigned a, unsigned b) {
+        return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+    }));
+}
+__device__ __forceinline__ unsigned wave_max_bits(unsigned v)
+{
+    return wave_all(v, [](unsigned a, unsigned b) { return max(a, b); });
 }
 
 __device__ __forceinline__ unsigned pack_h2(float lo, float hi)

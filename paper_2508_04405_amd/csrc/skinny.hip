@@ -33,6 +33,7 @@
 // epilogue; it resets the counter so the workspace is ready for the next call.
 #include "flexq_device.h"
 #include "flexq_kernels.h"
+#include "producer_math.h"
 
 namespace {
 
@@ -87,23 +88,6 @@ __device__ __forceinline__ void load_stage(Stage<MT, XLDS> &s, const v4i *packed
         for (int mt = 0; mt < MT; ++mt)
             s.xs[mt] = xact[mt] ? sxg[(long)t * sxg_stride + 32 * mt + (lane & 31)] : (uint16_t)0;
     }
-}
-
-// Quantizer arithmetic of the fused prologue: the same operations, in the same
-// order, as the stand-alone activation quantizer (scale = fp16(absmax / qmax),
-// 1.0 if zero; code = clamp(rne(v / scale))), so both give identical codes.
-__device__ __forceinline__ void prologue_scale(float amax, float qmax, float &sf)
-{
-    const float s32 = amax / qmax;
-    sf = h2f(f2h(s32));
-    if (amax == 0.0f || sf == 0.0f) sf = 1.0f;
-}
-
-__device__ __forceinline__ unsigned prologue_code(uint16_t hbits, float sf, float qmin, float qmax)
-{
-    float q = __builtin_rintf(h2f(hbits) / sf);
-    q = fminf(fmaxf(q, qmin), qmax);
-    return (unsigned)((int)q & 0xff);
 }
 
 template <int MT, int GROUP, bool XLDS, bool FUSEQ, int P, int W, int WPE, bool NTW = true, int XT = 0>
@@ -197,27 +181,16 @@ void skinny_kernel(flexq::LinearArgs a)
         // activations here instead of in a separate launch.  Every workgroup
         // scans the whole fp16 row (it is L2-resident) for the token's absmax,
         // then quantizes only its own K range into the LDS slice.
+        // The operations of the stand-alone quantizer in its order (producer_math.h, quant8), so that
+        // both give the same scales and codes.
         const float qmax = a.qmax, qmin = -a.qmax - 1.0f;
-        auto scan = [](const uint4 &v, unsigned best) {
-            const unsigned w4[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                best = max(best, w4[i] & 0x7fffu);     // fp16 magnitudes order like their bits
-                best = max(best, (w4[i] >> 16) & 0x7fffu);
-            }
-            return best;
-        };
+        float sf = 0.0f, rf = 0.0f;                        // one token: its scale, and 1 over it
         auto emit = [&](const uint4 &v, int m, int c) {    // chunk c of the K range of token m
-            const float sf = s_sx[m];
-            const unsigned w4[4] = {v.x, v.y, v.z, v.w};
-            unsigned out[2] = {0u, 0u};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned lo = prologue_code((uint16_t)(w4[i] & 0xffffu), sf, qmin, qmax);
-                const unsigned hi = prologue_code((uint16_t)(w4[i] >> 16), sf, qmin, qmax);
-                out[i >> 1] |= (lo | (hi << 8)) << (16 * (i & 1));
+            if (M > 1) {
+                sf = s_sx[m];
+                rf = 1.0f / sf;
             }
-            *reinterpret_cast<uint2 *>(xlds + m * xstride + 8 * c) = make_uint2(out[0], out[1]);
+            *reinterpret_cast<uint2 *>(xlds + m * xstride + 8 * c) = quant8(v, sf, rf, qmin, qmax);
         };
         // LDS-only barrier: __syncthreads() would also wait for the weight tiles
         auto lds_sync = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
@@ -228,25 +201,28 @@ void skinny_kernel(flexq::LinearArgs a)
                 for (int i = 0; i < XH; ++i) {
                     const int idx = tid + i * THREADS;
                     if (idx >= m * row_chunks && idx < (m + 1) * row_chunks)
-                        best = scan(xh[FUSEQ ? i : 0], best);
+                        best = max_bits(xh[FUSEQ ? i : 0], best);
                 }
             } else {
                 const uint4 *src = reinterpret_cast<const uint4 *>(a.x_fp16 + (long)m * a.K);
-                for (int c = tid; c < row_chunks; c += THREADS) best = scan(src[c], best);
+                for (int c = tid; c < row_chunks; c += THREADS) best = max_bits(src[c], best);
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1)
-                best = max(best, (unsigned)__shfl_xor((int)best, off, 64));
+            best = wave_max_bits(best);
             if (lane == 0) red[wave][0][m & 3] = (int)best;
-            if ((m & 3) == 3 || m == M - 1) {
+            if (M == 1) {          // every lane finds the scale itself: no second barrier
+                lds_sync();
+                unsigned b = 0;
+#pragma unroll
+                for (int w = 0; w < W; ++w) b = max(b, (unsigned)red[w][0][0]);
+                sf = h2f(token_scale(h2f((uint16_t)b), qmax));
+                rf = 1.0f / sf;
+                if (tid == 0) s_sx[0] = sf;
+            } else if ((m & 3) == 3 || m == M - 1) {
                 lds_sync();
                 if (tid <= (m & 3)) {
-                    const int mm = (m & ~3) + tid;
                     unsigned b = 0;
                     for (int w = 0; w < W; ++w) b = max(b, (unsigned)red[w][0][tid]);
-                    float sf;
-                    prologue_scale(h2f((uint16_t)b), qmax, sf);
-                    s_sx[mm] = sf;
+                    s_sx[(m & ~3) + tid] = h2f(token_scale(h2f((uint16_t)b), qmax));
                 }
                 lds_sync();
             }
