@@ -176,6 +176,33 @@ def test_two_streams_at_once():
         assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
 
 
+def test_beside_a_kernel_that_fills_the_chip():
+    """A prefill GEMM on another stream holds every CU for a while: some workgroups of the block start late or
+    find their partners missing, and the results stay the same."""
+    block, M = Block(1024, 2816, 3072, 0), 4
+    layer = block.layer((6, 6, 6, 8))
+    ws, data, want, out = layer.make_workspace(M), block.inputs(M, 1), block.outputs(M), block.outputs(M)
+    run(layer, M, ws, 2, x_ffn=want["o"], **data, **want)
+    K, N, T = 4096, 8192, 2048
+    packed = torch.zeros(fq.packed_bytes(N, K), dtype=torch.uint8, device=DEV)
+    xq, sx = fq.quant_act(torch.ones((T, K), dtype=torch.float16, device=DEV), 8)
+    big_ws, y = fq.make_workspace(T, N, K), torch.empty((T, N), dtype=torch.float16, device=DEV)
+    differs = torch.zeros(1, dtype=torch.int32, device=DEV)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for rep in range(30):
+        with torch.cuda.stream(a):
+            for _ in range(3):
+                fq.gemm_w6a8(packed, N, K, xq=xq, sx=sx, workspace=big_ws, out=y)
+        with torch.cuda.stream(b):
+            assert run(layer, M, ws, 1, x_ffn=out["o"], **data, **out)
+            for k in NAMES:
+                differs += (out[k] != want[k]).any()
+    torch.cuda.synchronize()
+    assert int(differs.item()) == 0
+    assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+
+
 def test_graph_replay():
     block, M = Block(1024, 2816, 3072, 0), 3
     layer = block.layer((6, 6, 6, 8))
