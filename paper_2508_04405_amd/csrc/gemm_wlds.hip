@@ -185,11 +185,11 @@ struct Item {
 //
 // The half height, 64 x 256 with two blocks a stage and the same slots, is for layers that leave
 // the chip short of items: it takes three quarters of a whole item's time (the expansion and
-// the hand-over stay), but cuts the tokens, not the sums.  Cutting K of the last round's tiles
-// instead was up to a fifth faster still (13824 x 5120 at 700 tokens with both operands'
-// scales 74 us against 93, at 2048 tokens 172 against 193), but then rows of one call were summed
-// in one chain or in pieces by where they lay.  LLaMA-2-13B's down projection at 2048 tokens 193
-// us against 211, with scales on both operands 229 against 266, at 700 tokens 93 against 124.
+// the hand-over stay), but cuts the tokens, not the sums.  Cutting K of the last round's tiles alone
+// was up to a fifth faster still (13824 x 5120 at 2048 tokens 172 us against 193), but then rows of
+// one call were summed in one chain or in pieces by where they lay; where a layer has no whole
+// round, group_split cuts all of its tiles alike.  LLaMA-2-13B's down projection at 2048 tokens 193
+// us against 211, with scales on both operands 229 against 266, at 700 tokens, unsplit, 93 against 124.
 template <int TILE, int GROUP, class DmaX, class DmaW, class DmaS>
 __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uint8_t *lds, int KN, int wave, int lane,
                                            const DmaX &dma_x, const DmaW &dma_w, const DmaS &dma_s)
@@ -1431,9 +1431,9 @@ int group_form(int M, int N, int split_k, size_t partial_bytes)
 // of a 128x256 item 0.86 and 1.08, plus 4.4 and 6.8 us; S pieces meet in 2.5 + 0.55 S us and what their
 // number in all costs.  Measured over 150 .. 3667 tokens, 1024 .. 24448 deep, 512 .. 5120 wide: 700 tokens
 // of 8576 x 512 44 -> 18.5 us, 1101 of 13824 x 512 68 -> 24, 2000 of 24448 x 512 117 -> 46, 500 of 13824 x
-// 5120 72 -> 53; with scales on both operands 700 of 13824 x 5120, with the quantizer, 98.5 -> 87.8.  A function of the shape alone,
-// for every row alike.  The splits show in the sums' last bits, so an unsplit layer is only cut for 7 %
-// of the time, one that is cut already only cut anew for a quarter of it.
+// 5120 72 -> 53; with scales on both operands 700 of 13824 x 5120, with the quantizer, 98.5 -> 87.8.  A
+// function of the shape alone, for every row alike.  The splits show in the sums' last bits, so an
+// unsplit layer is only cut for 7 % of the time, one that is cut already only cut anew for a quarter.
 int group_split(int M, int N, int K, int ks, size_t partial_bytes)
 {
     const int KT = K / FLEXQ_TILE_K, tiles_n = (N + 255) / 256;

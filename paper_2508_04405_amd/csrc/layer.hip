@@ -1,7 +1,8 @@
 // The linear layers of one decoder block as one call: each GEMM fed by the operator that
 // produces its input with the activation quantizer fused in (paper Section 4.1.3), the
 // activation width chosen per linear (Section 4.1.2: 8 bits for the down projection,
-// 6 bits elsewhere).  Host code only: it strings together the library's own launches.
+// 6 bits elsewhere).  Host code only: it strings together the library's own launches or, for a
+// handful of tokens, prepares the one launch of decode_block.hip.
 #include "api_internal.h"
 #include "decode_block.h"
 #include "flexq_kernels.h"
