@@ -132,6 +132,7 @@ struct WldsChoice {
 };
 WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut);
 WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes);   // tail_form 3 or 5
+double gemm_192_us(int M, int N, int K);                                 // tail_form 6
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st);
 // Group-128 scales (on both operands with a.sxg): 128x256 tiles of the same kernel, persistent;
 // the tiles beyond the last whole round of 256 run at half the height with `half`, and each is

@@ -689,7 +689,23 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
             // (against 256-row tiles cut along K the low tiles must promise 12 %: the two
             // estimates are good to about 6 % each, and at 256 tokens of a 10240 x 8192 layer
             // 36 against 33 us is where the line falls)
-            if (low.us < t_best && low.us < (c.tail_form == 2 ? 0.88 : 1.0) * c.us) {
+            const bool take_low = low.us < t_best && low.us < (c.tail_form == 2 ? 0.88 : 1.0) * c.us;
+            // 192-row tiles where 256 rows would be half padding (576 tokens of 15360 x 5120 53.0 ->
+            // 46.8 us, 333 of 27648 x 5120 56.7 -> 50.1, 576 of 57344 x 8192 287 -> 253) or leave a quarter
+            // of the chip idle (1152 of 8192 x 8192 81.5 -> 74.6): for 5 % of the estimated time, against a
+            // cut form, whose estimate is coarser, for 10.  Measured against every other form on fourteen layers at
+            // 256 .. 4096 tokens the line takes fourteen of 160 cells, 0.88 to 0.96 of the fastest other's
+            // time each; forced on the rest they take 0.86 to 3 times as long, 1.1 in the middle.
+            const double others = take_low ? low.us : c.us < t_best ? c.us : t_best;
+            const bool cut = take_low ? low.tail_form == 5 : c.us < t_best ? c.tail_form == 2 : a.split_k > 1;
+            if (device_cu_count() == kStreamKGrid &&
+                gemm_192_us(a.M, a.N, a.K) < (cut ? 0.90 : 0.95) * others) {
+                LinearArgs b = a;
+                b.split_k = 1;
+                *chosen = 20;
+                return launch_gemm_wlds(b, 6, 0, st);
+            }
+            if (take_low) {
                 LinearArgs b = a;
                 b.split_k = 1;
                 *chosen = low.tail_form == 5 ? 16 : 15;
@@ -732,6 +748,7 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
         return launch_gemm_wlds(a, 2, tail_wgs, st);
     }
     if (cfg == 15 && a.split_k == 1) return launch_gemm_wlds(a, 3, 0, st);
+    if (cfg == 20 && a.split_k == 1) return launch_gemm_wlds(a, 6, 0, st);
     if (cfg == 16) {   // 128x256 tiles, those beyond the last whole round cut into split_k pieces
         const int tail_wgs = ((a.M + 127) / 128) * ((a.N + 255) / 256) % kStreamKGrid * a.split_k;
         LinearArgs b = a;

@@ -80,7 +80,8 @@
 // the weights (about 37 GB/s per CU come through the DMA path, here as in the
 // whole tiles); on narrower layers, from 65 tokens, each cut evenly along K; and
 // above 128 tokens where they fill the chip more evenly than 256-row tiles
-// (gemm_low_choose), those beyond the last whole round cut evenly.
+// (gemm_low_choose), those beyond the last whole round cut evenly.  And 192-row tiles, 192x256,
+// whole, where their height fits the tokens or the rounds better (gemm_192_us).
 #include "flexq_device.h"
 #include "flexq_kernels.h"
 #include "gemm_common.h"
@@ -104,17 +105,21 @@ constexpr int SLOT_BYTES = 256 * 256 * 4;      // one workgroup's int32 sums of 
 // TILE names the shape: 2 the whole tile (256 x 256), 1 the half tile (256 x 128), 3 the
 // low tile (128 x 256, 2 x 4 wavefronts of 64 x 64: for up to 128 tokens on wide layers),
 // 4 the group tile (128 x 256, eight wavefronts side by side of 128 x 32: group-128 scales),
-// 5 the same at half the height (64 x 256)
+// 5 the same at half the height (64 x 256), 6 the three-quarter tile (192 x 256, 2 x 4
+// wavefronts of 96 x 64, 0.75 KiB of LDS reads per MFMA; its smaller stages leave room for both
+// operands two stages ahead)
 template <int TILE>
 struct Shape {
-    static_assert(TILE >= 1 && TILE <= 5, "half, whole, low or group tiles");
-    static constexpr int WN = TILE == 1 ? 2 : TILE >= 4 ? 8 : 4;
-    static constexpr int MT = TILE == 2 || TILE == 4 ? 4 : 2;
-    static constexpr int NT = TILE >= 4 ? 1 : 2;
+    static_assert(TILE >= 1 && TILE <= 6, "half, whole, low, group or three-quarter tiles");
+    static constexpr bool GROUPED = TILE == 4 || TILE == 5;
+    static constexpr int WN = TILE == 1 ? 2 : GROUPED ? 8 : 4;
+    static constexpr int MT = TILE == 2 || TILE == 4 ? 4 : TILE == 6 ? 3 : 2;
+    static constexpr int NT = GROUPED ? 1 : 2;
     static constexpr int BN = WN * NT * 32;
     static constexpr int BM = WAVES / WN * MT * 32;
     static_assert(BN == 256 || BN == 128, "whole or half width");
-    static_assert(BM == 256 || BM == 128 || (BM == 64 && TILE == 5), "whole, half or quarter height");
+    static_assert(BM == 256 || BM == 128 || (BM == 64 && TILE == 5) || (BM == 192 && TILE == 6),
+                  "whole, half, quarter or three-quarter height");
     static constexpr int XSTAGE = BM * 128;               // bytes of one activation stage
     static constexpr int XDMA = BM / 8 / WAVES;           // 1 KiB activation DMA loads per wavefront and stage
     static constexpr int WTILES = BN / 32;                        // packed tiles per stage
@@ -146,7 +151,7 @@ struct Shape {
     static constexpr int SRING = STG_END > WBASE + 3 * WSTAGE ? STG_END : WBASE + 3 * WSTAGE;
     static constexpr int SSLOT = BN * 2 + 256;                    // weight scales, 128 token scales
     static constexpr int SF32 = SRING + 4 * SSLOT;                // the current stage's weight scales in fp32
-    static constexpr int LDS_BYTES = TILE >= 4 ? SF32 + BN * 4 : SRING;
+    static constexpr int LDS_BYTES = GROUPED ? SF32 + BN * 4 : SRING;
     static_assert(LDS_BYTES + 1024 <= 160 * 1024, "LDS of one CU (plus the static part)");
 };
 
@@ -406,7 +411,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     constexpr int MT = S::MT, NT = S::NT;
     constexpr bool WHOLE = S::BN == 256;
     static_assert(!SK || WHOLE, "the tail is cut in whole-width tiles");
-    static_assert((GROUP != 0) == (TILE >= 4) && !(GROUP && SK == 1), "group scales run group tiles");
+    static_assert((GROUP != 0) == S::GROUPED && !(GROUP && SK == 1), "group scales run group tiles");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -677,7 +682,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                         }
                     }
                 };
-                static_assert((MT == 4 || MT == 2) && NT == 2, "the step tables below are written for these blockings");
+                static_assert((MT == 4 || MT == 3 || MT == 2) && NT == 2, "the step tables below are written for these blockings");
                 if constexpr (MT == 2) {
                     // 64 x 64 per wavefront: eight steps of two MFMAs, two dwords of the next
                     // step's operand expanded per MFMA; the dearer operands of the fourth k-step
@@ -777,16 +782,18 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                         for (int mt = 0; mt < MT; ++mt) {
                             acc[mt][nt] = mfma_i8(cur_b, af[j & 1][mt], acc[mt][nt]);
                             // shadow work of this MFMA: one dword of an operand that is due later
-                            if (s < 5) nxt[mt] = unpack_kstep_dword(wreg[(s + 1) & 1], (s + 1) >> 1, mt);
-                            if (s == 3) bf6[mt] = unpack_kstep_dword(wreg[0], 3, mt);
-                            if (s == 4) bf7[mt] = unpack_kstep_dword(wreg[1], 3, mt);
-                            if (s == 7) nxt[mt] = unpack_kstep_dword(wreg[0], 0, mt);   // the next stage's first
-                            {
-                                int p0 = nxt[mt], p1 = bf6[mt], p2 = bf7[mt];
+                            // (three MFMAs a step: the first has two)
+#pragma unroll
+                            for (int d = MT == 3 && mt > 0 ? mt + 1 : mt; d < (MT == 3 ? mt + 2 : mt + 1); ++d) {
+                                if (s < 5) nxt[d] = unpack_kstep_dword(wreg[(s + 1) & 1], (s + 1) >> 1, d);
+                                if (s == 3) bf6[d] = unpack_kstep_dword(wreg[0], 3, d);
+                                if (s == 4) bf7[d] = unpack_kstep_dword(wreg[1], 3, d);
+                                if (s == 7) nxt[d] = unpack_kstep_dword(wreg[0], 0, d);   // the next stage's first
+                                int p0 = nxt[d], p1 = bf6[d], p2 = bf7[d];
                                 asm volatile("" : "+v"(p0), "+v"(p1), "+v"(p2));   // pins the expansion here
-                                nxt[mt] = p0;
-                                bf6[mt] = p1;
-                                bf7[mt] = p2;
+                                nxt[d] = p0;
+                                bf6[d] = p1;
+                                bf7[d] = p2;
                             }
                             __builtin_amdgcn_sched_barrier(0);
                         }
@@ -1193,7 +1200,8 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 #endif
 }
 
-// FORM 3: `full_count` low tiles (tiles_m counts 128-row tiles) and nothing else.  FORM 5:
+// FORM 3: `full_count` low tiles (tiles_m counts 128-row tiles) and nothing else.  FORM 6: the
+// same with 192-row tiles.  FORM 5:
 // `full_count` low tiles, then `tail_count`, each cut along K into tail_wgs / tail_count pieces.
 // FORM 0: `full_count` whole tiles.  FORM 1: then the `tail_count` tiles that follow them as
 // 2 * tail_count half tiles.  FORM 2: then those tiles cut along K into `tail_wgs` runs
@@ -1209,6 +1217,10 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
     __shared__ int s_last;
     if (FORM == 3) {   // every item a low tile (128 x 256)
         run_items<3, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+        return;
+    }
+    if (FORM == 6) {   // every item a tile of 192 x 256
+        run_items<6, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
     }
     if (FORM == 5) {   // whole rounds of low tiles, then the rest cut evenly along K
@@ -1356,6 +1368,17 @@ WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes)
     return best;
 }
 
+// Estimated microseconds with 192-row tiles, all whole.  A stage takes 0.90 us while at most 150 CUs
+// have a tile, 1.32 on a full chip (a 256-row tile's: 1.20, 1.50).  Within 7 % of the time, mostly 3, on
+// fourteen layers (2048 .. 57344 wide, 4096 .. 28672 deep) at 256 .. 4096 tokens.
+double gemm_192_us(int M, int N, int K)
+{
+    const int tiles = ((M + 191) / 192) * ((N + 255) / 256), KT = K / FLEXQ_TILE_K;
+    auto round_us = [&](int n) { return (0.90 + (n > 150 ? 0.42 * (n - 150) / 106.0 : 0.0)) * KT + 5.0; };
+    const int tail = tiles % kStreamKGrid;
+    return tiles / kStreamKGrid * round_us(kStreamKGrid) + (tail ? round_us(tail) : 0.0) + 1.0;
+}
+
 namespace {
 
 constexpr int kLdsMax(int a, int b) { return a > b ? a : b; }
@@ -1367,10 +1390,11 @@ hipError_t launch_form(const LinearArgs &a, int tiles_m, int tiles_n, int full_c
 {
     auto kern = gemm_wlds_kernel<FORM>;
     static std::atomic<unsigned long long> lds_allowed{0};
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), kLdsBytes, lds_allowed);
+    constexpr int lds_bytes = FORM == 6 ? Shape<6>::LDS_BYTES : kLdsBytes;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds_bytes, lds_allowed);
         e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WAVES), kLdsBytes, st, a, tiles_m, tiles_n,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WAVES), lds_bytes, st, a, tiles_m, tiles_n,
                        full_count, tail_count, tail_wgs);
     return hipGetLastError();
 }
@@ -1492,6 +1516,10 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
     if (tail_form == 3) {   // low tiles throughout
         const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256;
         return launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
+    }
+    if (tail_form == 6) {   // 192-row tiles throughout
+        const int rows = (a.M + 191) / 192, cols = (a.N + 255) / 256;
+        return launch_form<6>(a, rows, cols, rows * cols, 0, 0, grid_for(rows * cols), st);
     }
     if (tail_form == 5) {   // low tiles, those beyond the last whole round cut into equal pieces
         const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256, all = low_m * cols;
