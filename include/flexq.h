@@ -309,8 +309,9 @@ flexq_status flexq_linear_g128(const void *packed, const int8_t *xq,
  * `stream`.  Results of every stage are those of the corresponding single calls
  * (flexq_rmsnorm_quant / flexq_swiglu_quant / flexq_gemm_w6a6 / _w6a8), status codes
  * as theirs; nothing is launched if an argument of any requested stage is bad.  Calls
- * of up to 16 tokens that hold stages 0 and 1 run as one launch where the buffers allow
- * it (no h_* output, no output overlapping another buffer but as `x_ffn` may alias `o`):
+ * of up to 16 tokens that hold stages 0 and 1 run as one launch where the codes of the
+ * deepest linear fit LDS (11 tokens of 11008 values, 5 of 28672) and the buffers allow it
+ * (no h_* output, no output overlapping another buffer but as `x_ffn` may alias `o`):
  * the same results.  The workspace must not be shared by calls that overlap in time.
  */
 typedef struct {
