@@ -26,8 +26,9 @@
 // order.  That needs nobody else and changes nothing: every result is a function of buffers that no
 // part of the launch overwrites -- the codes of every linear have a place of their own, and the host
 // takes this path only for buffers that do not overlap -- so work done twice stores the same
-// values, and a workgroup that starts late repeats what it finds done.  The last one to leave
-// clears the words.
+// values.  A workgroup that starts late finds its bit set by whoever did its row blocks and leaves
+// them alone (the bits are read with the words a wait looks at anyway: 0.2 us of a block, 115.3 -> 115.5).
+// The last one to leave clears the words.
 //
 // Who reads what from where.  Outputs are read back with device-scope loads.  The codes are read
 // with ordinary loads, so that an XCD fetches them once: no cache can hold an older value of
@@ -220,28 +221,43 @@ void decode_block_kernel(DecodeArgs)
         clear();
     };
 
-    // ---- waiting, with a bound; the answer goes to every wavefront ------------------------------
-    auto wait_for = [&](auto ready) INLINE -> bool {
+    // ---- waiting, with a bound; the answer (0: it ran out) goes to every wavefront ------------------
+    auto wait_for = [&](auto ready) INLINE -> int {
         if (wave == 0) {
-            bool ok = ready();
-            for (int i = 0; !ok && i < a.spin; ++i) {
+            int got = ready();
+            for (int i = 0; got == 0 && i < a.spin; ++i) {
                 __builtin_amdgcn_s_sleep(1);
-                ok = ready();
+                got = ready();
             }
-            if (lane == 0) s_flag = ok ? 1 : 0;
+            if (lane == 0) s_flag = got;
         }
         lds_barrier();
-        const bool ok = __builtin_amdgcn_readfirstlane(s_flag) != 0;
+        const int got = __builtin_amdgcn_readfirstlane(s_flag);
         lds_barrier();
-        return ok;
+        return got;
     };
     auto pieces_of = [&](int i) INLINE { return flexq::decode_pieces(a.pr[i].mode, a.pr[i].L); };
+    // What a wait is for may have been done in this workgroup's place, by one that no longer waited for
+    // it: the last lane looks for that, on the same trip through memory.
+    constexpr int kReady = 1, kDoneForUs = 2;
+    auto bit_of_last_lane = [&](unsigned v, int bit) INLINE { return (__builtin_amdgcn_readlane((int)v, 63) >> bit) & 1; };
     auto codes_there = [&](int k) INLINE {
         const int pieces = pieces_of(k);
-        return wait_for([&] { return (bool)__all(lane >= pieces || peek(codes_words(a, k, self & 7) + lane) == all_tokens); });
+        const unsigned *const word = lane == 63 ? done_word(a, k, self >> 5) : codes_words(a, k, self & 7) + (lane & 7);
+        return wait_for([&] {
+            unsigned v = all_tokens;
+            if (lane < pieces || lane == 63) v = peek(word);
+            if (bit_of_last_lane(v, self & 31)) return kDoneForUs;      // this workgroup's row blocks
+            return __all(lane >= pieces || v == all_tokens) ? kReady : 0;
+        });
     };
-    auto outputs_there = [&](int k) INLINE {
-        return wait_for([&] { return (bool)__all(peek(done_word(a, k, lane & 7)) == ~0u); });
+    auto outputs_there = [&](int k, int what) INLINE {                  // for piece `what` of the next linear's producer
+        const unsigned *const word = lane == 63 ? codes_words(a, k + 1, self & 7) + (what & 7) : done_word(a, k, lane & 7);
+        return wait_for([&] {
+            const unsigned v = peek(word);
+            if (bit_of_last_lane(v, what >> 3)) return kDoneForUs;
+            return __all(lane == 63 || v == ~0u) ? kReady : 0;
+        });
     };
     auto meet = [&](float v, bool sum, int waves) INLINE {
         v = sum ? wave_sum(v) : wave_max(v);
@@ -326,11 +342,11 @@ void decode_block_kernel(DecodeArgs)
                     __hip_atomic_store(top_words(a, i, m) + piece, 0x80000000u | f2h(top), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
                 unsigned seen = 0;
-                const bool ok = wait_for([&] {
+                const int ok = wait_for([&] {
                     seen = lane < pieces ? peek(top_words(a, i, m) + lane) : 0x80000000u;
-                    return (bool)__all((int)seen < 0);
+                    return __all((int)seen < 0) ? kReady : 0;
                 });
-                if (ok) {
+                if (ok != 0) {
                     top = meet(wave == 0 ? h2f((uint16_t)(seen & 0xffffu)) : 0.0f, false, 1);
                 } else {
                     float all = 0.0f;
@@ -466,6 +482,7 @@ void decode_block_kernel(DecodeArgs)
         const int kt = a.ph[k].kt, nb = a.ph[k].nb;
         int j = first_block(k, self);
         const bool feeds = feeds_later(k);
+        bool mine = j < nb;      // row blocks of this linear are left for this workgroup
         // Step 0: this workgroup's share of the producers whose input is complete once linear
         // k - 1 is (k = 0: of those that need none).  Step 1: the codes of linear k.  Where a wait
         // ran out, first everything that is missing, in order.
@@ -475,10 +492,16 @@ void decode_block_kernel(DecodeArgs)
             if (step == 0) {
                 if (k > 0) {
                     if (a.pr[k].dep != k - 1 || my_piece(k, 0) < 0) continue;
-                    ok = outputs_there(k - 1);
+                    const int got = outputs_there(k - 1, my_piece(k, 0));
+                    if (got == kDoneForUs) continue;
+                    ok = got == kReady;
                 }
-            } else if (j >= nb || (ok = codes_there(k))) {
-                break;
+            } else {
+                if (!mine) break;
+                const int got = codes_there(k);
+                mine = got != kDoneForUs;
+                if (got != 0) break;
+                ok = false;
             }
             for (int i = ok ? k : 0; i <= (k == 0 && step == 0 ? n - 1 : k); ++i) {
                 const bool own = step == 0 && i >= k;
@@ -499,7 +522,11 @@ void decode_block_kernel(DecodeArgs)
                 if (i < k && feeds_later(i)) run_missing(i);
             }
         }
-        if (j < nb) {
+        if (j < nb && !mine) {      // the tiles in flight are the next linear's instead
+            open(k + 1);
+            request_turn();
+        }
+        if (mine) {
             stage(k);
             // The masks are not looked at any more.  (Every bit this workgroup set is there: the loads
             // of `stage` were waited for, and with them all that wavefront 0 did before.)
@@ -523,7 +550,7 @@ void decode_block_kernel(DecodeArgs)
                 finish(k, j, GROUP ? (uint16_t)0 : s_sw[(j / kDecodeGrid) * 32 + (lane & 31)]);
             }
         }
-        if (feeds && wave == 0) {
+        if (feeds && wave == 0 && (mine || first_block(k, self) >= nb)) {
             __builtin_amdgcn_s_waitcnt(kNoLoads);
             set_done(k, self);
             if (first_block(k, self) < nb) request_turn();

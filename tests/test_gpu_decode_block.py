@@ -203,6 +203,35 @@ def test_beside_a_kernel_that_fills_the_chip():
     assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
 
 
+def test_a_workgroup_that_comes_late_repeats_nothing():
+    """A workgroup that starts when the others no longer wait for it finds its bit set in the linear's mask, set by
+    one that did its row blocks: it leaves them alone.  Here the bits are set ahead of the launch, and what
+    would have been stored there -- other values than the workgroups' own -- has to be there afterwards
+    and in everything computed from it."""
+    block, M = Block(1024, 2816, 3072, 0), 5
+    layer, H, F = block.layer((6, 6, 6, 8)), 1024, 2816
+    ws, data, other = layer.make_workspace(M), block.inputs(M, 3), block.inputs(M, 4)
+    words = ws[:16384].view(torch.int32)
+    plain, instead = block.outputs(M), block.outputs(M)
+    run(layer, M, ws, 2, x_ffn=plain["o"], **data, **plain)
+    run(layer, M, ws, 2, x_ffn=instead["o"], **other, **instead)
+    # row block 0 of a linear is that of the workgroup behind the owner of the last linear's last one;
+    # (linear, its first workgroup, row blocks): the attention output's 32, the gate and up projections' 176
+    for stage, name, home, rows in ((1, "o", 3072 // 32, (0, 5, 31)), (2, "gate_up", (3072 + H) // 32, (1, 100, 127, 175))):
+        for spin in (0, -1):
+            got, want = block.outputs(M), {k: v.clone() for k, v in plain.items()}
+            for b in rows:
+                for out in (got, want):
+                    out[name][:, 32 * b:32 * b + 32] = instead[name][:, 32 * b:32 * b + 32]
+                slot = (home + b) % 256
+                words[32 + (8 * stage + slot // 32) * 32] |= (1 << slot % 32) - (1 << 32 if slot % 32 == 31 else 0)
+            run(layer, M, ws, 2, 0, stage + 1, 3, x_ffn=want["o"], **want)
+            assert run(layer, M, ws, 1, spin, x_ffn=got["o"], **data, **got)
+            torch.cuda.synchronize()
+            assert int(words.abs().sum()) == 0
+            assert not equal(want, plain) and equal(got, want), (name, spin)
+
+
 def test_graph_replay():
     block, M = Block(1024, 2816, 3072, 0), 3
     layer = block.layer((6, 6, 6, 8))
