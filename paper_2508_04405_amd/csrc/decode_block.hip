@@ -385,11 +385,11 @@ void decode_block_kernel(DecodeArgs)
     };
     // Whose a producer's pieces are: numbered through (those of the producers that need no outputs one
     // after the other), they go to the workgroups that follow the owner of its linear's last row
-    // block, which have a row block less there (or none).  This workgroup's piece of producer i,
-    // `turn` 0 or 1 (there may be more than 256), as token * 8 + piece, or -1.
-    auto my_piece = [&](int i, int turn) INLINE {
+    // block, which have a row block less there (or none); the host sees to it that there are no more of
+    // them than workgroups.  This workgroup's piece of producer i as token * 8 + piece, or -1.
+    auto my_piece = [&](int i) INLINE {
         const int home = a.pr[i].dep < 0 ? 0 : i, pieces = pieces_of(i);
-        const int u = ((self - a.ph[home].off - a.ph[home].nb) & (kDecodeGrid - 1)) + kDecodeGrid * turn - a.pr[i].first;
+        const int u = ((self - a.ph[home].off - a.ph[home].nb) & (kDecodeGrid - 1)) - a.pr[i].first;
         if (u < 0 || u >= M * pieces) return -1;
         const int m = u / pieces;
         return m * 8 + u - m * pieces;
@@ -491,8 +491,8 @@ void decode_block_kernel(DecodeArgs)
             bool ok = true;
             if (step == 0) {
                 if (k > 0) {
-                    if (a.pr[k].dep != k - 1 || my_piece(k, 0) < 0) continue;
-                    const int got = outputs_there(k - 1, my_piece(k, 0));
+                    if (a.pr[k].dep != k - 1 || my_piece(k) < 0) continue;
+                    const int got = outputs_there(k - 1, my_piece(k));
                     if (got == kDoneForUs) continue;
                     ok = got == kReady;
                 }
@@ -506,12 +506,12 @@ void decode_block_kernel(DecodeArgs)
             for (int i = ok ? k : 0; i <= (k == 0 && step == 0 ? n - 1 : k); ++i) {
                 const bool own = step == 0 && i >= k;
                 if (!own || a.pr[i].dep == k - 1) {
-                    const int pieces = own ? 2 : pieces_of(i);
+                    const int pieces = own ? 1 : pieces_of(i);
                     for (int m = 0; m < (own ? 1 : M); ++m)
                         for (int p = 0; p < pieces; ++p) {
                             int what = 8 * m + p;
                             if (own) {
-                                what = my_piece(i, p);
+                                what = my_piece(i);
                             } else {
                                 read_words(codes_words(a, i, self & 7), 1);
                                 if (has_word(p, m)) what = -1;

@@ -121,7 +121,9 @@ bool one_launch(const flexq_layer *L, int M, const flexq_layer_io *io, int first
             if (overlap(in[q], out[i])) return false;
         if (pr.dep >= 0 && pr.dep != i - 1) return false;
         pr.first = pr.dep < 0 ? pieces : 0;
-        if (pr.dep < 0) pieces += M * decode_pieces(pr.mode, pr.L);
+        const int made = M * decode_pieces(pr.mode, pr.L);
+        if (pr.first + made > kDecodeGrid) return false;        // a workgroup makes one piece of a producer
+        if (pr.dep < 0) pieces += made;
     }
     if (p > end || lds_bytes > kDecodeLds) return false;
     return true;
