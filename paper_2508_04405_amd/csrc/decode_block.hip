@@ -23,12 +23,14 @@
 // write the codes with device-scope stores and set the piece's bit.  A linear starts when its
 // producer's bits are there.  No workgroup waits without a bound: when its polls run out (somebody
 // is not resident: a busy device, another launch of this kind) it does what is missing itself, in
-// order.  That needs nobody else and changes nothing: every result is a function of buffers that no
-// part of the launch overwrites -- the codes of every linear have a place of their own, and the host
-// takes this path only for buffers that do not overlap -- so work done twice stores the same
-// values.  A workgroup that starts late finds its bit set by whoever did its row blocks and leaves
-// them alone (the bits are read with the words a wait looks at anyway: 0.2 us of a block, 115.3 -> 115.5).
-// The last one to leave clears the words.
+// order, each beginning with a different part (with nobody waiting at all LLaMA-2-7B's block at 8
+// tokens takes 88 us, 70B's at one token 170; with one tile a wavefront in flight, everybody walking
+// the same way and a wait for every piece of a row 305 and 418).  That needs nobody else and changes
+// nothing: every result is a function of buffers that no part of the launch overwrites -- the codes
+// of every linear have a place of their own, and the host takes this path only for buffers that do
+// not overlap -- so work done twice stores the same values.  A workgroup that starts late finds its
+// bit set by whoever did its row blocks and leaves them alone (the bits are read with the words a
+// wait looks at anyway: 0.2 us of a block, 115.3 -> 115.5).  The last one to leave clears the words.
 //
 // Who reads what from where.  Outputs are read back with device-scope loads.  The codes are read
 // with ordinary loads, so that an XCD fetches them once: no cache can hold an older value of
@@ -222,10 +224,10 @@ void decode_block_kernel(DecodeArgs)
     };
 
     // ---- waiting, with a bound; the answer (0: it ran out) goes to every wavefront ------------------
-    auto wait_for = [&](auto ready) INLINE -> int {
+    auto wait_for = [&](auto ready, int polls) INLINE -> int {
         if (wave == 0) {
             int got = ready();
-            for (int i = 0; got == 0 && i < a.spin; ++i) {
+            for (int i = 0; got == 0 && i < polls; ++i) {
                 __builtin_amdgcn_s_sleep(1);
                 got = ready();
             }
@@ -249,15 +251,15 @@ void decode_block_kernel(DecodeArgs)
             if (lane < pieces || lane == 63) v = peek(word);
             if (bit_of_last_lane(v, self & 31)) return kDoneForUs;      // this workgroup's row blocks
             return __all(lane >= pieces || v == all_tokens) ? kReady : 0;
-        });
+        }, a.spin);
     };
     auto outputs_there = [&](int k, int what) INLINE {                  // for piece `what` of the next linear's producer
-        const unsigned *const word = lane == 63 ? codes_words(a, k + 1, self & 7) + (what & 7) : done_word(a, k, lane & 7);
+        const unsigned *const word = lane == 63 ? codes_words(a, k + 1, self & 7) + (what >> 5) : done_word(a, k, lane & 7);
         return wait_for([&] {
             const unsigned v = peek(word);
-            if (bit_of_last_lane(v, what >> 3)) return kDoneForUs;
+            if (bit_of_last_lane(v, what & 31)) return kDoneForUs;
             return __all(lane == 63 || v == ~0u) ? kReady : 0;
-        });
+        }, a.spin);
     };
     auto meet = [&](float v, bool sum, int waves) INLINE {
         v = sum ? wave_sum(v) : wave_max(v);
@@ -270,7 +272,7 @@ void decode_block_kernel(DecodeArgs)
     };
 
     // ---- one piece of a producer's token: fp16 in, codes and scale out (as producer_kernel) ----
-    auto produce_as = [&](auto mode_tag, int i, int m, int piece) INLINE {
+    auto produce_as = [&](auto mode_tag, int i, int m, int piece, int polls) INLINE {
         constexpr int MODE = decltype(mode_tag)::value;
         constexpr int CH = MODE == 0 ? 2 : 1;
         const auto &p = a.pr[i];
@@ -345,7 +347,7 @@ void decode_block_kernel(DecodeArgs)
                 const int ok = wait_for([&] {
                     seen = lane < pieces ? peek(top_words(a, i, m) + lane) : 0x80000000u;
                     return __all((int)seen < 0) ? kReady : 0;
-                });
+                }, polls);
                 if (ok != 0) {
                     top = meet(wave == 0 ? h2f((uint16_t)(seen & 0xffffu)) : 0.0f, false, 1);
                 } else {
@@ -374,25 +376,26 @@ void decode_block_kernel(DecodeArgs)
         if (tid < 8)
             __hip_atomic_fetch_or(codes_words(a, i, tid) + piece, 1u << m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto produce = [&](int i, int m, int piece) INLINE {
-        const int mode = a.pr[i].mode;
+    // `what`: piece * 32 + token; `polls`: how long to wait for the row's other pieces
+    auto produce = [&](int i, int what, int polls) INLINE {
+        const int mode = a.pr[i].mode, m = what & 31, piece = what >> 5;
         if (mode == 0)
-            produce_as(std::integral_constant<int, 0>{}, i, m, piece);
+            produce_as(std::integral_constant<int, 0>{}, i, m, piece, polls);
         else if (mode == 1)
-            produce_as(std::integral_constant<int, 1>{}, i, m, piece);
+            produce_as(std::integral_constant<int, 1>{}, i, m, piece, polls);
         else
-            produce_as(std::integral_constant<int, 2>{}, i, m, piece);
+            produce_as(std::integral_constant<int, 2>{}, i, m, piece, polls);
     };
     // Whose a producer's pieces are: numbered through (those of the producers that need no outputs one
     // after the other), they go to the workgroups that follow the owner of its linear's last row
     // block, which have a row block less there (or none); the host sees to it that there are no more of
-    // them than workgroups.  This workgroup's piece of producer i as token * 8 + piece, or -1.
+    // them than workgroups.  This workgroup's piece of producer i as piece * 32 + token, or -1.
     auto my_piece = [&](int i) INLINE {
         const int home = a.pr[i].dep < 0 ? 0 : i, pieces = pieces_of(i);
         const int u = ((self - a.ph[home].off - a.ph[home].nb) & (kDecodeGrid - 1)) - a.pr[i].first;
         if (u < 0 || u >= M * pieces) return -1;
         const int m = u / pieces;
-        return m * 8 + u - m * pieces;
+        return (u - m * pieces) * 32 + m;
     };
 
     // ---- linear k's codes and token scales into LDS --------------------------------------------
@@ -439,34 +442,63 @@ void decode_block_kernel(DecodeArgs)
         return any;
     };
 
-    auto read_words = [&](const unsigned *word, int step) INLINE {
-        if (wave == 0 && lane < 8) s_words[lane] = peek(word + step * lane);
-        lds_barrier();
-    };
-    auto has_word = [&](int i, int bit) INLINE {      // of the words read last
-        const unsigned have = (unsigned)__builtin_amdgcn_readfirstlane((int)s_words[i]);
-        lds_barrier();
-        return ((have >> bit) & 1u) != 0;
-    };
-    // linear q's row blocks that nobody has finished yet, by this workgroup
-    auto run_missing = [&](int q) INLINE {
-        stage(q);
-        for (int i = 0; i < kDecodeGrid; ++i) {
-            const int slot = (self + i) & (kDecodeGrid - 1);
-            read_words(done_word(a, q, 0), 32);
-            if (has_word(slot >> 5, slot & 31)) continue;
-            const int kt = a.ph[q].kt;
-            for (int j = first_block(q, slot); j < a.ph[q].nb; j += kDecodeGrid) {
-                for (int t = wave; t < kt; t += WAVES) {
-                    const long tile = (long)j * kt + t;
-                    const PackedTile w = load_packed_tile_cached(
-                        reinterpret_cast<const v4i *>(a.ph[q].packed) + tile * (FLEXQ_TILE_BYTES / 16), lane);
-                    consume(w, GROUP ? a.ph[q].scales[tile * 32 + (lane & 31)] : (uint16_t)0, t);
-                }
-                finish(q, j, GROUP ? (uint16_t)0 : a.ph[q].scales[32 * j + (lane & 31)]);
-            }
+    // ---- where a wait ran out: what nobody has done yet, by this workgroup ------------------------
+    // One of the bits of `wanted` that are clear in a row of words, as word * 32 + bit, or -1: those
+    // who ask at the same time get different ones where there are enough.  (Wavefront 0 set its own
+    // bits: they are there once its stores are.)
+    auto pick_missing = [&](const unsigned *word, int step, int words, unsigned wanted) INLINE {
+        if (wave == 0) {
             __builtin_amdgcn_s_waitcnt(kNoLoads);
-            if (wave == 0) set_done(q, slot);
+            if (lane < 8) s_words[lane] = lane < words ? ~peek(word + step * lane) & wanted : 0u;
+        }
+        lds_barrier();
+        int total = 0, at = 0, before = 0;
+        unsigned rest = 0;
+        for (int i = 0; i < 8; ++i) total += __builtin_popcount(__builtin_amdgcn_readfirstlane((int)s_words[i]));
+        const int rank = (self * total) >> 8;
+        for (int i = 0, sum = 0; i < 8; ++i) {
+            const unsigned w = (unsigned)__builtin_amdgcn_readfirstlane((int)s_words[i]);
+            if (sum <= rank) {
+                at = i;
+                before = sum;
+                rest = w;
+            }
+            sum += __builtin_popcount(w);
+        }
+        for (int i = before; i < rank; ++i) rest &= rest - 1u;
+        lds_barrier();
+        return total == 0 ? -1 : at * 32 + __builtin_ctz(rest);
+    };
+    // Linear q's row blocks, a workgroup's share at a time and a turn of tiles in flight.  The
+    // registers are those of the stream, which begins anew afterwards.
+    auto run_missing = [&](int q) INLINE {
+        bool staged = false;
+        for (int round = 0; round < kDecodeGrid; ++round) {       // (each sets a bit)
+            const int slot = pick_missing(done_word(a, q, 0), 32, 8, ~0u);
+            if (slot < 0) break;
+            if (!staged) stage(q);
+            staged = true;
+            n_kt = a.ph[q].kt;
+            n_blocks = a.ph[q].nb;
+            n_packed = (const uint8_t *)a.ph[q].packed;
+            n_scales = a.ph[q].scales;
+            const int turns = turns_of(n_kt);
+            for (nj = first_block(q, slot); nj < n_blocks; nj += kDecodeGrid) {
+                for (nr = 0; nr < turns; ++nr) {
+#pragma unroll
+                    for (int p = 0; p < GS; ++p) request(p, false);
+#pragma unroll
+                    for (int p = 0; p < GS; ++p) {
+                        const int t = (nr * GS + p) * WAVES + wave;
+                        if (t < n_kt) consume(st[p], GROUP ? gs[p] : (uint16_t)0, t);
+                    }
+                }
+                finish(q, nj, GROUP ? (uint16_t)0 : a.ph[q].scales[32 * nj + (lane & 31)]);
+            }
+            if (wave == 0) {
+                __builtin_amdgcn_s_waitcnt(kNoLoads);
+                set_done(q, slot);
+            }
         }
     };
 
@@ -505,21 +537,18 @@ void decode_block_kernel(DecodeArgs)
             }
             for (int i = ok ? k : 0; i <= (k == 0 && step == 0 ? n - 1 : k); ++i) {
                 const bool own = step == 0 && i >= k;
-                if (!own || a.pr[i].dep == k - 1) {
-                    const int pieces = own ? 1 : pieces_of(i);
-                    for (int m = 0; m < (own ? 1 : M); ++m)
-                        for (int p = 0; p < pieces; ++p) {
-                            int what = 8 * m + p;
-                            if (own) {
-                                what = my_piece(i);
-                            } else {
-                                read_words(codes_words(a, i, self & 7), 1);
-                                if (has_word(p, m)) what = -1;
-                            }
-                            if (what >= 0) produce(i, what >> 3, what & 7);
-                        }
+                if (own ? a.pr[i].dep != k - 1 : i < k && !feeds_later(i)) continue;
+                for (int round = 0; round < (own ? 1 : kDecodeGrid); ++round) {     // (each sets a bit)
+                    const int what = own ? my_piece(i)
+                                         : pick_missing(codes_words(a, i, self & 7), 1, pieces_of(i), all_tokens);
+                    if (what < 0) break;
+                    produce(i, what, own ? a.spin : 0);
                 }
-                if (i < k && feeds_later(i)) run_missing(i);
+                if (i < k) run_missing(i);
+            }
+            if (!ok) {
+                open(k);
+                request_turn();
             }
         }
         if (j < nb && !mine) {      // the tiles in flight are the next linear's instead
