@@ -56,7 +56,9 @@ def equal(a, b):
                                      (1280, 4224, 18464), (4224, 1152, 128), (4096, 4096, 4128)])
 def test_one_launch_equals_the_separate_ones(H, F, QKV, group):
     block = Block(H, F, QKV, group)
-    launched = 0
+    # with group-128 scales only where the streaming kernel adds in this one's order: every linear
+    # unsplit (fewer row blocks of short rows are cut) and by eight wavefronts
+    takes = group == 0 or (H, F, QKV) == (4096, 4096, 4128)
     for bits in ((6, 6, 6, 8), (8, 6, 8, 6)):
         layer = block.layer(bits)
         for M in (1, 2, 7, 8, 9, 16):
@@ -65,17 +67,41 @@ def test_one_launch_equals_the_separate_ones(H, F, QKV, group):
             assert not run(layer, M, ws, 2, x_ffn=want["o"], **data, **want)
             for spin in (0, -1):
                 got = block.outputs(M)
-                if not run(layer, M, ws, 1, spin, x_ffn=got["o"], **data, **got):
-                    assert group == 128          # its sums would have another order
-                    continue
-                launched += 1
+                assert run(layer, M, ws, 1, spin, x_ffn=got["o"], **data, **got) == takes
                 torch.cuda.synchronize()
                 assert equal(got, want), (M, spin)
                 assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
             got = block.outputs(M)
             fq.layer_linears(layer, M, ws, x_ffn=got["o"], **data, **got)
             assert equal(got, want)
-    assert launched > 0 or (group == 128 and H < 4096) or QKV == 128
+
+
+# Row blocks: one to four per workgroup.  Tiles per wavefront: 4 or 8 (whole turns of four), 10 or 11 (a part of
+# the third), 5 (turns of five), 13 or 14 (a part of the third), 28; rows of two to seven pieces per token.  Where the
+# launches are kept: sixteen or four wavefronts on some linear, or codes that do not fit LDS.
+@pytest.mark.parametrize("H,F,QKV,takes,keeps", [(4096, 11008, 12288, (5, 8, 9, 11), (1, 4, 12)),
+                                                 (5120, 13824, 15360, (5, 8, 9), (2, 4, 10, 16)),
+                                                 (8192, 28672, 10240, (1, 5), (6,)),
+                                                 (5120, 5120, 8192, (3, 15), (16,))])
+def test_group_scales_of_whole_models(H, F, QKV, takes, keeps):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(H)
+    block = Block.__new__(Block)
+    block.H, block.F, block.QKV, block.group = H, F, QKV, 128
+    block.packed = [fq.pack_w6(*fq.quant_w6(torch.randn((n, k), generator=g, device=DEV).mul_(0.02), 128), 128)
+                    for n, k in ((QKV, H), (H, H), (2 * F, H), (H, F))]
+    block.gains = [to_dev(synth.norm_gain(H, seed=i)) for i in (10, 11)]
+    layer = block.layer((6, 8, 6, 8))
+    for M in takes + keeps:
+        say(f"one launch, group scales: H={H} F={F} M={M}")
+        ws, data, want = layer.make_workspace(M), block.inputs(M, 100 * M), block.outputs(M)
+        assert not run(layer, M, ws, 2, x_ffn=want["o"], **data, **want)
+        for spin in (0, -1):
+            got = block.outputs(M)
+            assert run(layer, M, ws, 1, spin, x_ffn=got["o"], **data, **got) == (M in takes), M
+            torch.cuda.synchronize()
+            assert equal(got, want), (M, spin)
+            assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
 
 
 @pytest.mark.parametrize("first,last", [(0, 1), (0, 2), (1, 3), (2, 3), (0, 0), (3, 3)])
