@@ -157,7 +157,10 @@ void decode_block_kernel(DecodeArgs)
     };
     auto request_turn = [&]() INLINE {
 #pragma unroll
-        for (int p = 0; p < GS; ++p) request(p, false);
+        for (int p = 0; p < GS; ++p) {
+            request(p, false);
+            __builtin_amdgcn_sched_barrier(0);      // in this order: a wait counts the loads behind a tile's
+        }
         advance();
     };
 
@@ -240,23 +243,28 @@ void decode_block_kernel(DecodeArgs)
     };
     auto pieces_of = [&](int i) INLINE { return flexq::decode_pieces(a.pr[i].mode, a.pr[i].L); };
     // What a wait is for may have been done in this workgroup's place, by one that no longer waited for
-    // it: the last lane looks for that, on the same trip through memory.
+    // it: the last lane looks for that, on the first trip through memory.
     constexpr int kReady = 1, kDoneForUs = 2;
     auto bit_of_last_lane = [&](unsigned v, int bit) INLINE { return (__builtin_amdgcn_readlane((int)v, 63) >> bit) & 1; };
     auto codes_there = [&](int k) INLINE {
         const int pieces = pieces_of(k);
         const unsigned *const word = lane == 63 ? done_word(a, k, self >> 5) : codes_words(a, k, self & 7) + (lane & 7);
+        bool look = lane < pieces || lane == 63;
         return wait_for([&] {
-            unsigned v = all_tokens;
-            if (lane < pieces || lane == 63) v = peek(word);
+            unsigned v = lane == 63 ? 0u : all_tokens;
+            if (look) v = peek(word);
+            look = lane < pieces;
             if (bit_of_last_lane(v, self & 31)) return kDoneForUs;      // this workgroup's row blocks
             return __all(lane >= pieces || v == all_tokens) ? kReady : 0;
         }, a.spin);
     };
     auto outputs_there = [&](int k, int what) INLINE {                  // for piece `what` of the next linear's producer
         const unsigned *const word = lane == 63 ? codes_words(a, k + 1, self & 7) + (what >> 5) : done_word(a, k, lane & 7);
+        bool look = lane < 8 || lane == 63;
         return wait_for([&] {
-            const unsigned v = peek(word);
+            unsigned v = lane == 63 ? 0u : ~0u;
+            if (look) v = peek(word);
+            look = lane < 8;
             if (bit_of_last_lane(v, what & 31)) return kDoneForUs;
             return __all(lane == 63 || v == ~0u) ? kReady : 0;
         }, a.spin);
@@ -470,19 +478,18 @@ void decode_block_kernel(DecodeArgs)
         return total == 0 ? -1 : at * 32 + __builtin_ctz(rest);
     };
     // Linear q's row blocks, a workgroup's share at a time and a turn of tiles in flight.  The
-    // registers are those of the stream, which begins anew afterwards.
-    auto run_missing = [&](int q) INLINE {
-        bool staged = false;
-        for (int round = 0; round < kDecodeGrid; ++round) {       // (each sets a bit)
-            const int slot = pick_missing(done_word(a, q, 0), 32, 8, ~0u);
-            if (slot < 0) break;
-            if (!staged) stage(q);
-            staged = true;
-            n_kt = a.ph[q].kt;
-            n_blocks = a.ph[q].nb;
-            n_packed = (const uint8_t *)a.ph[q].packed;
-            n_scales = a.ph[q].scales;
-            const int turns = turns_of(n_kt);
+    // registers are those of the stream, which begins anew, at linear k, afterwards.
+    auto run_missing = [&](int q, int k) INLINE {
+        int slot = pick_missing(done_word(a, q, 0), 32, 8, ~0u);
+        if (slot < 0) return;
+        stage(q);
+        n_kt = a.ph[q].kt;
+        n_blocks = a.ph[q].nb;
+        n_packed = (const uint8_t *)a.ph[q].packed;
+        n_scales = a.ph[q].scales;
+        const int turns = turns_of(n_kt);
+        int rounds = 0;
+        do {                                    // (each sets a bit)
             for (nj = first_block(q, slot); nj < n_blocks; nj += kDecodeGrid) {
                 for (nr = 0; nr < turns; ++nr) {
 #pragma unroll
@@ -499,7 +506,10 @@ void decode_block_kernel(DecodeArgs)
                 __builtin_amdgcn_s_waitcnt(kNoLoads);
                 set_done(q, slot);
             }
-        }
+            slot = pick_missing(done_word(a, q, 0), 32, 8, ~0u);
+        } while (slot >= 0 && ++rounds < kDecodeGrid);
+        open(k);
+        request_turn();
     };
 
     // ---- the block ------------------------------------------------------------------------
@@ -517,39 +527,35 @@ void decode_block_kernel(DecodeArgs)
         bool mine = j < nb;      // row blocks of this linear are left for this workgroup
         // Step 0: this workgroup's share of the producers whose input is complete once linear
         // k - 1 is (k = 0: of those that need none).  Step 1: the codes of linear k.  Where a wait
-        // ran out, first everything that is missing, in order.
+        // ran out, first everything that is missing, in order.  (That part has a copy of the producers
+        // of its own and lies behind the rest: in between, the longer way through the instructions cost
+        // every launch 0.2 to 1 us.)
 #pragma clang loop unroll(disable)
         for (int step = 0; step < 2; ++step) {
-            bool ok = true;
+            int got = kReady;
             if (step == 0) {
                 if (k > 0) {
                     if (a.pr[k].dep != k - 1 || my_piece(k) < 0) continue;
-                    const int got = outputs_there(k - 1, my_piece(k));
-                    if (got == kDoneForUs) continue;
-                    ok = got == kReady;
+                    got = outputs_there(k - 1, my_piece(k));
                 }
-            } else {
-                if (!mine) break;
-                const int got = codes_there(k);
+            } else if (mine) {
+                got = codes_there(k);
                 mine = got != kDoneForUs;
-                if (got != 0) break;
-                ok = false;
             }
-            for (int i = ok ? k : 0; i <= (k == 0 && step == 0 ? n - 1 : k); ++i) {
-                const bool own = step == 0 && i >= k;
-                if (own ? a.pr[i].dep != k - 1 : i < k && !feeds_later(i)) continue;
-                for (int round = 0; round < (own ? 1 : kDecodeGrid); ++round) {     // (each sets a bit)
-                    const int what = own ? my_piece(i)
-                                         : pick_missing(codes_words(a, i, self & 7), 1, pieces_of(i), all_tokens);
-                    if (what < 0) break;
-                    produce(i, what, own ? a.spin : 0);
+            if (__builtin_expect(got == 0, 0)) {
+                for (int i = 0; i < k + step; ++i) {
+                    if (i < k && !feeds_later(i)) continue;
+                    for (int round = 0; round < kDecodeGrid; ++round) {     // (each sets a bit)
+                        const int what = pick_missing(codes_words(a, i, self & 7), 1, pieces_of(i), all_tokens);
+                        if (what < 0) break;
+                        produce(i, what, 0);
+                    }
+                    if (i < k) run_missing(i, k);
                 }
-                if (i < k) run_missing(i);
             }
-            if (!ok) {
-                open(k);
-                request_turn();
-            }
+            if (step == 1 || got == kDoneForUs) continue;
+            for (int i = k; i <= (k == 0 ? n - 1 : k); ++i)
+                if (a.pr[i].dep == k - 1 && my_piece(i) >= 0) produce(i, my_piece(i), a.spin);
         }
         if (j < nb && !mine) {      // the tiles in flight are the next linear's instead
             open(k + 1);
