@@ -44,17 +44,25 @@ namespace flexq {
 
 namespace {
 
-// The one-launch form of the call (decode_block.hip), where it applies: fills its arguments.  What it
-// gains is the launches between linears that do not wait for each other, so it is taken for calls
-// that hold stages 0 and 1 (measured on seven models of hidden size 512 .. 8192 at 1 .. 16 tokens,
-// stages 0 to 3: 0.82 .. 1.00 of the launches' time, LLaMA-2-7B's block at 8 tokens 56.4 -> 47.9 us,
-// 13B's 71.7 -> 61.6, 70B's at one token 125.5 -> 114.7; stages 0 and 1 alone 0.56 .. 0.88).  A wait
-// for another linear's outputs costs as much inside as two launches do (stages 2 and 3: 0.86 .. 1.17,
-// 1 and 2: 0.88 .. 1.27, one stage 0.73 .. 1.26): those keep the launches.
+// The one-launch form of the call (decode_block.hip), where it applies: fills its arguments.
+//
+// Where it is taken.  What it gains is the launches between linears that do not wait for each other, so
+// it is for calls that hold stages 0 and 1: one launch over launches, LLaMA-2's 7B, 13B and 70B shapes at
+// 1 .. 11 tokens, stages 0 to 3 0.85 .. 0.95 (7B at 8 tokens 54.1 -> 47.5 us, 13B's 69.1 -> 61.5, 70B's
+// at one token 125.7 -> 113), stages 0 and 1 alone 0.84 .. 1.02.  A wait for another linear's outputs costs
+// as much inside as two launches do: stages 2 and 3 0.95 .. 1.01, 1 and 2 0.95 .. 1.09, one stage 0.89 ..
+// 1.27; those keep the launches.
+// And for hidden sizes whose row block of tiles fills three quarters of a turn (24 of 32 tiles): below, fewer
+// bytes are in flight and a wait covers less.  In replayed graphs, stages 0 to 3 at 1 .. 16 tokens, hidden
+// size 512 1.10 .. 1.25, 1024 0.99 .. 1.10, 2048 0.92 .. 1.04, 2304 0.98 .. 1.13, 2560 0.96 .. 1.08, 3072 0.89 ..
+// 0.99, 3584 0.84 .. 0.95.  (Called eagerly, 512 to 2048 take 0.85 .. 1.1 of the launches, whose seven calls
+// are then the host's 26 us.)
+constexpr int kLeastHidden = 24 * 128;
+
 bool one_launch(const flexq_layer *L, int M, const flexq_layer_io *io, int first, int last, void *workspace,
                 size_t room, bool forced, DecodeArgs &a, int &lds_bytes)
 {
-    if (!forced && (first > 0 || last < 1)) return false;
+    if (!forced && (first > 0 || last < 1 || L->H < kLeastHidden)) return false;
     if (M > 16 || L->H > 8192 || L->F > 32768 || device_cu_count() != kDecodeGrid) return false;
     struct Stage {
         const void *w;

@@ -71,6 +71,10 @@ def test_one_launch_equals_the_separate_ones(H, F, QKV, group):
                 torch.cuda.synchronize()
                 assert equal(got, want), (M, spin)
                 assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
+            # by the library's own choice only where a row block of the hidden size fills a turn
+            got = block.outputs(M)
+            assert run(layer, M, ws, 0, x_ffn=got["o"], **data, **got) == (takes and H >= 3072)
+            assert equal(got, want)
             got = block.outputs(M)
             fq.layer_linears(layer, M, ws, x_ffn=got["o"], **data, **got)
             assert equal(got, want)
