@@ -308,11 +308,19 @@ flexq_status flexq_linear_g128(const void *packed, const int8_t *xq,
  * first call (flexq_workspace_init), shared by the stages, which run in order on
  * `stream`.  Results of every stage are those of the corresponding single calls
  * (flexq_rmsnorm_quant / flexq_swiglu_quant / flexq_gemm_w6a6 / _w6a8), status codes
- * as theirs; nothing is launched if an argument of any requested stage is bad.  Calls
- * of up to 16 tokens that hold stages 0 and 1 run as one launch where the codes of the
- * deepest linear fit LDS (11 tokens of 11008 values, 5 of 28672) and the buffers allow it
- * (no h_* output, no output overlapping another buffer but as `x_ffn` may alias `o`):
- * the same results.  The workspace must not be shared by calls that overlap in time.
+ * as theirs; nothing is launched if an argument of any requested stage is bad.  The
+ * workspace must not be shared by calls that overlap in time.
+ *
+ * A call runs as ONE launch, with the same results, where all of this holds: stages 0
+ * and 1 are both in it; at most 16 tokens; 3072 <= H <= 8192 and F <= 32768; the codes
+ * of its deepest linear fit LDS (stages 0 to 3: 11 tokens at F = 11008, 9 at 13824, 5 at
+ * 28672); no h_* output; no output overlaps another buffer, but `x_ffn` may be `o`; the
+ * device has 256 CUs.  With group 128 also: each of its linears is one that the
+ * streaming kernel runs unsplit with eight wavefronts, whose order of additions this is
+ * (LLaMA-2-7B's shapes at 5 to 11 tokens, 13B's at 5 to 9, 70B's at 1 to 5).
+ * It takes a whole CU per workgroup.  Beside other streams' kernels its workgroups start
+ * as CUs come free; those that are there wait 41 us for the others at most and then do
+ * their share, so that it ends whatever else runs, later than on an idle device.
  */
 typedef struct {
     int H, F, QKV, group;

@@ -321,11 +321,11 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
 
     // The streaming kernel quantizes the activations itself where that is little work: every
     // workgroup scans the tokens' whole fp16 rows, which for one token pays off up to about 1024
-    // workgroups (measured on sixteen layers of 512 .. 28672 deep: 0.73 .. 0.94 of the time with a
-    // quantize launch ahead, 1.00 at 1792 workgroups), for more while the values that a CU's workgroups
-    // scan one after the other stay under ten thousand (4096 x 4096 at two tokens 0.88, 1024 x 16384 at four
-    // 0.87, 512 x 1600 at eight 0.77; beyond, 4096 x 12288 at two 1.04, 2048 x 8192 at six 1.02).  The
-    // kernel can do up to eight; tune.fuse = 1 asks for that.
+    // workgroups (measured on eighteen layers N x K of 512 .. 28672 deep: 0.71 .. 0.93 of the time with a
+    // quantize launch ahead, 1.01 at 1792 workgroups), for more while the values that a CU's workgroups
+    // scan one after the other stay under ten thousand (4096 x 4096 at two tokens 0.74, 5120 x 5120 at two
+    // 0.83, 512 x 1536 at six 0.83; beyond, 4096 x 4096 at four 0.88, 12288 x 4096 at two 1.03, 2048 x 8192
+    // at four 1.06).  The kernel can do up to eight; tune.fuse = 1 asks for that.
     const int ks0 = choose_split(M, N, K, tune.split_k);
     const long wgs0 = (long)(N / 32) * ks0;
     const bool little = M == 1 ? wgs0 <= 1024 : (long)M * K * ((wgs0 + 255) / 256) <= 10240;

@@ -36,9 +36,11 @@
 // with ordinary loads, so that an XCD fetches them once: no cache can hold an older value of
 // their lines, which nobody reads before the bits are there and whose rows are whole lines.
 //
-// Results equal the separate launches bit for bit: the sums are exact integers, or, with group-128
-// scales, fp32 sums in the order of the streaming kernel with eight wavefronts and one K split,
-// and the producers are the same operations in the same order.
+// Results equal the separate launches bit for bit for finite inputs, which the library asks for (a
+// NaN hides its lane's other values from a row's maximum, and rows lie over lanes differently here):
+// the sums are exact integers, or, with group-128 scales, fp32 sums in the order of the streaming
+// kernel with eight wavefronts and one K split, and the producers are the same operations in the
+// same order.
 #include "../../include/flexq.h"
 #include "decode_block.h"
 #include "flexq_device.h"

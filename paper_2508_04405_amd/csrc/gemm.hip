@@ -687,15 +687,15 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
             if (c.tail_form == 2 && c.us >= 0.95 * t_best) c = gemm_wlds_choose(a.M, a.N, a.K, false);
             const WldsChoice low = gemm_low_choose(a.M, a.N, a.K, a.partial_bytes);
             // (against 256-row tiles cut along K the low tiles must promise 12 %: the two
-            // estimates are good to about 6 % each, and at 256 tokens of a 10240 x 8192 layer
-            // 36 against 33 us is where the line falls)
+            // estimates are good to about 6 % each.  Too much at 129 to 256 tokens of a 10240 x 8192
+            // layer, which run at 33 to 35 us where low tiles in three pieces take 29.5 to 32.)
             const bool take_low = low.us < t_best && low.us < (c.tail_form == 2 ? 0.88 : 1.0) * c.us;
             // 192-row tiles where 256 rows would be half padding (576 tokens of 15360 x 5120 53.0 ->
             // 46.8 us, 333 of 27648 x 5120 56.7 -> 50.1, 576 of 57344 x 8192 287 -> 253) or leave a quarter
             // of the chip idle (1152 of 8192 x 8192 81.5 -> 74.6): for 5 % of the estimated time, against a
-            // cut form, whose estimate is coarser, for 10.  Measured against every other form on fourteen layers at
-            // 256 .. 4096 tokens the line takes fourteen of 160 cells, 0.88 to 0.96 of the fastest other's
-            // time each; forced on the rest they take 0.86 to 3 times as long, 1.1 in the middle.
+            // cut form, whose estimate is coarser, for 10.  On 24 random layers that the line takes (2048 ..
+            // 22272 deep, 286 .. 2227 tokens) they need 0.88 to 1.01 of the fastest other form's time, 0.91 on
+            // average.
             const double others = take_low ? low.us : c.us < t_best ? c.us : t_best;
             const bool cut = take_low ? low.tail_form == 5 : c.us < t_best ? c.tail_form == 2 : a.split_k > 1;
             if (device_cu_count() == kStreamKGrid &&

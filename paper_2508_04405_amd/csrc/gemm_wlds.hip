@@ -1349,7 +1349,9 @@ WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut)
 // full chip -- 30 % more for the same work than a 256x256 tile's, which pays for itself where
 // that would leave CUs idle.  Fitted on eighteen layers (512 .. 57344 wide, 512 .. 28672 deep)
 // at 129 .. 2048 tokens; taken there it gains 5 to 45 % between 129 and 700 tokens (8192 x
-// 8192 at 300 tokens: 44.5 -> 34.9 us, 4096 x 4096 at 220: 23.8 -> 16.4).
+// 8192 at 300 tokens: 44.5 -> 34.9 us, 4096 x 4096 at 220: 23.8 -> 16.4).  The meeting of more than 192
+// pieces is priced too dear: 15360 x 5120 at 129 .. 256 tokens stays whole at 31 to 32 us, two pieces per tile
+// take 26 to 29.
 WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes)
 {
     const int tiles = ((M + 127) / 128) * ((N + 255) / 256), KT = K / FLEXQ_TILE_K;
@@ -1453,10 +1455,11 @@ int group_form(int M, int N, int split_k, size_t partial_bytes)
 // stages is then the whole time, and the sums are cheap.  Estimated as the time of one round: a
 // stage of a 64x256 item takes 0.59 us while at most half of the CUs have one, 0.74 on a full chip,
 // of a 128x256 item 0.86 and 1.08, plus 4.4 and 6.8 us; S pieces meet in 2.5 + 0.55 S us and what their
-// number in all costs.  Measured over 150 .. 3667 tokens, 1024 .. 24448 deep, 512 .. 5120 wide: 700 tokens
-// of 8576 x 512 44 -> 18.5 us, 1101 of 13824 x 512 68 -> 24, 2000 of 24448 x 512 117 -> 46, 500 of 13824 x
-// 5120 72 -> 53; with scales on both operands 700 of 13824 x 5120, with the quantizer, 98.5 -> 87.8.  A
-// function of the shape alone, for every row alike.  The splits show in the sums' last bits, so an
+// number in all costs.  Measured on 170 random layers of 1024 .. 24448 deep and 512 .. 5120 wide at 150 ..
+// 3667 tokens, scales on the weights and on both operands: 138 of the 340 cells are cut anew, in 0.31 ..
+// 0.94 of the time (700 tokens of K 8576, N 512 44 -> 19 us, 1101 of 13824, 512 69 -> 24, 2000 of 24448, 512
+// 120 -> 49, 500 of 13824, 5120 80 -> 54; both operands' scales, 700 of 13824, 5120 91 -> 81).  A function of
+// the shape alone, for every row alike.  The splits show in the sums' last bits, so an
 // unsplit layer is only cut for 7 % of the time, one that is cut already only cut anew for a quarter.
 int group_split(int M, int N, int K, int ks, size_t partial_bytes)
 {

@@ -80,6 +80,9 @@ bool one_launch(const flexq_layer *L, int M, const flexq_layer_io *io, int first
     a.group = L->group;
     a.eps = L->eps;
     a.words = (unsigned *)workspace;
+    // 41 us (0.16 us a poll).  Undisturbed no wait takes 128 polls: with bounds of 128, 256, 512 and 1024 the
+    // 70B block takes 115 us, with 64 117; and beside another stream's GEMMs of 2048, 1000 and 300 tokens or
+    // another block the four are equal within 1 %.
     a.spin = 256;
     // every linear's codes and token scales in a place of its own, behind the counters
     uint8_t *p = (uint8_t *)workspace + FLEXQ_WORKSPACE_COUNTER_BYTES, *const end = (uint8_t *)workspace + room;
