@@ -85,7 +85,7 @@ flexq_status flexq_dev_linear(const flexq_dev_tuning *tuning, int act_bits, cons
 
 /*
  * flexq_layer_linears with overrides: tuning->fuse 1 = one launch for all the stages wherever its
- * conditions allow (up to 16 tokens; buffers that do not overlap; no optional outputs), 2 =
+ * conditions allow (those of flexq_layer_linears, but any range of stages and any H up to 8192), 2 =
  * never; tuning->spin = polls before one of its workgroups stops waiting for the others and does
  * what is missing itself (0 = the library's, -1 = at once).  *launched (may be NULL) receives 1
  * for the one launch, else 0.  Results are the same either way.

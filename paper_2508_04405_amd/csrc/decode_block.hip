@@ -24,7 +24,7 @@
 // producer's bits are there.  No workgroup waits without a bound: when its polls run out (somebody
 // is not resident: a busy device, another launch of this kind) it does what is missing itself, in
 // order, each beginning with a different part (with nobody waiting at all LLaMA-2-7B's block at 8
-// tokens takes 88 us, 70B's at one token 170; with one tile a wavefront in flight, everybody walking
+// tokens takes 83 us, 70B's at one token 168; with one tile a wavefront in flight, everybody walking
 // the same way and a wait for every piece of a row 305 and 418).  That needs nobody else and changes
 // nothing: every result is a function of buffers that no part of the launch overwrites -- the codes
 // of every linear have a place of their own, and the host takes this path only for buffers that do
@@ -206,22 +206,35 @@ void decode_block_kernel(DecodeArgs)
             const int N = a.ph[k].nb * 32;
             uint16_t *const y = a.ph[k].y + 32 * j + (lane & 31);
 #pragma unroll
-            for (int q = 0; q < 4 * MQ; ++q) {
-                const int m = mfma_row(q, lane);
-                uint16_t h;
-                if (GROUP) {
-                    float f = 0.0f;
+            for (int first = 0; first < 4 * MQ; first += 4) {
+                int part[4][WAVES];
+                float sx[4];
 #pragma unroll
-                    for (int w = 0; w < WAVES; ++w) f += __int_as_float(r[(w * 4 * MQ + q) * 64 + lane]);
-                    h = f2h(f * 0.25f * s_sx[m]);
-                } else {
-                    int v = 0;
+                for (int i = 0; i < 4; ++i) {
+                    sx[i] = s_sx[mfma_row(first + i, lane)];
 #pragma unroll
-                    for (int w = 0; w < WAVES; ++w) v += r[(w * 4 * MQ + q) * 64 + lane];
-                    h = f2h((float)(v >> 2) * (s_sx[m] * h2f(sw)));
+                    for (int w = 0; w < WAVES; ++w) part[i][w] = r[(w * 4 * MQ + first + i) * 64 + lane];
                 }
-                if (m < M)
-                    __hip_atomic_store(y + (long)m * N, h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                // (all of them ahead of the sums: else a read waits for the one before, 32 in a row)
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int m = mfma_row(first + i, lane);
+                    uint16_t h;
+                    if (GROUP) {
+                        float f = 0.0f;
+#pragma unroll
+                        for (int w = 0; w < WAVES; ++w) f += __int_as_float(part[i][w]);
+                        h = f2h(f * 0.25f * sx[i]);
+                    } else {
+                        int v = 0;
+#pragma unroll
+                        for (int w = 0; w < WAVES; ++w) v += part[i][w];
+                        h = f2h((float)(v >> 2) * (sx[i] * h2f(sw)));
+                    }
+                    if (m < M)
+                        __hip_atomic_store(y + (long)m * N, h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         }
         half ^= 1;

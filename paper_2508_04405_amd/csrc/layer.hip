@@ -48,14 +48,14 @@ namespace {
 //
 // Where it is taken.  What it gains is the launches between linears that do not wait for each other, so
 // it is for calls that hold stages 0 and 1: one launch over launches, LLaMA-2's 7B, 13B and 70B shapes at
-// 1 .. 11 tokens, stages 0 to 3 0.86 .. 0.94 (7B at 8 tokens 53.9 -> 47.4 us, 13B's 68.7 -> 61.5, 70B's
-// at one token 125.8 -> 113.0), stages 0 and 1 alone 0.84 .. 1.01.  A wait for another linear's outputs
-// costs as much inside as two launches do: stages 2 and 3 0.93 .. 1.01, 1 and 2 0.93 .. 1.09, one stage
+// 1 .. 11 tokens, stages 0 to 3 0.86 .. 0.96 (7B at 8 tokens 54.1 -> 47.5 us, 13B's 69.0 -> 61.2, 70B's
+// at one token 123 -> 113), stages 0 and 1 alone 0.84 .. 1.01.  A wait for another linear's outputs
+// costs as much inside as two launches do: stages 2 and 3 0.93 .. 1.01, 1 and 2 0.90 .. 1.10, one stage
 // 0.83 .. 1.31; those keep the launches.
 // And for hidden sizes whose row block of tiles fills three quarters of a turn (24 of 32 tiles): below, fewer
 // bytes are in flight and a wait covers less.  In replayed graphs, stages 0 to 3 at 1 .. 16 tokens, hidden
-// size 512 1.10 .. 1.25, 1024 0.99 .. 1.10, 2048 0.92 .. 1.03, 2304 0.98 .. 1.12, 2560 0.98 .. 1.08, 3072 0.91 ..
-// 1.00, 3584 0.84 .. 0.95.  (Called eagerly, 512 to 2048 take 0.85 .. 1.13 of the launches, whose seven calls
+// size 512 1.10 .. 1.25, 1024 0.99 .. 1.10, 2048 0.92 .. 1.03, 2304 0.98 .. 1.12, 2560 0.96 .. 1.08, 3072 0.91 ..
+// 1.01, 3584 0.84 .. 0.97.  (Called eagerly, 512 to 2048 take 0.85 .. 1.13 of the launches, whose seven calls
 // are then the host's 26 us.)
 constexpr int kLeastHidden = 24 * 128;
 
