@@ -57,8 +57,10 @@ __device__ __forceinline__ float absmax4(const float4_any &v, float best)
 
 // One scale per row: a workgroup of T lanes holds its row in registers, CH float4 a lane,
 // between the absmax and the codes.  Bound by HBM: five bytes an element, each moved once
-// (a loop over the row with one float a lane, read twice, took 139 us for 8192 x 8192; this
-// takes 61 us, 5.5 TB/s, and 57344 x 8192 431 us instead of 1012).
+// (a loop over the row with one float a lane, read twice, took 139 us for 8192 x 8192, this
+// with cached loads 64 us).  The floats, read once, come past the caches, which keep the codes
+// for the packer: 57.8 us, 5.8 TB/s, and 75 us instead of 80 with the packer behind it.  (Stores
+// of the codes past the caches too: the packer loses more than this kernel gains, 82 us for both.)
 template <int CH, int T>
 __global__ __launch_bounds__(T) void quant_w6_row_kernel(const float *__restrict__ w, int K,
                                                          int8_t *__restrict__ wq, uint16_t *__restrict__ sw)
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(T) void quant_w6_row_kernel(const float *__restrict
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const int c = threadIdx.x + T * i;
-        if (c < chunks) held[i] = src[c];
+        if (c < chunks) held[i] = __builtin_nontemporal_load(src + c);
     }
     float amax = 0.0f;
 #pragma unroll
@@ -98,8 +100,8 @@ __global__ __launch_bounds__(T) void quant_w6_row_kernel(const float *__restrict
 
 // One scale per 128 consecutive k: 32 lanes own a group, four floats each, and the absmax
 // meets by five shuffles.  Groups follow each other through the whole matrix, four KiB of a
-// wavefront's loads in flight (8192 x 8192: 61 us; with one wavefront per
-// group and two floats a lane it took 189 us).
+// wavefront's loads in flight, past the caches as above (8192 x 8192: 53.4 us, with cached loads
+// 59.8; with one wavefront per group and two floats a lane it took 189 us).
 __global__ __launch_bounds__(256) void quant_w6_g128_kernel(const float *__restrict__ w, long chunks,
                                                             int8_t *__restrict__ wq, uint16_t *__restrict__ sw)
 {
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(256) void quant_w6_g128_kernel(const float *__restr
     float4_any held[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i)
-        if (c0 + 256 * i < chunks) held[i] = src[c0 + 256 * i];
+        if (c0 + 256 * i < chunks) held[i] = __builtin_nontemporal_load(src + c0 + 256 * i);
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const long c = c0 + 256 * i;
