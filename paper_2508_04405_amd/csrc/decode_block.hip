@@ -60,7 +60,6 @@ typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 constexpr int WAVES = 8;
 constexpr int THREADS = 64 * WAVES;
 constexpr int kScopeAgent = 16;            // cache policy of buffer accesses: device scope
-constexpr int kNonTemporal = 2;
 constexpr int kNoLoads = 0x0F70;          // s_waitcnt vmcnt(0), as the builtin encodes it
 constexpr unsigned kNowhere = 0xFFFFF000u; // a lane offset beyond every buffer: loads zero, touches nothing
 

@@ -6,6 +6,8 @@
 
 namespace {
 
+constexpr int kNonTemporal = 2;        // cache policy of a buffer load whose bytes are used once
+
 // swizzled byte offset of 16-byte chunk c (0..7) of row `row` in a stage
 __device__ __forceinline__ int lds_off(int row, int c)
 {

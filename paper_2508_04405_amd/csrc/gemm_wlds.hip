@@ -402,7 +402,8 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
 // or, with SK, the stages of `item_count` tiles cut into `tail_wgs` runs.
 // GROUP (group tiles only): 1 = weight scales per 128-k group, one scale per token; 2 = both
 // operands' scales per group.
-template <int TILE, int SK, int GROUP = 0>
+// WPOLICY: cache policy of the weights' DMA loads (per-channel scales).
+template <int TILE, int SK, int GROUP = 0, int WPOLICY = 0>
 __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *lds, int &s_last, int tiles_m,
                                           int tiles_n, int item_begin, int item_count, int tail_wgs)
 {
@@ -541,7 +542,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                 uint8_t *dst = lds + S::WBASE + buf * S::WSTAGE + p * 1024;
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     wrsrc, (void __attribute__((address_space(3))) *)dst, 16, wlane,
-                    (unsigned)(wtile * KT + ks + kb) * FLEXQ_TILE_BYTES + 1024u * plane, 0, 0);
+                    (unsigned)(wtile * KT + ks + kb) * FLEXQ_TILE_BYTES + 1024u * plane, 0, WPOLICY);
             }
         }
     };
@@ -1219,6 +1220,10 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
         run_items<3, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
     }
+    if (FORM == 7) {   // the same for one row of tiles, which uses a weight once
+        run_items<3, 0, 0, kNonTemporal>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+        return;
+    }
     if (FORM == 6) {   // every item a tile of 192 x 256
         run_items<6, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
@@ -1518,7 +1523,13 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
     if (a.group != 0 || a.split_k > 1 || a.sxg) return hipErrorInvalidValue;
     if (tail_form == 3) {   // low tiles throughout
         const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256;
-        return launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
+        // One row of tiles, up to 128 tokens on wide layers, uses a weight once: past the caches 57344 x
+        // 8192 takes 64.5 us instead of 68.3 at 33 tokens, 67 / 72.5 at 64, 71 / 75.6 at 100, 75.5 / 78.7 at
+        // 128, 45056 x 4096 at 50 30.8 / 31.7.  (Cut along K, 28672 x 8192 at 97, it makes no difference
+        // from HBM, 57.5 / 58, and costs 8 % where the Infinity Cache holds the weights.  A branch in the
+        // shared kernel costs 333 tokens of 13664 x 5248 3 %: a kernel of its own.)
+        return low_m == 1 ? launch_form<7>(a, low_m, cols, cols, 0, 0, grid_for(cols), st)
+                          : launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
     }
     if (tail_form == 6) {   // 192-row tiles throughout
         const int rows = (a.M + 191) / 192, cols = (a.N + 255) / 256;
