@@ -49,7 +49,7 @@ extern "C" {
  *             (0 = the library's 128; -1 = never wait, every piece gives up at once:
  *             the path a busy or smaller device takes; at most 1 << 20)
  * With gemm_cfg 13, split_k > 1 asks for that many pieces per tile of the last round.
- * gemm_cfg 12 to 17 and 20 with group-128 scales, and 18 or 19 without, return FLEXQ_EINVAL.
+ * gemm_cfg 12 to 17 and 20 with group-128 scales, and 18, 19 or 22 without, return FLEXQ_EINVAL.
  */
 typedef struct {
     int kernel, split_k, waves, gemm_cfg, ablate, fuse, tiles, spin;
@@ -69,9 +69,10 @@ typedef struct {
  * pieces (for fewer than 256 tiles: all of them); 17, forced only: 13 with the
  * tail cut into 256 runs that cross tile borders; 18: group-128 scales, persistent 128x256
  * tiles, those beyond the last whole round of 256 each cut along K into split_k pieces; 19:
- * with those run at half the height, 64x256; 20: 192x256 tiles of the kernel of 12), s = the number of K splits
+ * with those run at half the height, 64x256; 20: 192x256 tiles of the kernel of 12; 22: the tiles of 18, each in two
+ * pieces at the same stage), s = the number of K splits
  * (for 13, 16, 17: the number of runs in all; for 14: of half tiles; for 18, 19: of pieces
- * per cut tile; 500 more
+ * per cut tile; for 22: the first piece's stages; 500 more
  * when the streaming kernel read its activations in tile order).  Results are the same
  * whatever the overrides, but for group-128 scales, whose fp32 sums round by where K is cut:
  * there the same bits go with the same K splits.

@@ -383,7 +383,7 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
             if (a.split_k < 1) a.split_k = 1;
         }
         // room for the pieces by the shape, not by what this caller happens to bring
-        if (group != 0 && cfg == 0 && a.split_k > 1) a.partial_bytes = partial_bytes_for(M, N, K);
+        if (group != 0 && cfg == 0) a.partial_bytes = partial_bytes_for(M, N, K);
         int chosen = 0, tail_runs = 0;
         const hipError_t e = flexq::launch_gemm(a, cfg, st, &chosen, &tail_runs);
         if (dispatched) *dispatched = chosen * 1000 + (chosen >= 13 ? tail_runs : a.split_k);

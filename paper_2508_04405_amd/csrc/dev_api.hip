@@ -22,9 +22,10 @@ flexq_status flexq_dev_linear(const flexq_dev_tuning *tuning, int act_bits, cons
             tuning->fuse < 0 || tuning->fuse > 2 || tuning->tiles < 0 || tuning->tiles > 2 ||
             tuning->spin < -1 || tuning->spin > (1 << 20))
             return FLEXQ_EINVAL;
-        // 12 .. 17 and 20 are forms for per-channel scales, 18 and 19 for group-128 scales
+        // 12 .. 17 and 20 are forms for per-channel scales, 18, 19 and 22 for group-128 scales
         const int cfg = tuning->gemm_cfg;
-        if (cfg >= 12 && cfg <= 20 && (cfg == 18 || cfg == 19) != (group == 128)) return FLEXQ_EINVAL;
+        if (cfg >= 12 && cfg <= 22 && cfg != 21 && (cfg == 18 || cfg == 19 || cfg == 22) != (group == 128))
+            return FLEXQ_EINVAL;
         t.kernel = tuning->kernel;
         t.split_k = tuning->split_k;
         t.waves = tuning->waves;

@@ -139,6 +139,16 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
 // cut along K into `pieces` (the area must hold low_cut_bytes(their number in all), with `half`
 // half as much).
 hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStream_t st);
+// The same tiles, each in two pieces that meet in the area (group_pair_bytes of it): `first` first
+// pieces, `cut` stages long, a workgroup, `second` second pieces; all zero where they do not fit the chip.
+struct GroupPairs {
+    int first, second, cut;
+    double us;
+};
+GroupPairs group_pairs(int tiles, int KT);
+size_t group_pair_bytes(int tiles);
+bool group_pairs_pay(int M, int N, int K, size_t partial_bytes);
+hipError_t launch_gemm_group_pairs(const LinearArgs &a, hipStream_t st);
 // Which of these forms is taken for `split_k` K splits, as the code that flexq_dev_linear
 // reports: 18, 19 (half height), or 0 for the 128x128 tiles.
 int group_form(int M, int N, int split_k, size_t partial_bytes);

@@ -596,8 +596,13 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
     // out of the AGPR half of the register file (which vector instructions cannot read directly).
     if (a.group != 0) {
         // The sums over the groups are fp32, so where K is cut shows in the last bits.  Every
-        // form cuts it as choose_gemm_split and group_split say, for all rows alike, and adds the pieces in
-        // order: which one runs is a matter of speed alone.
+        // form cuts it as choose_gemm_split, group_split and group_pairs_pay say, for all rows alike, and adds
+        // the pieces in order: which one runs is a matter of speed alone.
+        if (cfg == 22 || (cfg == 0 && a.split_k == 1 && group_pairs_pay(a.M, a.N, a.K, a.partial_bytes))) {
+            *chosen = 22;
+            *tail_runs = group_pairs((a.M + 127) / 128 * ((a.N + 255) / 256), a.K / FLEXQ_TILE_K).cut;
+            return launch_gemm_group_pairs(a, st);
+        }
         int form = cfg == 18 || cfg == 19 ? cfg : 0;
         if (cfg == 0) form = group_form(a.M, a.N, a.split_k, a.partial_bytes);
         if (form != 0) {

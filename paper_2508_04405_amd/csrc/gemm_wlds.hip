@@ -413,6 +413,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     constexpr bool WHOLE = S::BN == 256;
     static_assert(!SK || WHOLE, "the tail is cut in whole-width tiles");
     static_assert((GROUP != 0) == S::GROUPED && !(GROUP && SK == 1), "group scales run group tiles");
+    static_assert(SK != 3 || (GROUP && NT == 1), "pairs of pieces are group tiles");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -429,10 +430,23 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
     int j_next = 0, j_end = 0;                      // !SK: this workgroup's items j_next, j_next + G/8, ...
     long u0 = 0, u1 = 0;                            // SK: this workgroup's run of stages
     int vt = -1;
+    int j_stride = 0, pair_ks = 0, pair_ke = 0;     // SK == 3: this workgroup's stages of every tile of its own
     const long U = (long)item_count * KT;           // SK: 128-k stages of the tail
     if (!SK) {
         j_next = (int)((long)xcd * item_count / 8) + slot;
         j_end = (int)((long)(xcd + 1) * item_count / 8);
+    } else if (SK == 3) {
+        // an XCD's tiles, twice: their first pieces among its first workgroups, `tail_wgs` & 255 each,
+        // their second pieces among the next ones, tail_wgs >> 8 each
+        const int begin = (int)((long)xcd * item_count / 8), end = (int)((long)(xcd + 1) * item_count / 8);
+        const int a1 = tail_wgs & 255, a2 = tail_wgs >> 8;
+        const int n1 = (end - begin + a1 - 1) / a1, n2 = (end - begin + a2 - 1) / a2;
+        const bool first = slot < n1;
+        j_stride = first ? n1 : n2;
+        j_next = begin + (first ? slot : slot - n1);
+        j_end = slot < n1 + n2 ? end : begin;
+        pair_ks = first ? 0 : item_begin;
+        pair_ke = first ? item_begin : KT;
     } else {
         const int per = tail_wgs / 8, rem = tail_wgs % 8;
         if (slot < per + (xcd < rem ? 1 : 0)) vt = xcd * per + min(xcd, rem) + slot;
@@ -453,6 +467,14 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             it.ks = 0;
             it.ke = KT;
             it.tj = 0;
+            return true;
+        } else if (SK == 3) {
+            if (j_next >= j_end) return false;
+            it.t256 = it.tj = j_next;
+            j_next += j_stride;
+            it.half = 0;
+            it.ks = pair_ks;
+            it.ke = pair_ke;
             return true;
         } else {
             if (u0 >= u1) return false;
@@ -999,6 +1021,75 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                 }
             }
             finish = fin_slabs != 0;
+        } else if constexpr (SK == 3) {
+            // PAIRS: every tile in two pieces at the same stage, run at different times.  Whoever is
+            // through first leaves its sums in its own slot and counts; the other, finding the count
+            // or bringing it to two, adds them and finishes the tile.  Nobody waits, and of two
+            // fp32 sums the order shows nowhere.
+            constexpr int kScopeAgent = 16;
+            constexpr int PIECE_BYTES = S::BM * 256 * 4;
+            const __amdgpu_buffer_rsrc_t prsrc = __builtin_amdgcn_make_buffer_rsrc(
+                a.partial, 0, (unsigned)(2 * item_count) * (unsigned)PIECE_BYTES, 0x00020000);
+            int lane_m = lane;
+            asm volatile("" : "+v"(lane_m));
+            const unsigned in_slot = (unsigned)(wave * (PIECE_BYTES / WAVES) + lane_m * 16);
+            const int tj = cur.tj, second = ks != 0 ? 1 : 0;
+            auto broadcast = [&](auto value) {       // thread 0's answer to everybody
+                if (tid == 0) s_last = value();
+                lds_barrier();
+                const bool yes = __builtin_amdgcn_readfirstlane(s_last) != 0;
+                lds_barrier();                       // (read by all before it is written again)
+                return yes;
+            };
+            finish = broadcast([&] {
+                return __hip_atomic_load(&a.counters[tj], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u ? 1 : 0;
+            });
+            if (!finish) {
+                const unsigned mine = (unsigned)(2 * tj + second) * PIECE_BYTES + in_slot;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        v4u piece;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const auto v = acc[mt][0][4 * q + c];
+                            piece[c] = __builtin_bit_cast(unsigned, v);
+                        }
+                        __builtin_amdgcn_raw_buffer_store_b128(piece, prsrc, mine + (unsigned)((mt * 4 + q) * 1024), 0,
+                                                               kScopeAgent);
+                    }
+                wait_vmcnt<0>();                     // acknowledged: visible device-wide
+                lds_barrier();
+                finish = broadcast([&] {
+                    return __hip_atomic_fetch_add(&a.counters[tj], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u
+                               ? 1 : 0;
+                });
+            }
+            if (finish) {
+                if (tid == 0)
+                    __hip_atomic_store(&a.counters[tj], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const unsigned theirs = (unsigned)(2 * tj + 1 - second) * PIECE_BYTES + in_slot;
+                v4u got[2][4];
+                auto load = [&](int mt) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        got[mt & 1][q] = __builtin_amdgcn_raw_buffer_load_b128(
+                            prsrc, theirs + (unsigned)((mt * 4 + q) * 1024), 0, kScopeAgent);
+                };
+                load(0);
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    if (mt + 1 < MT) load(mt + 1);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const unsigned v = got[mt & 1][q][c];
+                            acc[mt][0][4 * q + c] += __uint_as_float(v);
+                        }
+                }
+            }
         } else if constexpr (SK == 1) {
             if (KN != KT) {
                 // [slot][wavefront][block mt, nt][quarter][lane] 16-byte pieces: every store and
@@ -1247,6 +1338,19 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
     if (FORM == 1) run_items<1, 0>(a, lds, s_last, tiles_m, tiles_n, full_count, 2 * tail_count, 0);
     if (FORM == 2) run_items<2, 1>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
     if (FORM == 4) run_items<2, 2>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+}
+
+// Group tiles, every tile (128 rows high) in two pieces, stages [0, cut) and [cut, K / 128): `per_wg` & 255
+// first pieces a workgroup, per_wg >> 8 second pieces.  For layers of one to two rounds of tiles, whose last
+// round would leave most of the chip idle: the two pieces' lengths are such that workgroups of either
+// kind end together.
+template <int GROUP>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gemm_group_pair_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int cut, int per_wg)
+{
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    __shared__ int s_last;
+    run_items<4, 3, GROUP>(a, lds, s_last, tiles_m, tiles_n, cut, tiles_m * tiles_n, per_wg);
 }
 
 // Group tiles (tiles_m counts 128-row tiles): `full_count` whole ones, then `tail_count` of
@@ -1516,6 +1620,70 @@ hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStre
                      : launch_group<1, 5>(a, tiles_m, tiles_n, full, tail, tail * pieces, st);
     return a.sxg ? launch_group<2, 4>(a, tiles_m, tiles_n, full, tail, tail * pieces, st)
                  : launch_group<1, 4>(a, tiles_m, tiles_n, full, tail, tail * pieces, st);
+}
+
+// How pairs of pieces are dealt out: of an XCD's 32 workgroups some run its tiles' first pieces, `first`
+// each, the others its second pieces, `second` each, and the cut is where both take the same time.  A
+// piece costs 8 us beside its stages: first loads, and sums left or collected (128 KiB of them), which
+// nothing overlaps.  (The next piece's first loads ahead of that: no change, 190 us on the layer below.)
+GroupPairs group_pairs(int tiles, int KT)
+{
+    constexpr double kStage = 1.08, kPiece = 8.0;       // us on a full chip
+    GroupPairs best{0, 0, 0, 0.0};
+    const int share = (tiles + 7) / 8;
+    if (KT < 2) return best;
+    for (int f = 1; f <= 4; ++f)
+        for (int s = f; s <= 8; ++s) {
+            if ((share + f - 1) / f + (share + s - 1) / s > kStreamKGrid / 8) continue;
+            int cut = (int)((s * KT * kStage + (s - f) * kPiece) / ((f + s) * kStage) + 0.5);
+            cut = cut < 1 ? 1 : cut > KT - 1 ? KT - 1 : cut;
+            const double t1 = f * (cut * kStage + kPiece), t2 = s * ((KT - cut) * kStage + kPiece);
+            const double t = t1 > t2 ? t1 : t2;
+            if (best.first == 0 || t < best.us) best = GroupPairs{f, s, cut, t};
+        }
+    return best;
+}
+
+size_t group_pair_bytes(int tiles) { return 2 * low_cut_bytes(tiles); }
+
+// Taken for one to two rounds of tiles, where the last round, whole or at half the height, would leave most
+// of the chip idle, and for 5 % of the estimated time: 13824 x 5120 at 2048 tokens (320 tiles) 199 -> 189 us,
+// with both operands' scales 228 -> 214, at 1700 (280) 194 -> 165, at 2560 (400) 238 -> 228, 8192 x 8192 at 1100
+// (288) 120 -> 106, 11008 x 4096 at 2200 157 -> 142; beside the line 8192 x 5120 at 2048 122 / 125, 5120 x 5120 at
+// 2048 82 / 83, 4096 x 11008 at 1024 66 / 72 and 13824 x 5120 at 3000 (480) 253 / 266.  Below 32 stages a piece is
+// mostly its meeting.  (In a whole 13B block at 2048 tokens, whose clock is what the power allows, the down
+// projection takes 182 us instead of 198 and the kernels around it a percent more: 858 against 867.)  A
+// function of the shape alone: the cut shows in the sums' last bits.
+bool group_pairs_pay(int M, int N, int K, size_t partial_bytes)
+{
+    const int tiles = (M + 127) / 128 * ((N + 255) / 256), KT = K / FLEXQ_TILE_K, tail = tiles - kStreamKGrid;
+    if (tail <= 0 || tail >= kStreamKGrid || KT < 32 || device_cu_count() != kStreamKGrid ||
+        group_pair_bytes(tiles) > partial_bytes)
+        return false;
+    const GroupPairs p = group_pairs(tiles, KT);
+    if (p.first == 0) return false;
+    const double round = 1.08 * KT + 6.8;
+    auto busy = [](int n) { return n > 128 ? (n - 128) / 128.0 : 0.0; };
+    const double last = 2 * tail <= kStreamKGrid ? (0.59 + 0.15 * busy(2 * tail)) * KT + 4.4
+                                                 : (0.86 + 0.22 * busy(tail)) * KT + 6.8;
+    return p.us < 0.95 * (round + last);
+}
+
+hipError_t launch_gemm_group_pairs(const LinearArgs &a, hipStream_t st)
+{
+    const int tiles_m = (a.M + 127) / 128, tiles_n = (a.N + 255) / 256, tiles = tiles_m * tiles_n;
+    const GroupPairs p = group_pairs(tiles, a.K / FLEXQ_TILE_K);
+    if (a.group != 128 || p.first == 0 || a.partial_bytes < group_pair_bytes(tiles) || tiles > 2048 ||
+        device_cu_count() != kStreamKGrid)
+        return hipErrorInvalidValue;
+    static std::atomic<unsigned long long> allowed[2];
+    const auto kern = a.sxg ? gemm_group_pair_kernel<2> : gemm_group_pair_kernel<1>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), Shape<4>::LDS_BYTES, allowed[a.sxg != nullptr]);
+        e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(kern, dim3(kStreamKGrid), dim3(64 * WAVES), Shape<4>::LDS_BYTES, st, a, tiles_m, tiles_n, p.cut,
+                       p.first | p.second << 8);
+    return hipGetLastError();
 }
 
 hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hipStream_t st)
