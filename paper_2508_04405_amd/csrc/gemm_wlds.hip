@@ -1275,13 +1275,15 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                     }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // own region only: no barrier
+                // (past the caches, which keep the operand panels: 10240 x 8192 at 1024 tokens 85.5 -> 81.8 us,
+                // 13664 x 5248 at 333 35.6 -> 34.8, large prefill the same within 0.1 %)
 #pragma unroll
                 for (int i = 0; i < 32 / RPI; ++i) {
                     const int row = i * RPI + erow;
                     const v4u piece = *reinterpret_cast<const v4u *>(stg + row * S::ESTRIDE + echunk * 16);
                     if (m_slab + row < M && ecvalid)
                         __builtin_amdgcn_raw_buffer_store_b128(piece, yrsrc, yoff,
-                                                               (unsigned)((mt * 32 + i * RPI) * N * 2), 0);
+                                                               (unsigned)((mt * 32 + i * RPI) * N * 2), kNonTemporal);
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next slab overwrites
             }
