@@ -1464,9 +1464,10 @@ WldsChoice gemm_wlds_choose(int M, int N, int K, bool may_cut)
 // full chip -- 30 % more for the same work than a 256x256 tile's, which pays for itself where
 // that would leave CUs idle.  Fitted on eighteen layers (512 .. 57344 wide, 512 .. 28672 deep)
 // at 129 .. 2048 tokens; taken there it gains 5 to 45 % between 129 and 700 tokens (8192 x
-// 8192 at 300 tokens: 44.5 -> 34.9 us, 4096 x 4096 at 220: 23.8 -> 16.4).  The meeting of more than 192
-// pieces is priced too dear: 15360 x 5120 at 129 .. 256 tokens stays whole at 31 to 32 us, two pieces per tile
-// take 26 to 29.
+// 8192 at 300 tokens: 44.5 -> 34.9 us, 4096 x 4096 at 220: 23.8 -> 16.4).  More than 192 pieces meet at
+// little more than fewer do (15360 x 5120 at 129 .. 256 tokens, 240 pieces against 120 whole tiles: 26.7 .. 27.9
+// us against 32.8; 16384 x 6144 at 129, 256 pieces: 30.6 against 35.7), but not for one more piece a tile alone
+// (13824 x 5120 at 150: 160 pieces 29.1, 200 31.5).
 WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes)
 {
     const int tiles = ((M + 127) / 128) * ((N + 255) / 256), KT = K / FLEXQ_TILE_K;
@@ -1478,7 +1479,7 @@ WldsChoice gemm_low_choose(int M, int N, int K, size_t partial_bytes)
     for (int S = 2; S <= 16 && tail * S <= kStreamKGrid && S <= KT; ++S) {
         const int wgs = tail * S;
         if (partial_bytes < low_cut_bytes(wgs)) break;
-        const double meet = 3.0 + 0.4 * S + 0.015 * wgs + (wgs > 192 ? 0.05 * (wgs - 192) : 0.0);
+        const double meet = 3.0 + 0.4 * S + 0.015 * wgs + (wgs > 192 ? 0.5 + 0.015 * (wgs - 192) : 0.0);
         const double t = rounds + stage_us(wgs) * ((KT + S - 1) / S) + 4.0 + meet;
         if (t < best.us) best = WldsChoice{t, 5, wgs};
     }
@@ -1653,13 +1654,12 @@ GroupPairs group_pairs(int tiles, int KT)
 size_t group_pair_bytes(int tiles) { return 2 * low_cut_bytes(tiles); }
 
 // Taken for one to two rounds of tiles, where the last round, whole or at half the height, would leave most
-// of the chip idle, and for 5 % of the estimated time: 13824 x 5120 at 2048 tokens (320 tiles) 199 -> 189 us,
-// with both operands' scales 228 -> 214, at 1700 (280) 194 -> 165, at 2560 (400) 238 -> 228, 8192 x 8192 at 1100
-// (288) 120 -> 106, 11008 x 4096 at 2200 157 -> 142; beside the line 8192 x 5120 at 2048 122 / 125, 5120 x 5120 at
-// 2048 82 / 83, 4096 x 11008 at 1024 66 / 72 and 13824 x 5120 at 3000 (480) 253 / 266.  Below 32 stages a piece is
-// mostly its meeting.  (In a whole 13B block at 2048 tokens, whose clock is what the power allows, the down
-// projection takes 182 us instead of 198 and the kernels around it a percent more: 858 against 867.)  A
-// function of the shape alone: the cut shows in the sums' last bits.
+// of the chip idle, and for 10 % of the estimated time: 13824 x 5120 at 1700 tokens (280 tiles) 195 -> 165 us, with
+// both operands' scales 225 -> 187, 8192 x 8192 at 1100 (288) 119 -> 106, 11008 x 4096 at 2200 157 -> 138.  Beside
+// the line 13824 x 5120 at 2048 (320) 198 / 188 alone, but nothing in a whole 13B block, where the clock is what
+// the power allows (868 / 870 us), at 2300 207 / 204, 5120 x 5120 at 1900 79 / 77, 8192 x 5120 at 2048 122 / 125,
+// 13824 x 5120 at 3000 (480) 253 / 266.  Below 32 stages a piece is mostly its meeting (4096 x 11008 at 1024
+// 66 / 72).  A function of the shape alone: the cut shows in the sums' last bits.
 bool group_pairs_pay(int M, int N, int K, size_t partial_bytes)
 {
     const int tiles = (M + 127) / 128 * ((N + 255) / 256), KT = K / FLEXQ_TILE_K, tail = tiles - kStreamKGrid;
@@ -1672,7 +1672,7 @@ bool group_pairs_pay(int M, int N, int K, size_t partial_bytes)
     auto busy = [](int n) { return n > 128 ? (n - 128) / 128.0 : 0.0; };
     const double last = 2 * tail <= kStreamKGrid ? (0.59 + 0.15 * busy(2 * tail)) * KT + 4.4
                                                  : (0.86 + 0.22 * busy(tail)) * KT + 6.8;
-    return p.us < 0.95 * (round + last);
+    return p.us < 0.90 * (round + last);
 }
 
 hipError_t launch_gemm_group_pairs(const LinearArgs &a, hipStream_t st)
