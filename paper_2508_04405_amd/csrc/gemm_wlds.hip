@@ -871,10 +871,20 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             const int me = vt - tj * pieces;
             unsigned *flags = a.counters + 2048;
             auto owner = [&](int mt) { return (wave * MT + mt) % pieces; };      // uniform
-            // slabs of padding tokens alone are neither sent nor added: 28672 x 8192 at 140 tokens 66.1 -> 64.2
-            // us, at 333 101.5 -> 97.8, at 70 52 -> 50.4, 10240 x 8192 at 160 34.1 -> 32.5 (group tiles pad by less
-            // and gain nothing)
-            auto live = [&](int mt) { return GROUP || at.bm0 + (wm * MT + mt) * 32 < M; };
+            // Slabs of padding tokens alone are not added, and on 256-row tiles and in a single row of low tiles
+            // not sent either: 28672 x 8192 at 140 tokens 66.1 -> 64.2 us, at 333 101.5 -> 97.8, 10240 x 8192 at 160
+            // 34.1 -> 32.5, 16384 x 6144 at 66 (low) 30.9 -> 29.8.  Several rows of low tiles send them all the same:
+            // without, 14336 x 4096 at 200 tokens takes 30.6 us instead of 28.4, 11008 x 4096 at 150 26.4 / 25.0, 4096 x
+            // 4096 at 180 18.2 / 16.7 (why is not known: dealing the slabs that are left evenly to the
+            // pieces changes nothing), and left out of the additions alone they cost nothing on any of 315 cells.
+            auto live = [&](int mt) {
+                if constexpr (GROUP != 0) return true;      // (those pad by less and gain nothing)
+                else return at.bm0 + (wm * MT + mt) * 32 < M;
+            };
+            auto sent = [&](int mt) {
+                if constexpr (TILE == 2 || GROUP != 0) return live(mt);
+                else return tiles_m > 1 || live(mt);
+            };
             auto store_slab = [&](int mt) {
                 const unsigned mine = (unsigned)vt * PIECE_BYTES + in_slot;
 #pragma unroll
@@ -955,7 +965,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             };
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                if (owner(mt) != me && live(mt)) store_slab(mt);
+                if (owner(mt) != me && sent(mt)) store_slab(mt);
             wait_vmcnt<0>();
             lds_barrier();
             if (tid == 0) {
@@ -977,7 +987,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             if (state == 0) {
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    if (owner(mt) == me && live(mt)) store_slab(mt);
+                    if (owner(mt) == me && sent(mt)) store_slab(mt);
                 wait_vmcnt<0>();
                 lds_barrier();
                 if (tid == 0) {

@@ -13,7 +13,7 @@ from gpu_helpers import assert_y_close, prepare, say, to_dev
 pytestmark = pytest.mark.gpu
 
 
-def check(M, K, N, dispatch, want, spin=0):
+def check(M, K, N, dispatch, want, spin=0, stale=None):
     w = synth.weights(N, K, 0.02, seed=K)
     x = synth.activations(M, K, seed=M, outlier_frac=0.02)
     packed, _, _ = prepare(w)
@@ -23,6 +23,8 @@ def check(M, K, N, dispatch, want, spin=0):
     dev.set_spin(spin)
     try:
         for _ in range(2):
+            if stale is not None:
+                ws[16384:].fill_(stale)
             y, acc = dev.gemm_w6a6(packed, N, K, x_fp16=to_dev(x), workspace=ws, want_acc=True)
             assert dev.last_dispatch() == want
             assert np.array_equal(acc.cpu().numpy().astype(np.int64), ref["acc"])
@@ -39,6 +41,19 @@ def check(M, K, N, dispatch, want, spin=0):
 def test_round_then_cut(M, K, N, pieces, tail, spin):
     say(f"low tiles, a round then {tail} cut into {pieces}: M={M} K={K} N={N} spin={spin}")
     check(M, K, N, (2, pieces, 0, 16), (16, tail * pieces), spin)
+
+
+# One and several rows of low tiles and of 256-row tiles, one to all of the last row's slabs padding: what the
+# area for the partial sums held before, sums of a larger call say, is nowhere added.
+@pytest.mark.parametrize("spin", [0, -1])
+@pytest.mark.parametrize("cfg,M,K,N,pieces", [
+    (16, 1, 256, 288, 2), (16, 66, 640, 544, 5), (16, 96, 384, 256, 3), (16, 129, 512, 544, 4), (16, 161, 896, 288, 7),
+    (16, 225, 1408, 256, 11), (16, 300, 2048, 32, 16), (13, 129, 640, 288, 5), (13, 300, 384, 544, 3)])
+def test_padding_slabs(cfg, M, K, N, pieces, spin):
+    say(f"padding slabs: form {cfg} M={M} K={K} N={N} pieces={pieces} spin={spin}")
+    rows = 128 if cfg == 16 else 256
+    wgs = (M + rows - 1) // rows * ((N + 255) // 256) * pieces
+    check(M, K, N, (2, pieces, 0, cfg), (cfg, wgs), spin, stale=0x5b)
 
 
 @pytest.mark.parametrize("M,K,N,want", [(129, 2048, 2048, 16), (300, 4096, 1056, 16), (600, 4096, 12288, 15)])
