@@ -90,6 +90,15 @@
 namespace {
 
 constexpr int WAVES = 8;
+// The outputs' stores in the last round of a launch go past the caches, those of the rounds before it do
+// not.  Nothing follows the last round, and the lines that it leaves in the caches are written back while the
+// chip waits: layers of K -> N 1536 -> 8960 at 1024 tokens 22.2 -> 20.4 us, 3584 -> 18944 at 300 28.1 -> 26.7, 8192 ->
+// 10240 at 1024 83.0 -> 81.6, 4096 -> 12288 at 333 with group scales 34.6 -> 33.9; of 500 cells of one round none is
+// slower by more than the 2 % that runs differ.  Before that a workgroup waits for its stores together with
+// its next item's first loads, and past the caches they take longer: 4096 -> 22016 at 1024 tokens with
+// group scales 126 / 129 us, 5120 -> 27648 with both operands' 215 / 220, 5248 -> 13664 at 1300 (a round and half
+// tiles) 102.6 / 104.5, a 13B block with group scales at 2048 845 / 858 (by this rule 847).
+constexpr int kLastRound = kNonTemporal;
 constexpr int SLOT_BYTES = 256 * 256 * 4;      // one workgroup's int32 sums of a 256x256 tile
 
 // The eight wavefronts share a whole tile 2 along m x 4 along n, 128 x 64 each (MT = 4 row
@@ -402,8 +411,9 @@ __device__ __forceinline__ void group_item(v16f (&facc)[Shape<TILE>::MT][1], uin
 // or, with SK, the stages of `item_count` tiles cut into `tail_wgs` runs.
 // GROUP (group tiles only): 1 = weight scales per 128-k group, one scale per token; 2 = both
 // operands' scales per group.
-// WPOLICY: cache policy of the weights' DMA loads (per-channel scales).
-template <int TILE, int SK, int GROUP = 0, int WPOLICY = 0>
+// YPOLICY, WPOLICY: cache policies of the outputs' stores and of the weights' DMA loads (the latter
+// with per-channel scales).
+template <int TILE, int SK, int GROUP = 0, int YPOLICY = 0, int WPOLICY = 0>
 __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *lds, int &s_last, int tiles_m,
                                           int tiles_n, int item_begin, int item_count, int tail_wgs)
 {
@@ -872,10 +882,10 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             unsigned *flags = a.counters + 2048;
             auto owner = [&](int mt) { return (wave * MT + mt) % pieces; };      // uniform
             // Slabs of padding tokens alone are not added, and on 256-row tiles and in a single row of low tiles
-            // not sent either: 28672 x 8192 at 140 tokens 66.1 -> 64.2 us, at 333 101.5 -> 97.8, 10240 x 8192 at 160
-            // 34.1 -> 32.5, 16384 x 6144 at 66 (low) 30.9 -> 29.8.  Several rows of low tiles send them all the same:
-            // without, 14336 x 4096 at 200 tokens takes 30.6 us instead of 28.4, 11008 x 4096 at 150 26.4 / 25.0, 4096 x
-            // 4096 at 180 18.2 / 16.7 (why is not known: dealing the slabs that are left evenly to the
+            // not sent either: layers of K -> N 28672 -> 8192 at 140 tokens 66.1 -> 64.2 us, at 333 101.5 -> 97.8, 8192 ->
+            // 10240 at 160 34.1 -> 32.5, 16384 -> 6144 at 66 (low) 30.9 -> 29.8.  Several rows of low tiles send them all
+            // the same: without, 14336 -> 4096 at 200 tokens takes 30.6 us instead of 28.4, 11008 -> 4096 at 150 26.4 /
+            // 25.0, 4096 -> 4096 at 180 18.2 / 16.7 (why is not known: dealing the slabs that are left evenly to the
             // pieces changes nothing), and left out of the additions alone they cost nothing on any of 315 cells.
             auto live = [&](int mt) {
                 if constexpr (GROUP != 0) return true;      // (those pad by less and gain nothing)
@@ -1285,15 +1295,13 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
                     }
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // own region only: no barrier
-                // (past the caches, which keep the operand panels: 10240 x 8192 at 1024 tokens 85.5 -> 81.8 us,
-                // 13664 x 5248 at 333 35.6 -> 34.8, large prefill the same within 0.1 %)
 #pragma unroll
                 for (int i = 0; i < 32 / RPI; ++i) {
                     const int row = i * RPI + erow;
                     const v4u piece = *reinterpret_cast<const v4u *>(stg + row * S::ESTRIDE + echunk * 16);
                     if (m_slab + row < M && ecvalid)
                         __builtin_amdgcn_raw_buffer_store_b128(piece, yrsrc, yoff,
-                                                               (unsigned)((mt * 32 + i * RPI) * N * 2), kNonTemporal);
+                                                               (unsigned)((mt * 32 + i * RPI) * N * 2), YPOLICY);
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next slab overwrites
             }
@@ -1308,6 +1316,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 #endif
 }
 
+// ONE_ROUND: no workgroup has more than one item.
 // FORM 3: `full_count` low tiles (tiles_m counts 128-row tiles) and nothing else.  FORM 6: the
 // same with 192-row tiles.  FORM 5:
 // `full_count` low tiles, then `tail_count`, each cut along K into tail_wgs / tail_count pieces.
@@ -1316,23 +1325,24 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
 // across tile borders.  FORM 4: then those tiles each cut into tail_wgs / tail_count pieces.
 // One launch: a second launch for the tail would cost the first one's drain and the
 // end-of-kernel cache write-back in between (about 20 us, measured).
-template <int FORM>
+template <int FORM, bool ONE_ROUND = false>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_count, int tail_count,
                       int tail_wgs)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     __shared__ int s_last;
+    constexpr int YPOLICY = ONE_ROUND ? kLastRound : 0;
     if (FORM == 3) {   // every item a low tile (128 x 256)
-        run_items<3, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+        run_items<3, 0, 0, YPOLICY>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
     }
     if (FORM == 7) {   // the same for one row of tiles, which uses a weight once
-        run_items<3, 0, 0, kNonTemporal>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+        run_items<3, 0, 0, YPOLICY, kNonTemporal>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
     }
     if (FORM == 6) {   // every item a tile of 192 x 256
-        run_items<6, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+        run_items<6, 0, 0, YPOLICY>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
         return;
     }
     if (FORM == 5) {   // whole rounds of low tiles, then the rest cut evenly along K
@@ -1342,18 +1352,21 @@ void gemm_wlds_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_co
             lds_barrier();     // as below: the last epilogue's staging rows
 #endif
         }
-        run_items<3, 2>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+        run_items<3, 2, 0, kLastRound>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
         return;
     }
-    if (full_count > 0) run_items<2, 0>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+    if (full_count > 0) run_items<2, 0, 0, YPOLICY>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
 #if defined(__HIP_DEVICE_COMPILE__)
     // The two phases lay LDS out differently: every wavefront must be through with its last
     // epilogue's staging rows before anyone's first loads of the next phase land on them.
     if (FORM != 0) lds_barrier();
 #endif
-    if (FORM == 1) run_items<1, 0>(a, lds, s_last, tiles_m, tiles_n, full_count, 2 * tail_count, 0);
-    if (FORM == 2) run_items<2, 1>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
-    if (FORM == 4) run_items<2, 2>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+    if (FORM == 1)
+        run_items<1, 0, 0, kLastRound>(a, lds, s_last, tiles_m, tiles_n, full_count, 2 * tail_count, 0);
+    if (FORM == 2)
+        run_items<2, 1, 0, kLastRound>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+    if (FORM == 4)
+        run_items<2, 2, 0, kLastRound>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
 }
 
 // Group tiles, every tile (128 rows high) in two pieces, stages [0, cut) and [cut, K / 128): `per_wg` & 255
@@ -1366,28 +1379,32 @@ void gemm_group_pair_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int c
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     __shared__ int s_last;
-    run_items<4, 3, GROUP>(a, lds, s_last, tiles_m, tiles_n, cut, tiles_m * tiles_n, per_wg);
+    run_items<4, 3, GROUP, kLastRound>(a, lds, s_last, tiles_m, tiles_n, cut, tiles_m * tiles_n, per_wg);
 }
 
 // Group tiles (tiles_m counts 128-row tiles): `full_count` whole ones, then `tail_count` of
 // shape TAIL: as many of the same (4), or those that follow at half the height (5).  Each of them
-// is cut into tail_wgs / tail_count pieces.
+// is cut into tail_wgs / tail_count pieces.  TAIL 0: one round of whole ones.
 template <int GROUP, int TAIL>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_group_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n, int full_count, int tail_count, int tail_wgs)
 {
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     __shared__ int s_last;
+    if constexpr (TAIL == 0) {
+        run_items<4, 0, GROUP, kLastRound>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
+        return;
+    }
     if (full_count > 0) run_items<4, 0, GROUP>(a, lds, s_last, tiles_m, tiles_n, 0, full_count, 0);
     if (tail_count == 0) return;
 #if defined(__HIP_DEVICE_COMPILE__)
     lds_barrier();     // the last epilogue's staging rows, as above
 #endif
     if constexpr (TAIL == 5)   // tile t is tiles 2 t and 2 t + 1 of half the height, in the same super-block order
-        run_items<5, 2, GROUP>(a, lds, s_last, full_count > 0 ? 2 * tiles_m : (a.M + 63) / 64, tiles_n, 2 * full_count,
-                               tail_count, tail_wgs);
-    else
-        run_items<4, 2, GROUP>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
+        run_items<5, 2, GROUP, kLastRound>(a, lds, s_last, full_count > 0 ? 2 * tiles_m : (a.M + 63) / 64, tiles_n,
+                                           2 * full_count, tail_count, tail_wgs);
+    if constexpr (TAIL == 4)
+        run_items<4, 2, GROUP, kLastRound>(a, lds, s_last, tiles_m, tiles_n, full_count, tail_count, tail_wgs);
 }
 
 }  // namespace
@@ -1512,11 +1529,11 @@ namespace {
 constexpr int kLdsMax(int a, int b) { return a > b ? a : b; }
 constexpr int kLdsBytes = kLdsMax(Shape<2>::LDS_BYTES, kLdsMax(Shape<1>::LDS_BYTES, Shape<3>::LDS_BYTES));
 
-template <int FORM>
+template <int FORM, bool ONE_ROUND = false>
 hipError_t launch_form(const LinearArgs &a, int tiles_m, int tiles_n, int full_count, int tail_count,
                        int tail_wgs, int grid, hipStream_t st)
 {
-    auto kern = gemm_wlds_kernel<FORM>;
+    auto kern = gemm_wlds_kernel<FORM, ONE_ROUND>;
     static std::atomic<unsigned long long> lds_allowed{0};
     constexpr int lds_bytes = FORM == 6 ? Shape<6>::LDS_BYTES : kLdsBytes;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds_bytes, lds_allowed);
@@ -1526,6 +1543,9 @@ hipError_t launch_form(const LinearArgs &a, int tiles_m, int tiles_n, int full_c
                        full_count, tail_count, tail_wgs);
     return hipGetLastError();
 }
+
+// every workgroup has one item at most
+bool one_round(int items) { return items <= kStreamKGrid; }
 
 // workgroups for `items` items: a multiple of 8 (one share per XCD), at most one per CU
 // on the 256-CU device the persistent forms are laid out for, else one per item
@@ -1539,7 +1559,7 @@ template <int GROUP, int TAIL>
 hipError_t launch_group(const LinearArgs &a, int tiles_m, int tiles_n, int full, int tail, int tail_wgs, hipStream_t st)
 {
     auto kern = gemm_group_kernel<GROUP, TAIL>;
-    constexpr int lds_bytes = kLdsMax(Shape<4>::LDS_BYTES, Shape<TAIL>::LDS_BYTES);
+    constexpr int lds_bytes = kLdsMax(Shape<4>::LDS_BYTES, Shape<TAIL == 0 ? 4 : TAIL>::LDS_BYTES);
     static std::atomic<unsigned long long> lds_allowed{0};
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds_bytes, lds_allowed);
         e != hipSuccess)
@@ -1625,6 +1645,9 @@ hipError_t launch_gemm_group(const LinearArgs &a, bool half, int pieces, hipStre
     const int full = tiles - tail;
     if (pieces < 1) pieces = 1;
     if (half) tail = full ? 2 * tail : (a.M + 63) / 64 * tiles_n;
+    if ((tail == 0 || (pieces == 1 && !half)) && tiles <= kStreamKGrid)
+        return a.sxg ? launch_group<2, 0>(a, tiles_m, tiles_n, tiles, 0, 0, st)
+                     : launch_group<1, 0>(a, tiles_m, tiles_n, tiles, 0, 0, st);
     if (tail == 0 || (pieces == 1 && !half))
         return a.sxg ? launch_group<2, 4>(a, tiles_m, tiles_n, tiles, 0, 0, st)
                      : launch_group<1, 4>(a, tiles_m, tiles_n, tiles, 0, 0, st);
@@ -1712,12 +1735,15 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
         // 128, 45056 x 4096 at 50 30.8 / 31.7.  (Cut along K, 28672 x 8192 at 97, it makes no difference
         // from HBM, 57.5 / 58, and costs 8 % where the Infinity Cache holds the weights.  A branch in the
         // shared kernel costs 333 tokens of 13664 x 5248 3 %: a kernel of its own.)
-        return low_m == 1 ? launch_form<7>(a, low_m, cols, cols, 0, 0, grid_for(cols), st)
-                          : launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
+        if (low_m == 1 && one_round(cols)) return launch_form<7, true>(a, low_m, cols, cols, 0, 0, grid_for(cols), st);
+        if (one_round(low_m * cols))
+            return launch_form<3, true>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
+        return launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
     }
     if (tail_form == 6) {   // 192-row tiles throughout
         const int rows = (a.M + 191) / 192, cols = (a.N + 255) / 256;
-        return launch_form<6>(a, rows, cols, rows * cols, 0, 0, grid_for(rows * cols), st);
+        return one_round(rows * cols) ? launch_form<6, true>(a, rows, cols, rows * cols, 0, 0, grid_for(rows * cols), st)
+                                      : launch_form<6>(a, rows, cols, rows * cols, 0, 0, grid_for(rows * cols), st);
     }
     if (tail_form == 5) {   // low tiles, those beyond the last whole round cut into equal pieces
         const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256, all = low_m * cols;
@@ -1738,7 +1764,8 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
                            device_cu_count() != kStreamKGrid))
         tail_form = 0;
     if (tail_form == 0 || p.tail_tiles == 0)      // every tile whole
-        return launch_form<0>(a, tiles_m, tiles_n, p.tiles, 0, 0, grid_for(p.tiles), st);
+        return one_round(p.tiles) ? launch_form<0, true>(a, tiles_m, tiles_n, p.tiles, 0, 0, grid_for(p.tiles), st)
+                                  : launch_form<0>(a, tiles_m, tiles_n, p.tiles, 0, 0, grid_for(p.tiles), st);
     // the whole rounds first, then the tiles of the last, partial round in their own form
     const int g_full = p.full_tiles ? grid_for(p.full_tiles) : 0;
     if (tail_form == 1) {

@@ -146,11 +146,11 @@ def test_scales_that_are_not_finite(cfg, both):
     assert np.allclose(got[fine], want[fine], rtol=2e-3, atol=2e-3)
 
 
-# more than a round of 128-row tiles: several items per workgroup, then the 14 (8) behind the round,
+# exactly a round of 128-row tiles; more: several items per workgroup, then the 14 (8) behind the round,
 # whole or cut, 128 rows high (18) or 64 (19), at one to five stages and unequal pieces
 @pytest.mark.parametrize("both,spin", [(False, 0), (False, -1), (True, 0), (True, -1)])
 @pytest.mark.parametrize("M,K,N,cfg,pieces", [
-    (1029, 128, 7680, 18, 1), (1029, 256, 7680, 18, 2), (1029, 640, 7456, 18, 3), (33 * 128, 384, 1824, 18, 3),
+    (1024, 256, 8192, 18, 1), (1029, 128, 7680, 18, 1), (1029, 256, 7680, 18, 2), (1029, 640, 7456, 18, 3), (33 * 128, 384, 1824, 18, 3),
     (1029, 128, 7680, 19, 1), (1029, 256, 7456, 19, 1), (1029, 640, 7456, 19, 4), (33 * 128, 384, 1824, 19, 2)])
 def test_rounds_then_a_tail(M, K, N, cfg, pieces, both, spin):
     say(f"group tiles, a round and a tail: form {cfg} M={M} K={K} N={N} pieces={pieces} both={both} spin={spin}")

@@ -43,6 +43,13 @@ def test_round_then_cut(M, K, N, pieces, tail, spin):
     check(M, K, N, (2, pieces, 0, 16), (16, tail * pieces), spin)
 
 
+# 256 items, one for every workgroup, and 288: 256-row tiles, low ones, 192-row ones
+@pytest.mark.parametrize("cfg,M", [(12, 2048), (12, 2049), (15, 1024), (15, 1025), (20, 1536), (20, 1537)])
+def test_one_round_and_more(cfg, M):
+    say(f"one round of tiles and more: form {cfg} M={M}")
+    check(M, 128, 8192, (2, 0, 0, cfg), (cfg, 1 if cfg == 12 else 0))
+
+
 # One and several rows of low tiles and of 256-row tiles, one to all of the last row's slabs padding: what the
 # area for the partial sums held before, sums of a larger call say, is nowhere added.
 @pytest.mark.parametrize("spin", [0, -1])
