@@ -171,10 +171,6 @@ void gemm_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n)
                 for (int r = 0; r < 16; ++r) facc[GROUP ? mt : 0][GROUP ? nt : 0][r] = 0.0f;
     }
 
-    // The 64-row tiles serve up to 64 tokens, one row of tiles: every weight is used once (past
-    // the caches 10240 x 8192 at 40 tokens takes 21.3 us instead of 22.1, 8192 x 28672 at 64 44.5 / 45.5,
-    // 22016 x 4096 at 48 22.4 / 23.2).  Higher tiles share their weights with the rows below.
-    constexpr int WPOLICY = BM == 64 ? kNonTemporal : 0;
     PackedTile wreg[3][NT];
     uint16_t gsreg[3][NT];
     auto load_w = [&](int kb, auto buf_tag) {
@@ -182,9 +178,9 @@ void gemm_kernel(flexq::LinearArgs a, int tiles_m, int tiles_n)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const unsigned soff = (unsigned)(wnb[nt] * KT + kb0 + kb) * FLEXQ_TILE_BYTES;
-            wreg[B][nt].q0 = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane, soff, WPOLICY);
-            wreg[B][nt].q1 = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane, soff + 1024, WPOLICY);
-            wreg[B][nt].q2 = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane, soff + 2048, WPOLICY);
+            wreg[B][nt].q0 = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane, soff, 0);
+            wreg[B][nt].q1 = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane, soff + 1024, 0);
+            wreg[B][nt].q2 = (v4i)__builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane, soff + 2048, 0);
             if (GROUP) gsreg[B][nt] = a.scales[((long)wnb[nt] * KT + kb0 + kb) * 32 + (lane & 31)];
         }
     };

@@ -1730,12 +1730,17 @@ hipError_t launch_gemm_wlds(const LinearArgs &a, int tail_form, int tail_wgs, hi
     if (a.group != 0 || a.split_k > 1 || a.sxg) return hipErrorInvalidValue;
     if (tail_form == 3) {   // low tiles throughout
         const int low_m = (a.M + 127) / 128, cols = (a.N + 255) / 256;
-        // One row of tiles, up to 128 tokens on wide layers, uses a weight once: past the caches 57344 x
-        // 8192 takes 64.5 us instead of 68.3 at 33 tokens, 67 / 72.5 at 64, 71 / 75.6 at 100, 75.5 / 78.7 at
-        // 128, 45056 x 4096 at 50 30.8 / 31.7.  (Cut along K, 28672 x 8192 at 97, it makes no difference
-        // from HBM, 57.5 / 58, and costs 8 % where the Infinity Cache holds the weights.  A branch in the
-        // shared kernel costs 333 tokens of 13664 x 5248 3 %: a kernel of its own.)
-        if (low_m == 1 && one_round(cols)) return launch_form<7, true>(a, low_m, cols, cols, 0, 0, grid_for(cols), st);
+        // One row of tiles, up to 128 tokens on wide layers, uses a weight once: past the caches if the layer is
+        // more than the Infinity Cache (256 MiB) holds from one call to the next.  K -> N 8192 -> 57344 (352 MB) at
+        // 33 / 64 / 100 / 128 tokens 66 -> 64.5 us, 69.4 / 68.6, 74.9 / 74.5, 78.3 / 77; one layer called again and
+        // again, 5760 -> 65536 (283 MB) at 64 52 / 49.8, but 5504 -> 65536 (271 MB) 46.6 / 47.9, 4096 -> 65536 (201 MB)
+        // 34.6 / 43.6.  (Smaller layers gain 4 % among others that evict them and lose up to 26 % where they
+        // stay; so do the 64-row tiles, of which those with six K splits or more lose up to 11 % either way.
+        // Cut along K, 28672 -> 8192 at 97, it makes no difference from HBM, 57.5 / 58.  A kernel of its own: a branch in
+        // the shared one costs 5248 -> 13664 at 333 tokens 3 %.)
+        constexpr long kBeyondCaches = 280L * 1000 * 1000;
+        if (low_m == 1 && one_round(cols) && (long)a.N * a.K / 4 * 3 > kBeyondCaches)
+            return launch_form<7, true>(a, low_m, cols, cols, 0, 0, grid_for(cols), st);
         if (one_round(low_m * cols))
             return launch_form<3, true>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);
         return launch_form<3>(a, low_m, cols, low_m * cols, 0, 0, grid_for(low_m * cols), st);

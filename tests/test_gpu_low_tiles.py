@@ -63,7 +63,7 @@ def test_padding_slabs(cfg, M, K, N, pieces, spin):
     check(M, K, N, (2, pieces, 0, cfg), (cfg, wgs), spin, stale=0x5b)
 
 
-@pytest.mark.parametrize("M,K,N,want", [(129, 2048, 2048, 16), (300, 4096, 1056, 16), (600, 4096, 12288, 15)])
+@pytest.mark.parametrize("M,K,N,want", [(129, 2048, 2048, 16), (300, 4096, 1056, 16), (600, 4096, 12288, 15), (100, 512, 40960, 15)])
 def test_own_choice(M, K, N, want):
     say(f"low tiles by choice: M={M} K={K} N={N}")
     dev.gemm_w6a6(torch.zeros(fq.packed_bytes(N, K), dtype=torch.uint8, device="cuda"), N, K,
