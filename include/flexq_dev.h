@@ -75,7 +75,8 @@ typedef struct {
  * per cut tile; for 22: the first piece's stages; 500 more
  * when the streaming kernel read its activations in tile order).  Results are the same
  * whatever the overrides, but for group-128 scales, whose fp32 sums round by where K is cut:
- * there the same bits go with the same K splits.
+ * there the same bits go with the same K splits, and 22, whose two pieces meet at a stage of its
+ * own, has bits of its own.  With gemm_cfg 0, split_k = 1 excludes it.
  */
 flexq_status flexq_dev_linear(const flexq_dev_tuning *tuning, int act_bits, const void *packed,
                               int group, const int8_t *xq, const uint16_t *sx,

@@ -384,6 +384,11 @@ flexq_status linear_impl(const Tuning &tune, int act_bits, const void *packed, i
         }
         // room for the pieces by the shape, not by what this caller happens to bring
         if (group != 0 && cfg == 0) a.partial_bytes = partial_bytes_for(M, N, K);
+        // a forced single split is honoured as well: not the pairs of pieces
+        if (group != 0 && cfg == 0 && tune.split_k == 1) {
+            cfg = flexq::group_form(M, N, 1, a.partial_bytes);
+            if (cfg == 0) cfg = 8;
+        }
         int chosen = 0, tail_runs = 0;
         const hipError_t e = flexq::launch_gemm(a, cfg, st, &chosen, &tail_runs);
         if (dispatched) *dispatched = chosen * 1000 + (chosen >= 13 ? tail_runs : a.split_k);

@@ -591,9 +591,10 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
     // is bound by the vector unit.  128x128 tiles with two workgroups per CU keep the int32 sums
     // out of the AGPR half of the register file (which vector instructions cannot read directly).
     if (a.group != 0) {
-        // The sums over the groups are fp32, so where K is cut shows in the last bits.  Every
-        // form cuts it as choose_gemm_split, group_split and group_pairs_pay say, for all rows alike, and adds
-        // the pieces in order: which one runs is a matter of speed alone.
+        // The sums over the groups are fp32, so where K is cut shows in the last bits.  By the library's choice
+        // it is a function of the shape, for all rows alike: where group_pairs_pay holds, two pieces cut at
+        // group_pairs().cut, which form 22 alone runs; else as choose_gemm_split and group_split say, the
+        // pieces added in order, and which of the other forms runs is a matter of speed alone.
         if (cfg == 22 || (cfg == 0 && a.split_k == 1 && group_pairs_pay(a.M, a.N, a.K, a.partial_bytes))) {
             *chosen = 22;
             *tail_runs = group_pairs((a.M + 127) / 128 * ((a.N + 255) / 256), a.K / FLEXQ_TILE_K).cut;

@@ -57,11 +57,18 @@ def test_choice_and_equal_tokens(M, K, N, pairs, both):
     assert (dev.last_dispatch()[0] == 22) == pairs
     assert np.array_equal(call(packed, N, K, codes, both, 8, roomy).view(np.uint16), y.view(np.uint16))
     assert np.array_equal(y[:M // 2].view(np.uint16), y[M // 2:].view(np.uint16))
+    # one K split asked for: no form cuts K, and all that do not agree
     dev.set_dispatch(2, 1, 0, 18)
     try:
-        whole = call(packed, N, K, codes, both, 8, exact).astype(np.float64)
+        whole = call(packed, N, K, codes, both, 8, exact)
+        dev.set_dispatch(2, 1)
+        forced = call(packed, N, K, codes, both, 8, exact)
+        assert dev.last_dispatch() in ((18, 1), (19, 1))
     finally:
         dev.set_dispatch()
+    assert np.array_equal(forced.view(np.uint16), whole.view(np.uint16))
+    assert pairs or np.array_equal(y.view(np.uint16), whole.view(np.uint16))
+    whole = whole.astype(np.float64)
     # the same terms in one chain and in two: fp32 sums of K / 128 terms, then one rounding to fp16.
     # Relative to the output's spread the chains differ by far less than fp16's 2^-11.
     d = np.abs(y.astype(np.float64) - whole)
