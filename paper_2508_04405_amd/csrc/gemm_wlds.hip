@@ -1687,12 +1687,14 @@ GroupPairs group_pairs(int tiles, int KT)
 size_t group_pair_bytes(int tiles) { return 2 * low_cut_bytes(tiles); }
 
 // Taken for one to two rounds of tiles, where the last round, whole or at half the height, would leave most
-// of the chip idle, and for 10 % of the estimated time: 13824 x 5120 at 1700 tokens (280 tiles) 195 -> 165 us, with
-// both operands' scales 225 -> 187, 8192 x 8192 at 1100 (288) 119 -> 106, 11008 x 4096 at 2200 157 -> 138.  Beside
-// the line 13824 x 5120 at 2048 (320) 198 / 188 alone, but nothing in a whole 13B block, where the clock is what
-// the power allows (868 / 870 us), at 2300 207 / 204, 5120 x 5120 at 1900 79 / 77, 8192 x 5120 at 2048 122 / 125,
-// 13824 x 5120 at 3000 (480) 253 / 266.  Below 32 stages a piece is mostly its meeting (4096 x 11008 at 1024
-// 66 / 72).  A function of the shape alone: the cut shows in the sums' last bits.
+// of the chip idle, and for 10 % of the estimated time: layers of K -> N 13824 -> 5120 at 1692 tokens (280 tiles)
+// 192 -> 153 us, with both operands' scales 221 -> 173, 8192 -> 8192 at 1052 (288) 117 -> 98 and 134 -> 111, 11008 ->
+// 4096 at 2304 155 -> 129 and 179 -> 145.  Of 174 cells of 257 .. 416 tiles, either mode, the 48 that it takes
+// need 0.77 to 0.93 of the fastest other form's time.  Beside the line 13824 -> 5120 at 1948 (320) 192 / 174 and
+// 221 / 198 (a 13B block at 2048 876 / 865: there it is drawn too carefully), 8192 -> 10240 at 964 (320) 116 / 110 and
+// 134 / 122, at 1147 (360) 119 / 120 and 136 / 137, 5120 -> 5120 at 1920 (300) 77 / 71, at 2176 (340) 77 / 80, 4096 ->
+// 4096 at 2944 (368) 65 / 80.  Below 32 stages a piece is mostly its meeting.  A function of the shape alone: the cut shows in
+// the sums' last bits.
 bool group_pairs_pay(int M, int N, int K, size_t partial_bytes)
 {
     const int tiles = (M + 127) / 128 * ((N + 255) / 256), KT = K / FLEXQ_TILE_K, tail = tiles - kStreamKGrid;

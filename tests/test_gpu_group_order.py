@@ -115,9 +115,7 @@ def test_decode_from_fp16_and_from_codes(K, N, bits):
         assert np.array_equal(a.view(np.uint16), b.view(np.uint16)), M
 
 
-@pytest.mark.parametrize("both", [False, True])
-@pytest.mark.parametrize("cfg", [8, 18, 19])
-def test_scales_that_are_not_finite(cfg, both):
+def check_scales_that_are_not_finite(cfg, both):
     """A packed weight scale may be infinite or NaN: a group whose sum is not zero gives that
     sign's infinity, a zero sum NaN, and no other channel notices."""
     M, K, N = 130, 640, 288
@@ -136,7 +134,8 @@ def test_scales_that_are_not_finite(cfg, both):
     codes = (fq.quant_act_g128 if both else fq.quant_act)(to_dev(x16), 8)
     dev.set_dispatch(2, 1, 0, cfg)
     try:
-        got = call(packed, N, K, codes, both, 8, None).astype(np.float64)
+        got = call(packed, N, K, codes, both, 8, fq.make_workspace(M, N, K, extra=8 << 20)).astype(np.float64)
+        assert dev.last_dispatch()[0] == cfg
     finally:
         dev.set_dispatch()
     assert np.isposinf(want).any() and np.isneginf(want).any() and np.isnan(want).sum() >= M
@@ -144,6 +143,12 @@ def test_scales_that_are_not_finite(cfg, both):
     assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     fine = np.isfinite(want)
     assert np.allclose(got[fine], want[fine], rtol=2e-3, atol=2e-3)
+
+
+@pytest.mark.parametrize("both", [False, True])
+@pytest.mark.parametrize("cfg", [8, 18, 19])
+def test_scales_that_are_not_finite(cfg, both):
+    check_scales_that_are_not_finite(cfg, both)
 
 
 # exactly a round of 128-row tiles; more: several items per workgroup, then the 14 (8) behind the round,

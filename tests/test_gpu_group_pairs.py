@@ -10,7 +10,7 @@ import paper_2508_04405_amd as fq
 from paper_2508_04405_amd import dev, synth
 
 from gpu_helpers import assert_y_close, group_slack, say, to_dev
-from test_gpu_group_order import call, operands
+from test_gpu_group_order import call, check_scales_that_are_not_finite, operands
 from test_gpu_xgroup import assert_close, reference
 
 pytestmark = pytest.mark.gpu
@@ -74,6 +74,32 @@ def test_choice_and_equal_tokens(M, K, N, pairs, both):
     d = np.abs(y.astype(np.float64) - whole)
     assert d.max() <= 2.0 ** -10 * np.abs(whole).max()
     assert np.linalg.norm(d) <= 2.0 ** -13 * np.linalg.norm(whole)
+
+
+@pytest.mark.parametrize("both", [False, True])
+def test_scales_that_are_not_finite(both):
+    check_scales_that_are_not_finite(22, both)      # (infinities of both signs in different pieces among them)
+
+
+def test_in_the_block_runner():
+    """The output projection of a wide block takes the pairs: the bits of the layer called by itself."""
+    M, H, F, QKV = 1052, 8192, 128, 32
+    say("group pairs in the block runner")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    packed = [fq.pack_w6(*fq.quant_w6(torch.randn(s, generator=g, device="cuda") * 0.02, 128), 128)
+              for s in ((QKV, H), (H, H), (2 * F, H), (H, F))]
+    gain = torch.ones(H, dtype=torch.float16, device="cuda")
+    layer = fq.Layer(H, F, QKV, 128, *packed, gain, gain, 1e-5, (6, 6, 6, 8))
+    attn = to_dev(synth.activations(M, H, seed=9, outlier_frac=0.02))
+    o = torch.empty((M, H), dtype=torch.float16, device="cuda")
+    alone = dev.gemm_w6a6(packed[1], H, H, 128, x_fp16=attn)
+    assert dev.last_dispatch()[0] == 22
+    ws = layer.make_workspace(M)
+    for _ in range(2):
+        fq.layer_linears(layer, M, ws, 1, 1, attn=attn, o=o)
+        assert torch.equal(o, alone)
+    assert int(ws[:16384].view(torch.int32).abs().sum()) == 0
 
 
 def test_captured_and_replayed():
