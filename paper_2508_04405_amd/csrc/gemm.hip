@@ -694,7 +694,7 @@ hipError_t launch_gemm(const LinearArgs &a, int cfg, hipStream_t st, int *chosen
             const WldsChoice low = gemm_low_choose(a.M, a.N, a.K, a.partial_bytes);
             // (against 256-row tiles cut along K the low tiles must promise 12 %: the two
             // estimates are good to about 6 % each.  Too much at 129 to 256 tokens of a 10240 x 8192
-            // layer, which run at 33 to 35 us where low tiles in three pieces take 29.5 to 32.)
+            // layer, which run at 31.5 to 35.5 us where low tiles in three pieces take 29 to 32.)
             const bool take_low = low.us < t_best && low.us < (c.tail_form == 2 ? 0.88 : 1.0) * c.us;
             // 192-row tiles where 256 rows would be half padding (576 tokens of 15360 x 5120 53.0 ->
             // 46.8 us, 333 of 27648 x 5120 56.7 -> 50.1, 576 of 57344 x 8192 287 -> 253) or leave a quarter

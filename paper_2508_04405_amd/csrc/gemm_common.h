@@ -6,7 +6,7 @@
 
 namespace {
 
-constexpr int kNonTemporal = 2;        // cache policy of a buffer load whose bytes are used once
+constexpr int kNonTemporal = 2;        // cache policy of a buffer access past the caches
 
 // swizzled byte offset of 16-byte chunk c (0..7) of row `row` in a stage
 __device__ __forceinline__ int lds_off(int row, int c)

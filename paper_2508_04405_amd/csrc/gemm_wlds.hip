@@ -93,11 +93,12 @@ constexpr int WAVES = 8;
 // The outputs' stores in the last round of a launch go past the caches, those of the rounds before it do
 // not.  Nothing follows the last round, and the lines that it leaves in the caches are written back while the
 // chip waits: layers of K -> N 1536 -> 8960 at 1024 tokens 22.2 -> 20.4 us, 3584 -> 18944 at 300 28.1 -> 26.7, 8192 ->
-// 10240 at 1024 83.0 -> 81.6, 4096 -> 12288 at 333 with group scales 34.6 -> 33.9; of 500 cells of one round none is
-// slower by more than the 2 % that runs differ.  Before that a workgroup waits for its stores together with
-// its next item's first loads, and past the caches they take longer: 4096 -> 22016 at 1024 tokens with
-// group scales 126 / 129 us, 5120 -> 27648 with both operands' 215 / 220, 5248 -> 13664 at 1300 (a round and half
-// tiles) 102.6 / 104.5, a 13B block with group scales at 2048 845 / 858 (by this rule 847).
+// 10240 at 1024 83.0 -> 81.6, 4096 -> 12288 at 333 with group scales 34.6 -> 33.9; of 717 cells of one round the
+// mean is 0.99 and none is slower by more than single cells differ from run to run (2.5 %).  Before that a
+// workgroup waits for its stores together with its next item's first loads, and past the caches they take
+// longer: 4096 -> 22016 at 1024 tokens with group scales 126 / 129 us, 5120 -> 27648 with both operands' 215 / 220,
+// 5248 -> 13664 at 1300 (a round and half tiles) 102.6 / 104.5, a 13B block with group scales at 2048 850 / 863 (by
+// this rule 853).  Pairs of pieces, a few items a workgroup, count as a last round (0.997 of the time).
 constexpr int kLastRound = kNonTemporal;
 constexpr int SLOT_BYTES = 256 * 256 * 4;      // one workgroup's int32 sums of a 256x256 tile
 
@@ -886,7 +887,7 @@ __device__ __forceinline__ void run_items(const flexq::LinearArgs &a, uint8_t *l
             // 10240 at 160 34.1 -> 32.5, 16384 -> 6144 at 66 (low) 30.9 -> 29.8.  Several rows of low tiles send them all
             // the same: without, 14336 -> 4096 at 200 tokens takes 30.6 us instead of 28.4, 11008 -> 4096 at 150 26.4 /
             // 25.0, 4096 -> 4096 at 180 18.2 / 16.7 (why is not known: dealing the slabs that are left evenly to the
-            // pieces changes nothing), and left out of the additions alone they cost nothing on any of 315 cells.
+            // pieces changes nothing), and left out of the additions alone they cost nothing that shows on 315 cells.
             auto live = [&](int mt) {
                 if constexpr (GROUP != 0) return true;      // (those pad by less and gain nothing)
                 else return at.bm0 + (wm * MT + mt) * 32 < M;
